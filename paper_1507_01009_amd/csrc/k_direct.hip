@@ -2,18 +2,21 @@
 // (SMBH <-> stars; perturber <-> chain-member corrections), softening
 // max(eps_i, eps_j) per pair: Plummer, or the cubic spline with that h.
 //
-// Many targets (stars feeling the SMBHs): one thread per target takes every
-// source of its segment (or of a source chunk, combined in a second ordered
-// pass when targets are too few to fill the chip).  Few targets (SMBHs
-// feeling a million stars): one 256-thread block per (target, range of
-// kFewPerBlock sources), threads striding through the range with coalesced
-// loads, the block's sums combined in a fixed tree order and the per-block
-// partials summed in a second ordered pass.  Every sum is compensated
+// Many targets of one segment (checks of the tree's forces, perturbers on
+// perturbers): blocks of 64 or 128 targets over source tiles in LDS.  Few
+// targets (SMBHs feeling a million stars): one 256-thread block per (target,
+// range of kFewPerBlock sources), threads striding through the range with
+// coalesced loads, the block's sums combined in a fixed tree order and the
+// per-block partials summed in a second ordered pass.  Anything else
+// (several segments, a handful of pairs): one thread per target and source
+// chunk.  Every sum is compensated
 // (error-free TwoSum with a running correction), so the result does not
 // depend on the split beyond the last bit and is deterministic.  Every
 // operation is rounded on its own (no FMA contraction): the TwoSum steps
 // need it, and so does the fused drift-and-sum kernel, whose sums must equal
 // the unfused ones bit for bit.
+#include <type_traits>
+
 #include "tg_internal.h"
 
 namespace tg {
@@ -27,6 +30,19 @@ __device__ __forceinline__ int seg_of(const int64_t *off, int nseg, int64_t i) {
   return lo;
 }
 
+// 1 / sqrt(x) to about one unit in the last place: the hardware estimate and
+// one third-order step.  A rounded square root and division (1 / sqrt(x),
+// also about one unit) cost some 25 instructions more per pair; they stay
+// for everything but positive normal numbers (x = 0 of unsoftened coincident
+// pairs, subnormals, infinities, NaN).
+__device__ __forceinline__ double inv_sqrt(double x) {
+  constexpr int kPositiveNormal = 0x100;
+  if (__builtin_expect(!__builtin_amdgcn_class(x, kPositiveNormal), 0)) return 1.0 / sqrt(x);
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-(x * y), y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
 // m/r and m/r^3 with the pair's softening ep (soft: cubic spline, h = ep).
 __device__ __forceinline__ void pair_terms(double dx, double dy, double dz, double ep, double m,
                                            int soft, double &mD1, double &mD3) {
@@ -37,8 +53,7 @@ __device__ __forceinline__ void pair_terms(double dx, double dy, double dz, doub
     mD1 = m * p0;
     mD3 = m * p1;
   } else {
-    const double r2 = dx * dx + dy * dy + dz * dz + ep * ep;
-    const double D1 = 1.0 / sqrt(r2);
+    const double D1 = inv_sqrt(dx * dx + dy * dy + dz * dz + ep * ep);
     mD1 = m * D1;
     mD3 = mD1 * D1 * D1;
   }
@@ -89,6 +104,147 @@ __global__ void k_direct(const double *__restrict__ spos, const double *__restri
       o[0] = ax.s; o[1] = ax.c; o[2] = ay.s; o[3] = ay.c;
       o[4] = az.s; o[5] = az.c; o[6] = ph.s; o[7] = ph.c;
     }
+  }
+}
+
+// Many targets of one segment: a block of four waves takes 64 kT targets
+// (kT to a lane) and one chunk of the sources, staged kTileSrc at a time in
+// LDS; each wave sums its quarter of a tile onto all the block's targets,
+// and the four waves' sums are combined in order at the end.  A source is
+// read from memory once per block and from LDS as a broadcast; the next
+// tile's loads are in flight while a tile is summed.  Bound by FP64 issue:
+// about 50 instructions per pair, 28 of them the compensated sums.  Two
+// targets to a lane: with one the LDS reads set the rate (3.7e11 pairs/s on
+// 65536 x 65536), with three and four the lanes' sums leave too few waves
+// (5.0e11, 5.2e11); two reach 6.1e11 (2.0e11 with one thread per target and
+// every source read from memory by every thread).  8191 targets on 262144
+// sources: 13.9 -> 3.9 ms.
+constexpr int kTileSrc = 256;
+
+template <int kT, bool kSelf, bool kSoft>
+__global__ __launch_bounds__(256) void k_direct_tile(
+    const double *__restrict__ spos, const double *__restrict__ sm,
+    const double *__restrict__ seps, double seps_all, int64_t ns,
+    const double *__restrict__ tpos, const double *__restrict__ teps, int64_t nt,
+    int64_t chunk, int accumulate, double *__restrict__ acc, double *__restrict__ pot,
+    double *__restrict__ part) {
+#pragma clang fp contract(off)
+  constexpr int kW = kTileSrc / 64;
+  __shared__ double4 s_xm[kTileSrc];
+  __shared__ double s_e[kTileSrc];
+  __shared__ double2 s_sum[kW - 1][4 * kT][64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t i0 = (int64_t)blockIdx.x * (64 * kT) + lane;
+  const int64_t j0 = (int64_t)blockIdx.y * chunk, j1 = min(ns, j0 + chunk);
+  double xi[kT], yi[kT], zi[kT], ei[kT];
+#pragma unroll
+  for (int k = 0; k < kT; ++k) {
+    const int64_t i = min(i0 + 64 * k, nt - 1);     // lanes past the end repeat the last target
+    xi[k] = tpos[3 * i]; yi[k] = tpos[3 * i + 1]; zi[k] = tpos[3 * i + 2];
+    ei[k] = teps[i];
+  }
+  CSum r[kT][4];
+  double4 nx = make_double4(0.0, 0.0, 0.0, 0.0);
+  double ne = 0.0;
+  auto load = [&](int64_t j) {
+    if (j < j1) {
+      nx = make_double4(spos[3 * j], spos[3 * j + 1], spos[3 * j + 2], sm[j]);
+      ne = seps ? seps[j] : seps_all;
+    }
+  };
+  load(j0 + tid);
+  for (int64_t t0 = j0; t0 < j1; t0 += kTileSrc) {
+    s_xm[tid] = nx;
+    s_e[tid] = ne;
+    __syncthreads();
+    load(t0 + kTileSrc + tid);
+    const int m = __builtin_amdgcn_readfirstlane((int)min<int64_t>(64, j1 - t0 - 64 * w));
+#pragma unroll 2
+    for (int q = 0; q < m; ++q) {
+      const double4 s = s_xm[64 * w + q];
+      const double es = s_e[64 * w + q];
+#pragma unroll
+      for (int k = 0; k < kT; ++k) {
+        const double dx = xi[k] - s.x, dy = yi[k] - s.y, dz = zi[k] - s.z;
+        double mD1, mD3;
+        pair_terms(dx, dy, dz, fmax(es, ei[k]), s.w, kSoft, mD1, mD3);
+        if constexpr (kSelf) {
+          const bool own = t0 + 64 * w + q == i0 + 64 * k;   // its own pair adds zeros
+          mD1 = own ? 0.0 : mD1;
+          mD3 = own ? 0.0 : mD3;
+        }
+        r[k][0].add(-mD3 * dx);
+        r[k][1].add(-mD3 * dy);
+        r[k][2].add(-mD3 * dz);
+        r[k][3].add(-mD1);
+      }
+    }
+    __syncthreads();
+  }
+  if (w > 0) {
+#pragma unroll
+    for (int k = 0; k < kT; ++k)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) s_sum[w - 1][4 * k + c][lane] = make_double2(r[k][c].s, r[k][c].c);
+  }
+  __syncthreads();
+  if (w > 0) return;
+#pragma unroll
+  for (int k = 0; k < kT; ++k) {
+    const int64_t i = i0 + 64 * k;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+#pragma unroll
+      for (int q = 0; q < kW - 1; ++q) {
+        const double2 o = s_sum[q][4 * k + c][lane];
+        r[k][c].add(o.x);
+        r[k][c].c += o.y;
+      }
+    }
+    if (i >= nt) continue;
+    if (gridDim.y == 1) {
+      const double a0 = r[k][0].get(), a1 = r[k][1].get(), a2 = r[k][2].get(), p = r[k][3].get();
+      if (accumulate) {
+        acc[3 * i] += a0; acc[3 * i + 1] += a1; acc[3 * i + 2] += a2;
+        if (pot) pot[i] += p;
+      } else {
+        acc[3 * i] = a0; acc[3 * i + 1] = a1; acc[3 * i + 2] = a2;
+        if (pot) pot[i] = p;
+      }
+    } else {
+      double *o = part + 8 * (size_t)(blockIdx.y * nt + i);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) { o[2 * c] = r[k][c].s; o[2 * c + 1] = r[k][c].c; }
+    }
+  }
+}
+
+// The chunks' partial sums of a target added in order by one thread (few
+// chunks, many targets).
+__global__ __launch_bounds__(64) void k_direct_chunks(int64_t nt, int nchunks, int accumulate,
+                                                      const double *__restrict__ part,
+                                                      double *__restrict__ acc,
+                                                      double *__restrict__ pot) {
+#pragma clang fp contract(off)
+  const int64_t i = blockIdx.x * (int64_t)64 + threadIdx.x;
+  if (i >= nt) return;
+  CSum r[4];
+  for (int c = 0; c < nchunks; ++c) {
+    const double *o = part + 8 * (size_t)(c * nt + i);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      r[k].add(o[2 * k]);
+      r[k].c += o[2 * k + 1];
+    }
+  }
+  const double v0 = r[0].get(), v1 = r[1].get(), v2 = r[2].get(), v3 = r[3].get();
+  if (accumulate) {
+    acc[3 * i] += v0; acc[3 * i + 1] += v1; acc[3 * i + 2] += v2;
+    if (pot) pot[i] += v3;
+  } else {
+    acc[3 * i] = v0; acc[3 * i + 1] = v1; acc[3 * i + 2] = v2;
+    if (pot) pot[i] = v3;
   }
 }
 
@@ -244,8 +400,13 @@ __global__ __launch_bounds__(256) void k_drift_smbh(
 // Whether sums of n sources on nt targets take the few-target path of
 // launch_direct (part_cap doubles of partials; the star sums on the SMBHs
 // that take it may be fused with the drift).
+// Up to kFewTargets targets: 262144 sources on 64 targets take 47 us against
+// 73 in the tiled kernel (half of whose lanes idle there), on 128 targets 83
+// against 70.
+constexpr int64_t kFewTargets = 127;
+
 static bool few_path(int64_t part_cap, int64_t n, int64_t nt) {
-  if (!(nt <= 4096 && n >= 2 * kFewPerBlock)) return false;
+  if (!(nt <= kFewTargets && n >= 2 * kFewPerBlock)) return false;
   const int64_t bpt = (n + kFewPerBlock - 1) / kFewPerBlock;
   return bpt * nt * 8 <= part_cap && bpt <= 65535;
 }
@@ -275,6 +436,53 @@ hipError_t launch_drift_smbh(tg_ctx *c, double *pos, const double *vel, const ui
   return hipGetLastError();
 }
 
+template <int kT, bool kSelf, bool kSoft>
+static void launch_tile_kernel(const DirectEnv &e, const double *spos, const double *sm,
+                               const double *seps, double seps_all, int64_t ns,
+                               const double *tpos, const double *teps, int64_t nt, int64_t nchunks,
+                               int64_t chunk, int accumulate, double *acc, double *pot) {
+  const dim3 grid((unsigned)((nt + 64 * kT - 1) / (64 * kT)), (unsigned)nchunks);
+  hipLaunchKernelGGL((k_direct_tile<kT, kSelf, kSoft>), grid, dim3(256), 0, e.stream, spos, sm,
+                     seps, seps_all, ns, tpos, teps, nt, chunk, accumulate, acc, pot, e.part);
+}
+
+// The tiled kernel's split: chunks of whole tiles, enough for kTileBlocks
+// blocks (eight per CU, two rounds of those resident) where the partial sums
+// fit.  One target to a lane where two would give less than a block per CU
+// (1000 targets on 1000 sources: 19.5 against 26.7 us).
+constexpr int64_t kTileBlocks = 2048;
+
+static hipError_t launch_tiles(const DirectEnv &e, const double *spos, const double *sm,
+                               const double *seps, double seps_all, int64_t ns,
+                               const double *tpos, const double *teps, int64_t nt,
+                               int self_pairs, int accumulate, double *acc, double *pot) {
+  const int64_t tiles = (ns + kTileSrc - 1) / kTileSrc;
+  const bool two = (nt + 127) / 128 * tiles >= 256;
+  const int64_t bx = two ? (nt + 127) / 128 : (nt + 63) / 64;
+  int64_t nchunks = std::min((kTileBlocks + bx - 1) / bx, tiles);
+  nchunks = std::max<int64_t>(1, std::min(nchunks, e.part_cap / (8 * nt)));
+  const int64_t chunk = (tiles + nchunks - 1) / nchunks * kTileSrc;
+  nchunks = (ns + chunk - 1) / chunk;
+  auto go = [&](auto self, auto soft) {
+    constexpr bool kSelf = decltype(self)::value, kSoft = decltype(soft)::value;
+    (two ? launch_tile_kernel<2, kSelf, kSoft> : launch_tile_kernel<1, kSelf, kSoft>)(
+        e, spos, sm, seps, seps_all, ns, tpos, teps, nt, nchunks, chunk, accumulate, acc, pot);
+  };
+  const std::true_type yes;
+  const std::false_type no;
+  if (self_pairs && e.soft) go(yes, yes);
+  else if (self_pairs) go(yes, no);
+  else if (e.soft) go(no, yes);
+  else go(no, no);
+  if (nchunks > 64)       // a block per target (300 targets: 800 chunks)
+    hipLaunchKernelGGL(k_direct_reduce, dim3((unsigned)std::min<int64_t>(nt, 4096)), dim3(256), 0,
+                       e.stream, nt, (int)nchunks, accumulate, e.part, acc, pot);
+  else if (nchunks > 1)
+    hipLaunchKernelGGL(k_direct_chunks, dim3((unsigned)((nt + 63) / 64)), dim3(64), 0, e.stream,
+                       nt, (int)nchunks, accumulate, e.part, acc, pot);
+  return hipGetLastError();
+}
+
 hipError_t launch_direct_env(const DirectEnv &e, const int64_t *dseg, const double *spos,
                              const double *sm, const double *seps, double seps_all,
                              const double *tpos, const double *teps, int64_t nt, int nseg,
@@ -290,6 +498,11 @@ hipError_t launch_direct_env(const DirectEnv &e, const int64_t *dseg, const doub
                        dim3(256), 0, e.stream, nt, (int)bpt, accumulate, e.part, acc, pot);
     return hipGetLastError();
   }
+  // one segment: tiles, from a wave of targets and of sources on (fewer pairs
+  // than that are one launch of the kernel below either way)
+  if (nseg == 1 && nt >= 64 && max_seg_src >= 64)
+    return launch_tiles(e, spos, sm, seps, seps_all, max_seg_src, tpos, teps, nt, self_pairs,
+                        accumulate, acc, pot);
   // aim for >= 2^16 independent (target, chunk) sums; with part_cap >= 2^19
   // doubles the partials of nt < 2^16 targets always fit at some chunk
   int64_t nchunks = 1, chunk = std::max<int64_t>(max_seg_src, 1);
