@@ -1,8 +1,9 @@
 // Active groups, the group tree walk with the opening-angle
 // test, and the softened P2P / quadrupole P2M force sums.
 //
-// One 64-lane wavefront owns one group of targets at a time (persistent
-// grid, groups taken from per-XCD queues).  The walk is breadth first: the
+// One 64-lane wavefront owns one group of targets at a time, or one part of a
+// group's sources where there are few groups (persistent grid, items taken
+// from per-XCD queues).  The walk is breadth first: the
 // frontier holds the cells opened on the level above as ranges of
 // consecutive children, and the wave tests the children of eight of them at
 // once (eight lanes each) against the group's box,
@@ -81,6 +82,12 @@ struct WalkArgs {
   const uint32_t *perm;
   TreeCounters *ctr;
   unsigned long long *wtot;   // force walk: per workgroup {P2P, P2M, targets, groups}
+  const uint2 *items;         // force walk: {group, part | (parts - 1) << 5 | first slot << 10}
+  uint32_t item_gap;          // extra entries of each queue's range of items
+  const uint2 *slots;         // split groups: {group, parts} at the slot of part 0
+  double4 *wpart;             // partial results of split groups [slot][stride]
+  uint32_t stride;
+  uint32_t starts;            // blocks that start with an item of their own
   uint32_t *err;
   uint32_t *frontier;
   int fcap;
@@ -110,6 +117,14 @@ __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t &tot) {
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
   tot = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
   return x - v;
+}
+
+// LDS written by some lanes of a wave, read by others of the same wave: a
+// wave's LDS accesses execute in order, so only the compiler has to keep it.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Squared distance from the group box to the centre of mass, the same
@@ -362,17 +377,13 @@ template <> union __align__(16) TileMem<false> {
   double red[kRedT<false> * 256];
 };
 
-// ------------------------------------------------------- force-mode sink
+// ------------------------------------------- one wave's tiles and targets
 template <bool kMixed, bool kSpline>
-struct ForceSink {
+struct Eval {
   using R = typename std::conditional<kMixed, float, double>::type;
   using R4 = typename Vec4<R>::T;
   static constexpr int kMaxT = Shape<kMixed, kSpline>::kMaxT;
-  uint32_t *s_m;
-  uint32_t *s_q;
   TileMem<kMixed> *tile;
-  uint32_t nm, nq;
-  unsigned long long cells, parts;   // wave-uniform totals
   int T, lt, slices, tfull, F, my_s;
   double cgx, cgy, cgz;              // coordinate origin of the group (0 in FP64)
   R e2;
@@ -388,6 +399,53 @@ struct ForceSink {
   // per-target totals in FP64 (mixed: each tile's FP32 partial sums are
   // added here, so rounding accumulates only within a tile)
   double hax[kMaxT], hay[kMaxT], haz[kMaxT], hph[kMaxT];
+
+  // The lane shape and targets of a group (box lo, hi) whose active targets
+  // are listed in tgt[0, n): T targets per lane (at least ceil(n / 64)), lt
+  // lane-targets, slices source slices; minimise T / slices.  Ties go to the
+  // larger T (fewer tile reads per pair), except that in mixed precision
+  // three targets to a lane are taken only where they evaluate strictly
+  // fewer pairs: measured on the 1M cusp, ties between two and three ran
+  // slower with three.
+  __device__ __forceinline__ void init(const WalkArgs &A, uint4 gr, const double lo[3],
+                                       const double hi[3], const uint32_t *tgt, int n) {
+    const unsigned lane = lane_id();
+    T = (n + 63) / 64;
+    lt = (n + T - 1) / T;
+    slices = 64 / lt;
+#pragma unroll
+    for (int t = 2; t <= kMaxT; ++t) {
+      if (t <= T) continue;
+      const int l2 = (n + t - 1) / t, s2 = 64 / l2;
+      const bool better = (kMixed && t >= 3) ? t * slices < T * s2 : t * slices <= T * s2;
+      if (better) { T = t; lt = l2; slices = s2; }
+    }
+    g0 = gr.x; gn = gr.y; own0 = own1 = 0ull;
+    s_tgt = tgt; nt = n;
+    tfull = 128 / slices;
+    F = slices * tfull;
+    const int j = (int)lane % lt;
+    const int sl = (int)lane / lt;
+    my_s = sl < slices ? sl : 0;             // idle lanes shadow slice 0 (discarded)
+    if constexpr (kMixed) {
+      cgx = 0.5 * (lo[0] + hi[0]);
+      cgy = 0.5 * (lo[1] + hi[1]);
+      cgz = 0.5 * (lo[2] + hi[2]);
+    } else {
+      cgx = cgy = cgz = 0.0;
+    }
+    e2 = (R)A.eps2;
+    h = (R)A.eps;
+    ih = (R)(1.0 / A.eps);
+#pragma unroll
+    for (int k = 0; k < kMaxT; ++k) {
+      // lane-target j holds targets j, j + lt, ...; missing ones repeat j
+      const int i = j + k * lt;
+      const double4 p = A.spart[tgt[i < n ? i : j]];
+      tx[k] = (R)(p.x - cgx); ty[k] = (R)(p.y - cgy); tz[k] = (R)(p.z - cgz);
+      hax[k] = hay[k] = haz[k] = hph[k] = 0.0;
+    }
+  }
 
   __device__ void add(int k, R ax, R ay, R az, R ph) {
     hax[k] += (double)ax; hay[k] += (double)ay; haz[k] += (double)az; hph[k] += (double)ph;
@@ -485,22 +543,27 @@ struct ForceSink {
     }
   }
 
-  __device__ void flush_p2m(const WalkArgs &A, const uint32_t *list, int k) {
+  // k cells, lane l holding the ids of entries l and l + 64
+  __device__ void tile_p2m(const WalkArgs &A, uint32_t v0, uint32_t v1, int k) {
     const int lane = (int)lane_id();
     const int trips = trips_for(k);
     const int ne = slices * trips;
     const int e0 = lane, e1 = lane + 64;
-    const uint32_t v0 = e0 < k ? list[e0] : 0u, v1 = e1 < k ? list[e1] : 0u;
     if (e0 < ne) stage_cell(A, e0, e0 < k, v0);
     if (e1 < ne) stage_cell(A, e1, e1 < k, v1);
-    __syncthreads();
+    wave_sync();
     const int base = my_s;
     if (T == 1) eval_m<1>(base, trips, slices);
     else if constexpr (kMaxT >= 2) {
       if (T == 2) eval_m<2>(base, trips, slices);
       else if constexpr (kMaxT >= 3) eval_m<3>(base, trips, slices);
     }
-    __syncthreads();
+    wave_sync();
+  }
+
+  __device__ void flush_p2m(const WalkArgs &A, const uint32_t *list, int k) {
+    const int e0 = (int)lane_id(), e1 = e0 + 64;
+    tile_p2m(A, e0 < k ? list[e0] : 0u, e1 < k ? list[e1] : 0u, k);
   }
 
   __device__ void stage_part(const WalkArgs &A, int e, bool live, uint32_t j) {
@@ -512,22 +575,27 @@ struct ForceSink {
     tile->p[e] = v;
   }
 
-  __device__ void flush_p2p(const WalkArgs &A, const uint32_t *list, int k) {
+  // k particles, lane l holding the indices of entries l and l + 64
+  __device__ void tile_p2p(const WalkArgs &A, uint32_t j0, uint32_t j1, int k) {
     const int lane = (int)lane_id();
     const int trips = trips_for(k);
     const int ne = slices * trips;
     const int e0 = lane, e1 = lane + 64;
-    const uint32_t j0 = e0 < k ? list[e0] : 0u, j1 = e1 < k ? list[e1] : 0u;
     if (e0 < ne) stage_part(A, e0, e0 < k, j0);
     if (e1 < ne) stage_part(A, e1, e1 < k, j1);
-    __syncthreads();
+    wave_sync();
     const int base = my_s;
     if (T == 1) eval_p<1>(base, trips, slices);
     else if constexpr (kMaxT >= 2) {
       if (T == 2) eval_p<2>(base, trips, slices);
       else if constexpr (kMaxT >= 3) eval_p<3>(base, trips, slices);
     }
-    __syncthreads();
+    wave_sync();
+  }
+
+  __device__ void flush_p2p(const WalkArgs &A, const uint32_t *list, int k) {
+    const int e0 = (int)lane_id(), e1 = e0 + 64;
+    tile_p2p(A, e0 < k ? list[e0] : 0u, e1 < k ? list[e1] : 0u, k);
   }
 
   // rank among the own particles of bit b (b < 128)
@@ -544,7 +612,7 @@ struct ForceSink {
   // One tile of the kq queued particles s_q[0, kq) followed by the own
   // particles of ranks [o, o + k) at entries kq + rank - o, each target
   // without itself.
-  __device__ void flush_own(const WalkArgs &A, int kq, uint32_t o, int k) {
+  __device__ void flush_own(const WalkArgs &A, const uint32_t *s_q, int kq, uint32_t o, int k) {
     const uint32_t lane = lane_id();
     const int trips = trips_for(kq + k);
     const int ne = slices * trips;
@@ -565,14 +633,68 @@ struct ForceSink {
       const uint32_t b = s_tgt[i < nt ? i : j] - g0;   // < gn: targets lie in the group
       et[q] = own_bit(b) ? own_rank(b) - o + (uint32_t)kq : 0xffffffffu;
     }
-    __syncthreads();
+    wave_sync();
     const int base = my_s;
     if (T == 1) eval_p<1, true>(base, trips, slices, et);
     else if constexpr (kMaxT >= 2) {
       if (T == 2) eval_p<2, true>(base, trips, slices, et);
       else if constexpr (kMaxT >= 3) eval_p<3, true>(base, trips, slices, et);
     }
-    __syncthreads();
+    wave_sync();
+  }
+
+  // Marks of the group's own particles in the leaf [f, f + c) of the lanes
+  // of `omask` (own part [oa, ob)); rare, one leaf after another.
+  __device__ void mark_own(unsigned long long omask, uint32_t oa, uint32_t ob) {
+    while (omask) {
+      const int L = __ffsll((long long)omask) - 1;
+      omask &= omask - 1ull;
+      const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)oa, L) - g0;
+      const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)ob, L) - g0;
+      own0 |= bits_below(b) & ~bits_below(a);                 // b <= gn <= 128
+      own1 |= bits_below(b - min(b, 64u)) & ~bits_below(a - min(a, 64u));
+    }
+  }
+
+  // the lowest n bits (all of them from 64 on)
+  __device__ static unsigned long long bits_below(uint32_t n) {
+    return n >= 64u ? ~0ull : (1ull << n) - 1ull;
+  }
+
+  __device__ uint32_t own_count() const {
+    return (uint32_t)(__popcll(own0) + __popcll(own1));
+  }
+
+  // per-lane totals -> LDS, [k][lane][4]
+  __device__ void store_red() {
+    double *red = tile->red;
+    const int lane = (int)lane_id();
+#pragma unroll
+    for (int k = 0; k < kMaxT; ++k) {
+      double *o = red + 4 * (64 * k + lane);
+      o[0] = hax[k]; o[1] = hay[k]; o[2] = haz[k]; o[3] = hph[k];
+    }
+  }
+};
+
+// ------------------------------------------------------- force-mode sink
+// The lists of a group; an item that is one of several parts of a group
+// evaluates every parts-th tile.
+template <bool kMixed, bool kSpline>
+struct ForceSink : Eval<kMixed, kSpline> {
+  using E = Eval<kMixed, kSpline>;
+  using E::F; using E::g0; using E::gn; using E::own0; using E::own1;
+  using E::flush_p2m; using E::flush_p2p; using E::flush_own;
+  uint32_t *s_m;
+  uint32_t *s_q;
+  uint32_t nm, nq;
+  unsigned long long cells, parts;   // wave-uniform totals
+  int turn, parts_;                  // tiles until this item's next one; the group's parts
+
+  __device__ bool my_turn() {
+    const bool mine = turn == 0;
+    turn = mine ? parts_ - 1 : turn - 1;
+    return mine;
   }
 
   // Queue the particles [lf, lf + lc), flushing whenever a tile is full.
@@ -583,7 +705,7 @@ struct ForceSink {
       for (uint32_t j = lane_id(); j < take; j += 64u) s_q[nq + j] = lf + o + j;
       nq += take;
       o += take;
-      __syncthreads();
+      wave_sync();
       drain_q(A);
     }
   }
@@ -595,16 +717,16 @@ struct ForceSink {
     const uint32_t c = (uint32_t)__popcll(mask);
     nm += c;
     cells += c;
-    __syncthreads();
+    wave_sync();
     if (nm >= (uint32_t)F) {          // nm < F + 64 <= 2 F: one flush
-      flush_p2m(A, s_m + (nm - F), F);
+      if (my_turn()) flush_p2m(A, s_m + (nm - F), F);
       nm -= F;
     }
   }
 
   __device__ void drain_q(const WalkArgs &A) {
     while (nq >= (uint32_t)F) {
-      flush_p2p(A, s_q + (nq - F), F);
+      if (my_turn()) flush_p2p(A, s_q + (nq - F), F);
       nq -= F;
     }
   }
@@ -626,16 +748,7 @@ struct ForceSink {
     const unsigned long long omask = __ballot(ob > oa);
     if (omask != 0ull) {
       // rare (the group's own leaves): mark them, queue the rest
-      unsigned long long m = omask;
-      while (m) {
-        const int L = __ffsll((long long)m) - 1;
-        m &= m - 1ull;
-        const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)oa, L) - g0;
-        const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)ob, L) - g0;
-        for (uint32_t q = a; q < b; ++q) {     // at most gn <= 128 bits in all
-          if (q < 64u) own0 |= 1ull << q; else own1 |= 1ull << (q - 64u);
-        }
-      }
+      this->mark_own(omask, oa, ob);
       pre = wave_excl_scan(c - (ob - oa), tot);
     }
     const uint32_t left = oa - f, right = f + c - ob;
@@ -643,7 +756,7 @@ struct ForceSink {
       for (uint32_t k = 0; k < left; ++k) s_q[nq + pre + k] = f + k;
       for (uint32_t k = 0; k < right; ++k) s_q[nq + pre + left + k] = ob + k;
       nq += tot;
-      __syncthreads();
+      wave_sync();
       drain_q(A);
       return;
     }
@@ -658,14 +771,14 @@ struct ForceSink {
   }
 
   __device__ void finish(const WalkArgs &A) {
-    if (nm > 0) flush_p2m(A, s_m, (int)nm);
+    if (nm > 0 && my_turn()) flush_p2m(A, s_m, (int)nm);
     nm = 0;
     // the queue's rest (nq < F) and the own particles share the last tiles
-    const uint32_t no = (uint32_t)(__popcll(own0) + __popcll(own1));
+    const uint32_t no = this->own_count();
     uint32_t o = 0;
     while (nq + (no - o) > 0u) {
       const uint32_t k = min(no - o, (uint32_t)F - nq);
-      flush_own(A, (int)nq, o, (int)k);
+      if (my_turn()) flush_own(A, s_q, (int)nq, o, (int)k);
       nq = 0;
       o += k;
     }
@@ -710,16 +823,17 @@ struct FillSink {
 // child k of cell j, so an opened cell is pushed with one store and no
 // per-child loop.  The walk starts from the range {root, 1}.  Returns false
 // if the frontier overflowed (the group's results are then invalid).
+// wave: its number in the grid (its part of the frontier's memory).
 template <bool kRel, class Sink>
-__device__ bool traverse(const WalkArgs &A, Sink &sink, uint32_t root,
+__device__ bool traverse(const WalkArgs &A, Sink &sink, uint32_t wave, uint32_t root,
                          const double lo[3], const double hi[3], double arel) {
   const unsigned lane = lane_id();
   const uint32_t cap = (uint32_t)A.fcap >> 1;     // ranges per half (two words each)
-  uint2 *cur = reinterpret_cast<uint2 *>(A.frontier + (size_t)blockIdx.x * 2 * A.fcap);
+  uint2 *cur = reinterpret_cast<uint2 *>(A.frontier + (size_t)wave * 2 * A.fcap);
   uint2 *nxt = cur + cap;
   if (lane == 0) cur[0] = make_uint2(root, 1u);
   __threadfence_block();
-  __syncthreads();
+  wave_sync();
   uint32_t fsize = 1;
   const uint32_t kk = lane & 7u;
   while (fsize > 0) {
@@ -761,7 +875,7 @@ __device__ bool traverse(const WalkArgs &A, Sink &sink, uint32_t root,
       nf += no;
     }
     __threadfence_block();
-    __syncthreads();
+    wave_sync();
     uint2 *tmp = cur;
     cur = nxt;
     nxt = tmp;
@@ -795,7 +909,100 @@ struct GroupQueue {
   }
 };
 
+// The force walk's queues: range q of the items starts at q G / 8 plus q
+// gaps (G active groups; the gap is room for the parts of split groups) and
+// holds n[q] items.  Workgroups are dispatched to the XCDs round robin:
+// block b < starts begins with item b / 8 of queue b mod 8, then drains that
+// queue through its counter (which counts from the last start) and helps
+// the others.  A queue that the starts exhaust is never asked: with few
+// items, thousands of waves asking eight counters each had delayed the ones
+// with work.
+struct ItemQueue {
+  uint32_t q, tried;
+  bool started;
+  __device__ explicit ItemQueue(uint32_t starts)
+      : q(blockIdx.x & 7u), tried(0), started(blockIdx.x >= starts) {}
+  __device__ bool next(const WalkArgs &A, uint32_t G, uint32_t &at) {
+    TreeCounters *ctr = A.ctr;
+    while (tried < 8u) {
+      const uint32_t n = ctr->q_items[q], starts = (A.starts - q + 7u) >> 3;
+      uint32_t i = blockIdx.x >> 3;
+      if (started) {
+        i = n;
+        if (n > starts) {
+          if (lane_id() == 0) i = starts + atomicAdd(&ctr->xq[kQueueStride * q], 1u);
+          // every lane is active here: the first lane is lane 0, and the item
+          // (with all that is loaded from it) is known to be uniform
+          i = (uint32_t)__builtin_amdgcn_readfirstlane((int)i);
+        }
+      }
+      started = true;
+      if (i < n) {
+        at = (uint32_t)(((uint64_t)q * G) >> 3) + q * A.item_gap + i;
+        return true;
+      }
+      if (n <= starts || i >= n) {
+        q = (q + 1u) & 7u;
+        ++tried;
+      }
+    }
+    return false;
+  }
+};
+
 // ------------------------------------------------------------ force kernel
+// The active targets of a group, compacted into s_tgt in order by one wave.
+__device__ __forceinline__ int active_targets(const WalkArgs &A, uint4 gr, uint32_t *s_tgt) {
+  const uint32_t lane = lane_id();
+  int nt = 0;
+  for (uint32_t c0 = 0; c0 < gr.y; c0 += 64u) {
+    const bool act = c0 + lane < gr.y && A.sact[gr.x + c0 + lane];
+    const unsigned long long amask = __ballot(act);
+    if (act) s_tgt[nt + lanes_below(amask)] = gr.x + c0 + lane;
+    nt += __popcll(amask);
+  }
+  return nt;
+}
+
+// The result of sorted target r_t of system sys: the tree's sums (NaN after
+// a failed walk) and the SMBH terms (FP64 in both precision modes).
+template <bool kSpline>
+__device__ __forceinline__ void store_target(const WalkArgs &A, uint32_t sys, uint32_t r_t,
+                                             double ax, double ay, double az, double ph) {
+  const double4 p = A.spart[r_t];
+  const uint32_t orig = A.perm[r_t];
+  double ex = 0.0, ey = 0.0, ez = 0.0, ep = 0.0;
+  if (A.ext_seg) {
+    for (int32_t e = A.ext_seg[sys]; e < A.ext_seg[sys + 1]; ++e) {
+      const double es = fmax(A.eps, A.ext_eps[e]);
+      const double dx = p.x - A.ext_pos[3 * e], dy = p.y - A.ext_pos[3 * e + 1],
+                   dz = p.z - A.ext_pos[3 * e + 2];
+      double mD1, mD3;
+      if constexpr (kSpline) {
+        double p0, p1;
+        spline_pair_dp(sqrt(dx * dx + dy * dy + dz * dz), es, p0, p1);
+        mD1 = A.ext_mass[e] * p0;
+        mD3 = A.ext_mass[e] * p1;
+      } else {
+        const double r2 = dx * dx + dy * dy + dz * dz + es * es;
+        const double D1 = 1.0 / sqrt(r2);
+        mD1 = A.ext_mass[e] * D1;
+        mD3 = mD1 * D1 * D1;
+      }
+      ex -= mD3 * dx; ey -= mD3 * dy; ez -= mD3 * dz; ep -= mD1;
+    }
+  }
+  A.acc[3 * (size_t)orig + 0] = A.G * (ax + ex);
+  A.acc[3 * (size_t)orig + 1] = A.G * (ay + ey);
+  A.acc[3 * (size_t)orig + 2] = A.G * (az + ez);
+  if (A.pot) A.pot[orig] = A.G * (ph + ep);
+}
+
+// One wave takes one item at a time: a group, or one of the parts of a group
+// that was split to give every wave several items of about the same work.
+// Each part makes the whole walk and evaluates every parts-th tile, so
+// lists, tiles and the sums inside a tile are those of the unsplit group;
+// the parts' FP64 totals are added in order by k_walk_finish.
 template <bool kMixed, bool kRel, bool kSpline>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kMixed ? TG_WALK_WAVES_MIXED : TG_WALK_WAVES_FP64)))
 void k_walk_forces(const int32_t *__restrict__ gate, WalkArgs A) {
@@ -805,126 +1012,52 @@ void k_walk_forces(const int32_t *__restrict__ gate, WalkArgs A) {
   __shared__ uint32_t s_q[kQCap];
   __shared__ TileMem<kMixed> tile;
   using Sink = ForceSink<kMixed, kSpline>;
-  using R = typename Sink::R;
-  constexpr int kMaxT = Sink::kMaxT;
   const unsigned lane = lane_id();
   const uint32_t n_groups = A.ctr->n_active_groups;
   unsigned long long tot_p2p = 0, tot_p2m = 0, tot_t = 0, tot_g = 0;
-  GroupQueue Q(blockIdx.x);
-  for (;;) {
-    const uint32_t gi = Q.next(A.ctr, n_groups);
-    if (gi >= n_groups) break;
-    const uint32_t g = A.alist[gi];
+  ItemQueue Q(A.starts);
+  uint32_t at;
+  while (Q.next(A, n_groups, at)) {
+    const uint2 item = A.items[at];
+    const uint32_t g = item.x;
+    const uint32_t part = item.y & 31u, parts = ((item.y >> 5) & 31u) + 1u;
     const uint4 gr = A.groups[g];
     double lo[3], hi[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) { lo[k] = A.abox[6 * (size_t)g + k]; hi[k] = A.abox[6 * (size_t)g + 3 + k]; }
-    // compact the active targets of the group
-    int nt = 0;
-    for (uint32_t c0 = 0; c0 < gr.y; c0 += 64u) {
-      const bool act = c0 + lane < gr.y && A.sact[gr.x + c0 + lane];
-      const unsigned long long amask = __ballot(act);
-      if (act) s_tgt[nt + lanes_below(amask)] = gr.x + c0 + lane;
-      nt += __popcll(amask);
-    }
+    const int nt = active_targets(A, gr, s_tgt);
     __syncthreads();
     if (nt == 0) continue;   // cannot happen for a listed group; keeps s_tgt reads defined
-    // shape: T targets per lane (at least ceil(nt / 64)), lt lane-targets,
-    // slices source slices; minimise T / slices.  Ties go to the larger T
-    // (fewer tile reads per pair), except that in mixed precision three
-    // targets to a lane are taken only where they evaluate strictly fewer
-    // pairs: measured on the 1M cusp, ties between two and three ran slower
-    // with three.
-    int T = (nt + 63) / 64;
-    int lt = (nt + T - 1) / T, slices = 64 / lt;
-#pragma unroll
-    for (int t = 2; t <= kMaxT; ++t) {
-      if (t <= T) continue;
-      const int l2 = (nt + t - 1) / t, s2 = 64 / l2;
-      const bool better = (kMixed && t >= 3) ? t * slices < T * s2 : t * slices <= T * s2;
-      if (better) { T = t; lt = l2; slices = s2; }
-    }
     Sink S;
     S.s_m = s_m; S.s_q = s_q; S.tile = &tile;
     S.nm = 0; S.nq = 0; S.cells = 0; S.parts = 0;
-    S.g0 = gr.x; S.gn = gr.y; S.own0 = S.own1 = 0ull;
-    S.s_tgt = s_tgt; S.nt = nt;
-    S.T = T; S.lt = lt; S.slices = slices;
-    S.tfull = 128 / slices;
-    S.F = slices * S.tfull;
-    const int j = (int)lane % lt;
-    const int sl = (int)lane / lt;
-    S.my_s = sl < slices ? sl : 0;           // idle lanes shadow slice 0 (discarded)
-    if constexpr (kMixed) {
-      S.cgx = 0.5 * (lo[0] + hi[0]);
-      S.cgy = 0.5 * (lo[1] + hi[1]);
-      S.cgz = 0.5 * (lo[2] + hi[2]);
-    } else {
-      S.cgx = S.cgy = S.cgz = 0.0;
-    }
-    S.e2 = (R)A.eps2;
-    S.h = (R)A.eps;
-    S.ih = (R)(1.0 / A.eps);
-#pragma unroll
-    for (int k = 0; k < kMaxT; ++k) {
-      // lane-target j holds targets j, j + lt, ...; missing ones repeat j
-      const int i = j + k * lt;
-      const double4 p = A.spart[s_tgt[i < nt ? i : j]];
-      S.tx[k] = (R)(p.x - S.cgx); S.ty[k] = (R)(p.y - S.cgy); S.tz[k] = (R)(p.z - S.cgz);
-      S.hax[k] = S.hay[k] = S.haz[k] = S.hph[k] = 0.0;
-    }
-    const bool ok = traverse<kRel>(A, S, A.root_of[gr.w], lo, hi, kRel ? A.arel[g] : 0.0);
-    // per-lane totals -> LDS, [k][lane][4]
-    double *red = tile.red;
-#pragma unroll
-    for (int k = 0; k < kMaxT; ++k) {
-      double *o = red + 4 * (64 * k + (int)lane);
-      o[0] = S.hax[k]; o[1] = S.hay[k]; o[2] = S.haz[k]; o[3] = S.hph[k];
-    }
+    S.turn = (int)part; S.parts_ = (int)parts;
+    S.init(A, gr, lo, hi, s_tgt, nt);
+    const bool ok = traverse<kRel>(A, S, blockIdx.x, A.root_of[gr.w], lo, hi,
+                                   kRel ? A.arel[g] : 0.0);
+    S.store_red();
+    const double *red = tile.red;
     __syncthreads();
+    double4 *out = A.wpart + (size_t)((item.y >> 10) + part) * A.stride;
     for (int i = (int)lane; i < nt; i += 64) {
       // target i sits at k = i / lt, lane-target i % lt of every slice; sum
       // the slices in slice order (deterministic)
-      const int k = i / lt, jj = i % lt;
+      const int k = i / S.lt, jj = i % S.lt;
       double ax = 0.0, ay = 0.0, az = 0.0, ph = 0.0;
-      for (int q = 0; q < slices; ++q) {
-        const double *o = red + 4 * (64 * k + q * lt + jj);
+      for (int q = 0; q < S.slices; ++q) {
+        const double *o = red + 4 * (64 * k + q * S.lt + jj);
         ax += o[0]; ay += o[1]; az += o[2]; ph += o[3];
       }
-      const uint32_t r_t = s_tgt[i];
-      const double4 p = A.spart[r_t];
-      const uint32_t orig = A.perm[r_t];
-      const double nanv = __longlong_as_double(0x7ff8000000000000ll);
-      double ex = 0.0, ey = 0.0, ez = 0.0, ep = 0.0;
-      if (A.ext_seg) {   // SMBH terms, FP64 in both precision modes
-        for (int32_t e = A.ext_seg[gr.w]; e < A.ext_seg[gr.w + 1]; ++e) {
-          const double es = fmax(A.eps, A.ext_eps[e]);
-          const double dx = p.x - A.ext_pos[3 * e], dy = p.y - A.ext_pos[3 * e + 1],
-                       dz = p.z - A.ext_pos[3 * e + 2];
-          double mD1, mD3;
-          if constexpr (kSpline) {
-            double p0, p1;
-            spline_pair_dp(sqrt(dx * dx + dy * dy + dz * dz), es, p0, p1);
-            mD1 = A.ext_mass[e] * p0;
-            mD3 = A.ext_mass[e] * p1;
-          } else {
-            const double r2 = dx * dx + dy * dy + dz * dz + es * es;
-            const double D1 = 1.0 / sqrt(r2);
-            mD1 = A.ext_mass[e] * D1;
-            mD3 = mD1 * D1 * D1;
-          }
-          ex -= mD3 * dx; ey -= mD3 * dy; ez -= mD3 * dz; ep -= mD1;
-        }
-      }
-      A.acc[3 * (size_t)orig + 0] = ok ? A.G * (ax + ex) : nanv;
-      A.acc[3 * (size_t)orig + 1] = ok ? A.G * (ay + ey) : nanv;
-      A.acc[3 * (size_t)orig + 2] = ok ? A.G * (az + ez) : nanv;
-      if (A.pot) A.pot[orig] = ok ? A.G * (ph + ep) : nanv;
+      if (!ok) ax = ay = az = ph = __longlong_as_double(0x7ff8000000000000ll);
+      if (parts > 1u) out[i] = make_double4(ax, ay, az, ph);
+      else store_target<kSpline>(A, gr.w, s_tgt[i], ax, ay, az, ph);
     }
-    tot_p2m += S.cells * (unsigned long long)nt;
-    tot_p2p += S.parts * (unsigned long long)nt - (unsigned long long)nt;
-    tot_t += (unsigned long long)nt;
-    tot_g += 1;
+    if (part == 0u) {
+      tot_p2m += S.cells * (unsigned long long)nt;
+      tot_p2p += S.parts * (unsigned long long)nt - (unsigned long long)nt;
+      tot_t += (unsigned long long)nt;
+      tot_g += 1;
+    }
     __syncthreads();
   }
   // each workgroup stores its own totals (k_walk_sum adds them up): eight
@@ -939,34 +1072,65 @@ void k_walk_forces(const int32_t *__restrict__ gate, WalkArgs A) {
   }
 }
 
-// The force walk's counts: the sums of the nb workgroups' totals, into the
-// last walk's counts and added to the running ones.
-constexpr int kSumThreads = 1024;
+// After the walk.  Block 0: the counts, the sums of the nb workgroups'
+// totals, into the last walk's counts and added to the running ones.  The
+// other blocks: the results of the split groups, a wave to a group, its
+// parts' totals added in order.
+constexpr int kFinishThreads = 256;
+constexpr int kFinishBlocks = 1 + 512;
 
-__global__ __launch_bounds__(kSumThreads) void k_walk_sum(const int32_t *__restrict__ gate, TreeCounters *ctr,
-                                                  const unsigned long long *__restrict__ wtot,
-                                                  int nb) {
-  if (gate && *gate <= 0) return;   // nothing active: skipped
-  __shared__ unsigned long long part[kSumThreads / 64][4];
+template <bool kSpline>
+__global__ __launch_bounds__(kFinishThreads) void k_walk_finish(const int32_t *__restrict__ gate,
+                                                                WalkArgs A, int nb) {
+  if (gate && *gate <= 0) {         // nothing active: no walk, its counts are zero
+    if (blockIdx.x == 0 && threadIdx.x < 4) (&A.ctr->n_p2p)[threadIdx.x] = 0;
+    return;
+  }
+  constexpr int kWaves = kFinishThreads / 64;
+  __shared__ unsigned long long part[kWaves][4];
+  __shared__ uint32_t s_tgt[kWaves][kMaxGroup];
+  const unsigned lane = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (blockIdx.x > 0) {
+    const uint32_t ns = A.ctr->n_slots;
+    for (uint32_t s = (blockIdx.x - 1u) * kWaves + w; s < ns; s += (gridDim.x - 1u) * kWaves) {
+      const uint2 sl = A.slots[s];
+      if (sl.y == 0u) continue;           // a later part
+      const uint4 gr = A.groups[sl.x];
+      const int nt = active_targets(A, gr, s_tgt[w]);
+      wave_sync();
+      for (int i = (int)lane; i < nt; i += 64) {
+        const double4 *o = A.wpart + (size_t)s * A.stride + i;
+        double4 v = o[0];
+        for (uint32_t k = 1; k < sl.y; ++k) {
+          const double4 u = o[(size_t)k * A.stride];
+          v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+        }
+        store_target<kSpline>(A, gr.w, s_tgt[w][i], v.x, v.y, v.z, v.w);
+      }
+      wave_sync();
+    }
+    return;
+  }
   unsigned long long v[4] = {0, 0, 0, 0};
-  for (int b = threadIdx.x; b < nb; b += blockDim.x)
+#pragma unroll 4
+  for (int b = threadIdx.x; b < nb; b += kFinishThreads)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] += wtot[4 * (size_t)b + k];
+    for (int k = 0; k < 4; ++k) v[k] += A.wtot[4 * (size_t)b + k];
 #pragma unroll
   for (int k = 0; k < 4; ++k)
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
-  const unsigned w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63u) == 0)
+  if (lane == 0)
 #pragma unroll
     for (int k = 0; k < 4; ++k) part[w][k] = v[k];
   __syncthreads();
   if (threadIdx.x < 4) {
     const unsigned k = threadIdx.x;
     unsigned long long t = 0;
-    for (int q = 0; q < kSumThreads / 64; ++q) t += part[q][k];
-    (&ctr->n_p2p)[k] = t;
-    (&ctr->cum_p2p)[k] += t;
+    for (int q = 0; q < kWaves; ++q) t += part[q][k];
+    (&A.ctr->n_p2p)[k] = t;
+    (&A.ctr->cum_p2p)[k] += t;
   }
 }
 
@@ -989,7 +1153,7 @@ __global__ __launch_bounds__(64) void k_walk_lists(WalkArgs A) {
       // the fill pass repeats this walk exactly (also up to a frontier
       // overflow), so these counts bound what it writes
       CountSink S;
-      traverse<kRel>(A, S, A.root_of[gr.w], lo, hi, arel);
+      traverse<kRel>(A, S, blockIdx.x, A.root_of[gr.w], lo, hi, arel);
       if (lane_id() == 0) {
         A.wl_count[2 * (size_t)gi] = S.nm;
         A.wl_count[2 * (size_t)gi + 1] = S.np;
@@ -998,7 +1162,7 @@ __global__ __launch_bounds__(64) void k_walk_lists(WalkArgs A) {
       FillSink S;
       S.base_m = A.wl_off[2 * (size_t)gi];
       S.base_p = A.wl_off[2 * (size_t)gi + 1];
-      traverse<kRel>(A, S, A.root_of[gr.w], lo, hi, arel);
+      traverse<kRel>(A, S, blockIdx.x, A.root_of[gr.w], lo, hi, arel);
     }
     __syncthreads();
   }
@@ -1039,7 +1203,7 @@ __device__ __forceinline__ double qmax(double v) {
 // particles.  With old accelerations (caller order, reached through perm)
 // also the relative test's group threshold (alpha alpha) min |a_old|^2,
 // |a|^2 = (ax ax + ay ay) + az az unfused.
-__global__ __launch_bounds__(256) void k_group_active(const int32_t *__restrict__ gate, const TreeCounters *ctr,
+__global__ __launch_bounds__(256) void k_group_active(const int32_t *__restrict__ gate, TreeCounters *ctr,
                                                       const uint4 *__restrict__ groups,
                                                       const uint8_t *__restrict__ sact,
                                                       const double4 *__restrict__ spart,
@@ -1053,6 +1217,7 @@ __global__ __launch_bounds__(256) void k_group_active(const int32_t *__restrict_
 #pragma clang fp contract(off)
   if (gate && *gate <= 0) return;   // nothing active: skipped
   const uint32_t ng = ctr->n_groups;
+  if (blockIdx.x == 0 && threadIdx.x == 0) ctr->n_slots = 0;    // counted by k_order_items
   const unsigned q = threadIdx.x & 15u;
   const uint32_t qpb = blockDim.x >> 4;
   for (uint32_t g0 = blockIdx.x * qpb; g0 < ng; g0 += gridDim.x * qpb) {
@@ -1108,28 +1273,32 @@ __global__ void k_compact_groups(const int32_t *__restrict__ gate, const TreeCou
     if (aflag[g]) alist[aidx[g]] = g;
 }
 
-// The order in which the force walk takes the active groups: each XCD's
-// queue range [q G / 8, (q + 1) G / 8) of the compacted list keeps its
-// groups (and so its part of the tree), taken by size class, largest class
-// first (kSizeClass thresholds on the active targets), and in tree order
-// within a class.  The walk's wall time ends with the last groups taken, so
-// ending on the small ones shortens the tail in which few waves are left;
-// keeping tree order inside a class keeps neighbouring groups, which share
-// most of their cells, close in time for the XCD's L2.  One block per range:
-// a first sweep counts the classes (coalesced reads), then the range is
-// taken in chunks staged in LDS, each thread placing a contiguous run of
-// the chunk at offsets from one block scan of its four class counts packed
-// in 16-bit fields.  Stable, so deterministic.  No result depends on the
-// order in which groups are walked.
+// The force walk's items and their order.  A group with nt targets becomes
+// ceil(nt / per) items of about equal work, per = max(kMinPart, targets /
+// want): the walk's wall time ends with its longest items, and a group of 64
+// targets is three to five times the work of an average one, more than a
+// wave's share when there are few groups.  What a part repeats of its group
+// (the traversal, a tenth to a sixth of an unsplit group's time) is the
+// price; with many groups per wave nothing is split.
+// Each XCD's queue range [q G / 8, (q + 1) G / 8) of the compacted list keeps
+// its groups (and so its part of the tree), taken by size class, largest
+// class first (thresholds on the active targets), and in tree order
+// within a class: ending on the small ones shortens the tail in which few
+// waves are left, and keeping tree order inside a class keeps neighbouring
+// groups, which share most of their cells, close in time for the XCD's L2.
+// One block per range: a first sweep counts the classes' items, then the
+// range is taken in chunks staged in LDS, each thread placing a contiguous
+// run of the chunk at offsets from one block scan of its counts.  Stable,
+// so deterministic.  No result depends on the order in which items are
+// walked.
 constexpr int kSizeClasses = 4;
 __device__ __forceinline__ uint32_t size_class(uint32_t nt) {
   return nt >= 48u ? 0u : nt >= 32u ? 1u : nt >= 16u ? 2u : 3u;
 }
 
 constexpr int kOrderThreads = 1024;
-constexpr uint32_t kOrderItems = 8;                                // per thread and chunk
-constexpr uint32_t kOrderChunk = kOrderThreads * kOrderItems;      // < 2^16 per class field
-static_assert(kOrderChunk < 65536u, "a chunk's class counts fit 16-bit fields");
+constexpr uint32_t kOrderItems = 8;                                // groups per thread and chunk
+constexpr uint32_t kOrderChunk = kOrderThreads * kOrderItems;
 
 // Exclusive block prefix of a 64-bit value (four 16-bit fields; no carries
 // between fields since every field's total stays below 2^16).
@@ -1155,44 +1324,64 @@ __device__ __forceinline__ uint64_t block_exclusive_scan64(uint64_t v, uint64_t 
   return base + x - v;
 }
 
-__global__ __launch_bounds__(kOrderThreads) void k_order_groups(const int32_t *__restrict__ gate,
-                                                      const TreeCounters *ctr,
-                                                      const uint32_t *__restrict__ alist,
-                                                      const uint32_t *__restrict__ acnt,
-                                                      uint32_t *__restrict__ order) {
+__global__ __launch_bounds__(kOrderThreads) void k_order_items(
+    const int32_t *__restrict__ gate, TreeCounters *ctr, const uint32_t *__restrict__ alist,
+    const uint32_t *__restrict__ acnt, const int32_t *__restrict__ n_act, int64_t n, uint32_t want,
+    uint32_t gap, uint2 *__restrict__ items, uint2 *__restrict__ slots) {
   if (gate && *gate <= 0) return;   // nothing active: skipped
   __shared__ uint64_t scan_sh[kOrderThreads / 64];
   __shared__ uint32_t s_g[kOrderChunk];
-  __shared__ uint8_t s_c[kOrderChunk];
-  const uint32_t tid = threadIdx.x;
+  __shared__ uint8_t s_n[kOrderChunk];
+  __shared__ uint32_t s_sum[kOrderThreads / 64][kSizeClasses + 1], s_tot[kSizeClasses + 1];
+  __shared__ uint32_t s_slot0;
+  const uint32_t tid = threadIdx.x, w = tid >> 6;
   const uint32_t G = ctr->n_active_groups;
   const uint32_t lo = (uint32_t)(((uint64_t)blockIdx.x * G) >> 3);
   const uint32_t hi = (uint32_t)(((uint64_t)(blockIdx.x + 1) * G) >> 3);
-  // class totals of the range
-  uint32_t cnt[kSizeClasses] = {};
-  for (uint32_t p0 = lo + tid; p0 < hi; p0 += kOrderThreads * kOrderItems) {
-    uint32_t gg[kOrderItems];       // the loads of kOrderItems groups in flight at once
+  const uint32_t targets = (uint32_t)(n_act ? min((int64_t)n_act[0], n) : n);
+  const uint32_t per = max((uint32_t)kMinPart, (targets + want - 1u) / want);
+  auto parts_of = [&](uint32_t nt) { return min((uint32_t)kMaxParts, (nt + per - 1u) / per); };
+  // the range's items of each class and slots
+  uint32_t cnt[kSizeClasses + 1] = {};
+  for (uint32_t p0 = lo + tid; p0 < hi; p0 += kOrderChunk) {
+    uint32_t nt[kOrderItems];       // the loads of kOrderItems groups in flight at once
 #pragma unroll
     for (uint32_t j = 0; j < kOrderItems; ++j) {
       const uint32_t p = p0 + j * kOrderThreads;
-      gg[j] = p < hi ? alist[p] : 0u;
+      nt[j] = p < hi ? acnt[alist[p]] : 0u;
     }
 #pragma unroll
     for (uint32_t j = 0; j < kOrderItems; ++j) {
       if (p0 + j * kOrderThreads >= hi) continue;
-      const uint32_t k = size_class(acnt[gg[j]]);
+      const uint32_t k = size_class(nt[j]), np = parts_of(nt[j]);
 #pragma unroll
-      for (uint32_t q = 0; q < kSizeClasses; ++q) cnt[q] += k == q ? 1u : 0u;
+      for (uint32_t q = 0; q < kSizeClasses; ++q) cnt[q] += k == q ? np : 0u;
+      cnt[kSizeClasses] += np > 1u ? np : 0u;
     }
   }
-  uint32_t next[kSizeClasses];      // next free slot of each class
-  uint32_t base = lo;
 #pragma unroll
-  for (int k = 0; k < kSizeClasses; ++k) {
-    uint32_t tot;
-    block_exclusive_scan(cnt[k], reinterpret_cast<uint32_t *>(scan_sh), tot);
-    next[k] = base;
-    base += tot;
+  for (int k = 0; k <= kSizeClasses; ++k) {
+    uint32_t v = cnt[k], t;
+    (void)wave_excl_scan(v, t);
+    if ((tid & 63u) == 0u) s_sum[w][k] = t;
+  }
+  __syncthreads();
+  if (tid <= (uint32_t)kSizeClasses) {
+    uint32_t t = 0;
+    for (int q = 0; q < kOrderThreads / 64; ++q) t += s_sum[q][tid];
+    s_tot[tid] = t;
+    if (tid == (uint32_t)kSizeClasses) s_slot0 = t ? atomicAdd(&ctr->n_slots, t) : 0u;
+  }
+  __syncthreads();
+  uint32_t next[kSizeClasses];      // next free place of each class
+  next[0] = lo + blockIdx.x * gap;
+#pragma unroll
+  for (int k = 1; k < kSizeClasses; ++k) next[k] = next[k - 1] + s_tot[k - 1];
+  uint32_t slot = s_slot0;
+  const bool split = s_tot[kSizeClasses] > 0u;     // uniform
+  if (tid == 0) {
+    ctr->q_items[blockIdx.x] = s_tot[0] + s_tot[1] + s_tot[2] + s_tot[3];
+    ctr->xq[kQueueStride * blockIdx.x] = 0;        // the walk's queue starts over
   }
   for (uint32_t c0 = lo; c0 < hi; c0 += kOrderChunk) {
     const uint32_t m = min(kOrderChunk, hi - c0);
@@ -1207,34 +1396,52 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_groups(const int32_t *_
       const uint32_t i = tid + j * kOrderThreads;
       if (i < m) {
         s_g[i] = gg[j];
-        s_c[i] = (uint8_t)size_class(acnt[gg[j]]);
+        s_n[i] = (uint8_t)acnt[gg[j]];
       }
     }
     __syncthreads();
-    // this thread's run [kOrderItems tid, kOrderItems (tid + 1)) of the chunk
+    // this thread's run [kOrderItems tid, kOrderItems (tid + 1)) of the
+    // chunk; a chunk has at most kOrderChunk + 2 want items (split groups
+    // have more than `per` targets each)
     const uint32_t r0 = kOrderItems * tid;
     uint64_t mine = 0;
+    uint32_t my_slots = 0;
 #pragma unroll
-    for (uint32_t j = 0; j < kOrderItems; ++j)
-      if (r0 + j < m) mine += 1ull << (16u * s_c[r0 + j]);
+    for (uint32_t j = 0; j < kOrderItems; ++j) {
+      if (r0 + j >= m) break;
+      const uint32_t nt = s_n[r0 + j], np = parts_of(nt);
+      mine += (uint64_t)np << (16u * size_class(nt));
+      my_slots += np > 1u ? np : 0u;
+    }
     uint64_t tot;
     const uint64_t ex = block_exclusive_scan64(mine, scan_sh, tot);
+    uint32_t slot_tot = 0, s0 = slot;
+    if (split) s0 += block_exclusive_scan(my_slots, reinterpret_cast<uint32_t *>(scan_sh), slot_tot);
     uint32_t at[kSizeClasses];
 #pragma unroll
     for (uint32_t q = 0; q < kSizeClasses; ++q) at[q] = next[q] + (uint32_t)((ex >> (16u * q)) & 0xffffu);
 #pragma unroll
     for (uint32_t j = 0; j < kOrderItems; ++j) {
       if (r0 + j >= m) break;
-      const uint32_t k = s_c[r0 + j];
+      const uint32_t nt = s_n[r0 + j], k = size_class(nt), np = parts_of(nt), g = s_g[r0 + j];
       uint32_t dst = at[0];
 #pragma unroll
       for (uint32_t q = 1; q < kSizeClasses; ++q) dst = k == q ? at[q] : dst;
 #pragma unroll
-      for (uint32_t q = 0; q < kSizeClasses; ++q) at[q] += k == q ? 1u : 0u;
-      order[dst] = s_g[r0 + j];
+      for (uint32_t q = 0; q < kSizeClasses; ++q) at[q] += k == q ? np : 0u;
+      if (np == 1u) {
+        items[dst] = make_uint2(g, 0u);
+      } else {
+        for (uint32_t e = 0; e < np; ++e) {
+          items[dst + e] = make_uint2(g, e | (np - 1u) << 5 | s0 << 10);
+          slots[s0 + e] = make_uint2(g, e == 0u ? np : 0u);
+        }
+        s0 += np;
+      }
     }
 #pragma unroll
     for (uint32_t q = 0; q < kSizeClasses; ++q) next[q] += (uint32_t)((tot >> (16u * q)) & 0xffffu);
+    slot += slot_tot;
     __syncthreads();                // the chunk's LDS is read before the next is staged
   }
 }
@@ -1263,6 +1470,30 @@ __global__ void k_walk_reset(TreeCounters *ctr) {
   }
 }
 
+// As many waves as asked for (the list kernels' launch).
+static int walk_grid(const tg_ctx *c) {
+  return std::max(1, c->n_cu * c->waves_per_cu);
+}
+
+// The force walk's waves that are sure to be resident: as asked for, up to
+// what the kernel is compiled for.  Each of them starts with an item of its
+// own, the largest first (one that started only when others end would leave
+// a longest item to the end: the FP64 walk of the 1M cusp took 8% longer
+// with 16 such waves per CU).
+static int walk_per_cu(const tg_ctx *c) {
+  return 4 * (c->cfg.precision == TG_MIXED ? TG_WALK_WAVES_MIXED : TG_WALK_WAVES_FP64);
+}
+static int walk_waves(const tg_ctx *c) {
+  return std::max(1, c->n_cu * std::min(c->waves_per_cu, walk_per_cu(c)));
+}
+
+// Its launch.  The FP64 kernel fits a ninth wave into a CU: with many groups
+// per wave that is 2% faster (1M cusp 7.30 against 7.48 ms a step), with few
+// the SIMDs holding three waves end last (131072 stars 1.14 against 1.11 ms).
+static int walk_blocks(const tg_ctx *c) {
+  return c->n >= (1 << 19) ? walk_grid(c) : walk_waves(c);
+}
+
 hipError_t launch_active_groups(tg_ctx *c, const int32_t *idx,
                                 const int32_t *n_act, const double *acc_old,
                                 double alpha) {
@@ -1283,10 +1514,14 @@ hipError_t launch_active_groups(tg_ctx *c, const int32_t *idx,
   e = scan_u32(b.aflag, b.gflag, 0u, &b.ctr->n_groups, &b.ctr->n_active_groups,
                b.scan_part, c->stream, c->gate);
   if (e != hipSuccess) return e;
+  // the split is for the waves that fit, whatever the launch: results do
+  // not depend on waves_per_cu
+  const uint32_t want = (uint32_t)(kItemsPerWave * c->n_cu * walk_per_cu(c));
   hipLaunchKernelGGL(k_compact_groups, dim3(1024), dim3(256), 0, c->stream, c->gate,
                      b.ctr, b.aflag, b.gflag, b.alist);
-  hipLaunchKernelGGL(k_order_groups, dim3(8), dim3(kOrderThreads), 0, c->stream, c->gate, b.ctr,
-                     b.alist, b.acnt, b.gorder);
+  hipLaunchKernelGGL(k_order_items, dim3(8), dim3(kOrderThreads), 0, c->stream, c->gate, b.ctr,
+                     b.alist, b.acnt, idx ? n_act : nullptr, c->n,
+                     want, (uint32_t)c->split_cap, b.items, b.slots);
   return hipGetLastError();
 }
 
@@ -1305,6 +1540,7 @@ static WalkArgs make_args(tg_ctx *c, double theta) {
   A.ext_pos = c->ext_pos; A.ext_mass = c->ext_mass; A.ext_eps = c->ext_eps;
   A.ext_seg = c->n_ext > 0 ? c->b.ext_seg : nullptr;
   A.eps = 0.0;
+  A.items = nullptr; A.item_gap = 0; A.slots = nullptr; A.wpart = nullptr; A.stride = 0; A.starts = 0;
   A.wl_count = b.wl_count; A.wl_off = b.wl_off; A.ids = nullptr;
   return A;
 }
@@ -1373,17 +1609,13 @@ static hipError_t launch_rel_records(tg_ctx *c) {
   return hipGetLastError();
 }
 
-static int walk_grid(tg_ctx *c) {
-  return std::max(1, c->n_cu * c->waves_per_cu);
-}
-
 template <bool kRel, bool kSpline>
 static void launch_force_kernel(tg_ctx *c, const WalkArgs &A) {
   if (c->cfg.precision == TG_MIXED)
-    hipLaunchKernelGGL((k_walk_forces<true, kRel, kSpline>), dim3(walk_grid(c)), dim3(64), 0,
+    hipLaunchKernelGGL((k_walk_forces<true, kRel, kSpline>), dim3(walk_blocks(c)), dim3(64), 0,
                        c->stream, c->gate, A);
   else
-    hipLaunchKernelGGL((k_walk_forces<false, kRel, kSpline>), dim3(walk_grid(c)), dim3(64), 0,
+    hipLaunchKernelGGL((k_walk_forces<false, kRel, kSpline>), dim3(walk_blocks(c)), dim3(64), 0,
                        c->stream, c->gate, A);
 }
 
@@ -1391,7 +1623,9 @@ hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta,
                               double *acc, double *pot, hipEvent_t before,
                               hipEvent_t after, bool rel) {
   WalkArgs A = make_args(c, theta);
-  A.alist = c->b.gorder;      // largest groups first in each XCD's range
+  A.items = c->b.items; A.item_gap = (uint32_t)c->split_cap;
+  A.slots = c->b.slots; A.wpart = c->b.wpart; A.stride = (uint32_t)c->group_size;
+  A.starts = (uint32_t)walk_waves(c);
   A.eps2 = eps * eps;
   A.eps = eps;
   A.acc = acc;
@@ -1407,7 +1641,6 @@ hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta,
     hipError_t e = launch_rel_records(c);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_walk_reset, dim3(1), dim3(64), 0, c->stream, c->b.ctr);
   if (before) {
     hipError_t e = hipEventRecord(before, c->stream);
     if (e != hipSuccess) return e;
@@ -1423,8 +1656,12 @@ hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta,
     hipError_t e = hipEventRecord(after, c->stream);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_walk_sum, dim3(1), dim3(kSumThreads), 0, c->stream, c->gate, c->b.ctr, c->b.wtot,
-                     walk_grid(c));
+  if (spline)
+    hipLaunchKernelGGL(k_walk_finish<true>, dim3(kFinishBlocks), dim3(kFinishThreads), 0, c->stream,
+                       c->gate, A, walk_blocks(c));
+  else
+    hipLaunchKernelGGL(k_walk_finish<false>, dim3(kFinishBlocks), dim3(kFinishThreads), 0, c->stream,
+                       c->gate, A, walk_blocks(c));
   return hipGetLastError();
 }
 

@@ -44,6 +44,12 @@ constexpr int64_t sort_hist_words(int64_t S, int64_t tiles) {
 }
 constexpr int kScanBlocks = 256;
 constexpr int kMaxWavesPerCU = 16;
+// The force walk splits groups into parts of at least kMinPart targets' work,
+// at most kMaxParts, until there are about kItemsPerWave items for each
+// resident wave.  (131072 stars: the walk takes 522 us with one item per wave
+// to fill, 537 with two, 592 with four, 585 unsplit; 1021 stars: 114 us
+// unsplit, 34 split, the same with 8 and 16 parts.)
+constexpr int kItemsPerWave = 1, kMaxParts = 8, kMinPart = 2;
 constexpr int kMaxExternal = 1024;               // SMBHs / external point masses
 constexpr int kMaxChain = 256;                   // chain members
 constexpr int kChainBlocks = 1024;               // partial sums of the chain particle's force
@@ -63,7 +69,9 @@ struct TreeCounters {
   uint32_t n_groups;
   uint32_t n_active_groups;
   uint32_t overflow;         // node capacity exceeded during this build
-  uint32_t pad[11];
+  uint32_t n_slots;          // force walk: items of split groups (partial results)
+  uint32_t q_items[8];       // force walk: items of each XCD's queue
+  uint32_t pad[2];
   unsigned long long n_p2p, n_p2m, n_targets, n_walked;      // last walk
   unsigned long long cum_p2p, cum_p2m, cum_targets, cum_walked;  // since reset
   // walk work counters, one queue per XCD, each on a line of its own
@@ -114,7 +122,9 @@ struct Buffers {
   uint32_t *aflag = nullptr;      // [N + 1] active-group flags / scan
   uint32_t *alist = nullptr;      // [N] active group ids
   uint32_t *acnt = nullptr;       // [N] active targets per group
-  uint32_t *gorder = nullptr;     // [N] active group ids in the force walk's order
+  uint2 *items = nullptr;         // [N + 8 split_cap] force walk items, one range per XCD queue
+  uint2 *slots = nullptr;         // [split_cap] {group, parts} of a split group's first item
+  double4 *wpart = nullptr;       // [split_cap][kMaxGroup] partial results of split groups
   double *abox = nullptr;         // [N][6] box of active targets per group
   double *arel = nullptr;         // [N] relative test: (alpha alpha) min |a_old|^2 per group
   // chain coupling
@@ -153,6 +163,7 @@ struct tg_ctx {
   int64_t n = 0;
   int32_t S = 0;
   int32_t leaf_size = 8, group_size = 64, waves_per_cu = 8;
+  int64_t split_cap = 0;           // items that split groups may have in one force walk
   int32_t max_level = tg::kMaxLevel;   // octree depth: 21, or 42 with two key words
   int64_t max_nodes = 0;
   int64_t max_tiles = 0;

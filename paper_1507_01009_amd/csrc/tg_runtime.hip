@@ -76,7 +76,7 @@ static void free_all(tg_ctx *c) {
                   b.root_of, b.key[0], b.key[1], b.val[0], b.val[1], b.hist,
                   b.rank, b.spart, b.level, b.nchild, b.first, b.count,
                   b.child, b.parent, b.nsys, b.com, b.mom, b.ninfo, b.cell, b.lcp, b.fl_lt, b.fl_bits, b.fl_cnt, b.fl_fst, b.fl_tot, b.gflag,
-                  b.groups, b.aflag, b.alist, b.acnt, b.gorder, b.abox, b.sact, b.frontier, b.wtot,
+                  b.groups, b.aflag, b.alist, b.acnt, b.items, b.slots, b.wpart, b.abox, b.sact, b.frontier, b.wtot,
                   b.wl_count, b.wl_off, b.scan_part, b.scan_total, b.ctr,
                   b.err, b.dpart, b.dseg, b.ext_seg, b.rel, b.side, b.bbox,
                   b.refit_flag, b.refit_gates, b.arel, b.cflag, b.ctile, b.cpart,
@@ -170,7 +170,10 @@ tg_status tg_create(const tg_config *cfg_in, void *stream, tg_ctx **out) {
   A(dalloc(&b.gflag, N + 1));
   A(dalloc(&b.groups, N));
   A(dalloc(&b.aflag, N + 1));
-  A(dalloc(&b.alist, N)); A(dalloc(&b.acnt, N)); A(dalloc(&b.gorder, N));
+  A(dalloc(&b.alist, N)); A(dalloc(&b.acnt, N));
+  c->split_cap = 2 * kItemsPerWave * waves;
+  A(dalloc(&b.items, N + 8 * c->split_cap)); A(dalloc(&b.slots, c->split_cap));
+  A(dalloc(&b.wpart, c->split_cap * kMaxGroup));
   A(dalloc(&b.abox, 6 * N)); A(dalloc(&b.arel, N));
   A(dalloc(&b.cflag, N + 1)); A(dalloc(&b.ctile, N / 1024 + 2)); A(dalloc(&b.cpart, 6 * kChainBlocks));
   A(dalloc(&b.sact, N));

@@ -1,0 +1,84 @@
+"""The force walk with groups split into parts: how a group is split depends
+on the number of targets of the whole walk, its lists and its sums inside a
+tile do not."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1507_01009_amd import ics
+from gpu_helpers import gpu_run, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+# Parts are sums of the same tiles (same FP32 values in mixed precision, the
+# same terms in FP64) grouped differently in FP64: at most some 40 tiles of
+# up to 64 slices each, so a few hundred roundings of 2^-53 of a sum of
+# magnitudes that exceeds the result by less than a hundredfold.
+TOL = 1e-12
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n,ng,every,soft", [(7, 64, 1, None), (65, 1, 1, None),
+                                             (700, 128, 1, None), (3001, 64, 1, "spline"),
+                                             (9000, 16, 7, None), (9000, 128, 50, None),
+                                             (40000, 64, 1, None)])
+def test_results_do_not_depend_on_the_split(n, ng, every, soft, precision):
+    """A system alone (few targets: its groups are split) and in a batch with
+    a much larger one (split into fewer parts or not at all)."""
+    say("split", n, ng, every, soft, precision)
+    pos, _, m = ics.plummer(n, 300 + n)
+    act = None if every == 1 else np.arange(0, n, every, dtype=np.int32)
+    rows = slice(0, n) if act is None else act
+    alone = gpu_run(pos, m, 0.01, 0.5, 8, ng, active=act, precision=precision, softening=soft)
+    big = 300000
+    rng = np.random.default_rng(n)
+    act2 = None if act is None else np.concatenate([act, np.arange(n, n + big, dtype=np.int32)])
+    both = gpu_run(np.concatenate([pos, rng.normal(size=(big, 3))]),
+                   np.concatenate([m, np.full(big, 1.0 / big)]), 0.01, 0.5, 8, ng, active=act2,
+                   sys_off=np.array([0, n, n + big]), precision=precision, softening=soft)
+    e = rel_err(both["acc"][rows], alone["acc"][rows]).max()
+    p = np.max(np.abs(both["pot"][rows] / alone["pot"][rows] - 1.0))
+    say("  acc %.3g pot %.3g" % (e, p))
+    assert e <= TOL and p <= TOL
+    if precision == 0 and soft is None:
+        ev = oracle.tree_forces(pos, m, 0.01, 0.5, 8, ng, active=act)
+        assert rel_err(alone["acc"][rows], ev.acc[rows]).max() <= 1e-12
+        assert (alone["counts"]["n_p2p"], alone["counts"]["n_p2m"]) == (ev.n_p2p, ev.n_p2m)
+
+
+def test_one_context_over_changing_active_sets():
+    """Walks of one context with few, many and no active targets in turn: each
+    is split on its own, and rows that are not active keep their values."""
+    import torch
+    from paper_1507_01009_amd import binding as B
+    from gpu_helpers import to_dev
+    n = 20000
+    pos, _, m = ics.plummer(n, 77)
+    full = gpu_run(pos, m, 0.01, 0.5, precision=0)
+    ctx = B.Context(n)
+    ctx.build_tree(to_dev(pos))
+    ctx.compute_moments(to_dev(m))
+    for count in (3, 20000, 150, 0, 5000):
+        say("active", count)
+        idx = np.sort(np.random.default_rng(count).choice(n, count, replace=False)).astype(np.int32)
+        acc = torch.full((n, 3), 7.0, dtype=torch.float64, device="cuda")
+        ctx.tree_forces(0.01, 0.5, acc, None, to_dev(idx if count else np.zeros(1, np.int32)),
+                        to_dev(np.array([count], np.int32)))
+        ctx.sync()
+        a = acc.cpu().numpy()
+        rest = np.setdiff1d(np.arange(n), idx)
+        assert np.all(a[rest] == 7.0)
+        assert ctx.get_counts()["n_targets"] == count
+        if count == n:
+            assert rel_err(a, full["acc"]).max() <= TOL
+        elif count:      # the active targets' boxes differ, so do the lists: the truncation error
+            assert np.median(rel_err(a[idx], full["acc"][idx])) <= 1e-2
+    ctx.close()
