@@ -455,6 +455,21 @@ __device__ __forceinline__ void set_err(uint32_t *err, uint32_t bit) {
   atomicOr(err, bit);
 }
 
+// Exclusive prefix sum over the 64 lanes and the wave total, on DPP lane
+// moves: shifts by 1, 2, 4, 8 inside each row of 16, then row 0's total to
+// rows 1 and 3 and the first 32 lanes' total to rows 2 and 3.
+__device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t &tot) {
+  uint32_t x = v;
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  tot = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+  return x - v;
+}
+
 // Exclusive scan of one value per thread across the block (multiple of 64
 // threads); sh needs blockDim/64 entries.  Contains two barriers.
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *sh,
