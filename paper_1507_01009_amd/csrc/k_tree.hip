@@ -486,8 +486,10 @@ __global__ void k_group_write(const int32_t *__restrict__ gate, const TreeCounte
                               const uint32_t *__restrict__ parent,
                               const uint32_t *__restrict__ nsys,
                               const uint32_t *__restrict__ gidx,
-                              uint4 *__restrict__ groups) {
+                              uint4 *__restrict__ groups, int32_t *__restrict__ built) {
   if (gate && *gate <= 0) return;   // nothing active: skipped
+  // a build exists now (read by the device-side rebuild / refit choice)
+  if (blockIdx.x == 0 && threadIdx.x == 0) *built = 1;
   const uint32_t nn = ctr->n_nodes;
   for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nn;
        v += gridDim.x * blockDim.x) {
@@ -504,7 +506,8 @@ __global__ void k_group_write(const int32_t *__restrict__ gate, const TreeCounte
 hipError_t launch_groups(tg_ctx *c) {
   Buffers &b = c->b;
   if (c->n == 0) {
-    return fill_u32(&b.ctr->n_groups, 0u, 1, c->stream);
+    const hipError_t e = fill_u32((uint32_t *)(b.refit_gates + 2), 1u, 1, c->stream, c->gate);
+    return e != hipSuccess ? e : fill_u32(&b.ctr->n_groups, 0u, 1, c->stream);
   }
   // the flags were cleared by k_lcp in the build
   const int g = 1024;
@@ -516,7 +519,7 @@ hipError_t launch_groups(tg_ctx *c) {
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_group_write, dim3(g), dim3(256), 0, c->stream, c->gate, b.ctr,
                      (uint32_t)c->group_size, b.nchild, b.first, b.count,
-                     b.parent, b.nsys, b.gflag, b.groups);
+                     b.parent, b.nsys, b.gflag, b.groups, b.refit_gates + 2);
   return hipGetLastError();
 }
 

@@ -78,7 +78,7 @@ struct WalkArgs {
   const uint4 *groups;
   const uint32_t *alist;
   const double *abox;
-  const uint8_t *sact;
+  const uint8_t *sact;        // active flag per sorted particle (null: all active)
   const uint32_t *perm;
   TreeCounters *ctr;
   unsigned long long *wtot;   // force walk: per workgroup {P2P, P2M, targets, groups}
@@ -941,7 +941,7 @@ __device__ __forceinline__ int active_targets(const WalkArgs &A, uint4 gr, uint3
   const uint32_t lane = lane_id();
   int nt = 0;
   for (uint32_t c0 = 0; c0 < gr.y; c0 += 64u) {
-    const bool act = c0 + lane < gr.y && A.sact[gr.x + c0 + lane];
+    const bool act = c0 + lane < gr.y && (!A.sact || A.sact[gr.x + c0 + lane]);
     const unsigned long long amask = __ballot(act);
     if (act) s_tgt[nt + lanes_below(amask)] = gr.x + c0 + lane;
     nt += __popcll(amask);
@@ -1159,15 +1159,11 @@ __global__ void k_mark_active(const int32_t *__restrict__ gate, const int32_t *_
                               const uint32_t *__restrict__ rank,
                               uint8_t *__restrict__ sact) {
   if (gate && *gate <= 0) return;   // nothing active: skipped
-  const int64_t m = idx ? (int64_t)min((int64_t)n_act[0], n) : n;
+  const int64_t m = min((int64_t)n_act[0], n);
   for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < m;
        k += (int64_t)gridDim.x * blockDim.x) {
-    if (idx) {
-      const int32_t i = idx[k];
-      if (i >= 0 && i < n) sact[rank[i]] = 1;
-    } else {
-      sact[k] = 1;
-    }
+    const int32_t i = idx[k];
+    if (i >= 0 && i < n) sact[rank[i]] = 1;
   }
 }
 
@@ -1187,7 +1183,9 @@ __device__ __forceinline__ double qmax(double v) {
 // flag groups with an active particle and store the box of their active
 // particles.  With old accelerations (caller order, reached through perm)
 // also the relative test's group threshold (alpha alpha) min |a_old|^2,
-// |a|^2 = (ax ax + ay ay) + az az unfused.
+// |a|^2 = (ax ax + ay ay) + az az unfused.  Without active flags (sact null)
+// every particle is active, every group is in the list in its own place, and
+// there is nothing to compact.
 __global__ __launch_bounds__(256) void k_group_active(const int32_t *__restrict__ gate, TreeCounters *ctr,
                                                       const uint4 *__restrict__ groups,
                                                       const uint8_t *__restrict__ sact,
@@ -1197,12 +1195,16 @@ __global__ __launch_bounds__(256) void k_group_active(const int32_t *__restrict_
                                                       double alpha2,
                                                       uint32_t *__restrict__ aflag,
                                                       uint32_t *__restrict__ acnt,
+                                                      uint32_t *__restrict__ alist,
                                                       double *__restrict__ abox,
                                                       double *__restrict__ arel) {
 #pragma clang fp contract(off)
   if (gate && *gate <= 0) return;   // nothing active: skipped
   const uint32_t ng = ctr->n_groups;
-  if (blockIdx.x == 0 && threadIdx.x == 0) ctr->n_slots = 0;    // counted by k_order_items
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ctr->n_slots = 0;               // counted by the ordering
+    if (!sact) ctr->n_active_groups = ng;
+  }
   const unsigned q = threadIdx.x & 15u;
   const uint32_t qpb = blockDim.x >> 4;
   for (uint32_t g0 = blockIdx.x * qpb; g0 < ng; g0 += gridDim.x * qpb) {
@@ -1217,7 +1219,7 @@ __global__ __launch_bounds__(256) void k_group_active(const int32_t *__restrict_
 #pragma unroll
     for (int r = 0; r < kMaxGroup / 16; ++r) {
       const uint32_t j = q + 16u * r;
-      const bool a = j < gr.y && sact[gr.x + j];
+      const bool a = j < gr.y && (!sact || sact[gr.x + j]);
       nact += (uint32_t)__popcll((__ballot(a) >> (threadIdx.x & 48u)) & 0xffffull);
       if (a) {
         const double4 p = spart[gr.x + j];
@@ -1238,7 +1240,8 @@ __global__ __launch_bounds__(256) void k_group_active(const int32_t *__restrict_
     const unsigned long long m = __ballot(any);
     const unsigned long long mine = (m >> (threadIdx.x & 48u)) & 0xffffull;
     if (live && q == 0) {
-      aflag[g] = mine ? 1u : 0u;
+      if (sact) aflag[g] = mine ? 1u : 0u;
+      else alist[g] = g;
       acnt[g] = nact;
       double *b = abox + 6 * (size_t)g;
       b[0] = lx; b[1] = ly; b[2] = lz; b[3] = hx; b[4] = hy; b[5] = hz;
@@ -1309,11 +1312,11 @@ __device__ __forceinline__ uint64_t block_exclusive_scan64(uint64_t v, uint64_t 
   return base + x - v;
 }
 
-__global__ __launch_bounds__(kOrderThreads) void k_order_items(
-    const int32_t *__restrict__ gate, TreeCounters *ctr, const uint32_t *__restrict__ alist,
-    const uint32_t *__restrict__ acnt, const int32_t *__restrict__ n_act, int64_t n, uint32_t want,
-    uint32_t gap, uint2 *__restrict__ items, uint2 *__restrict__ slots) {
-  if (gate && *gate <= 0) return;   // nothing active: skipped
+__device__ __forceinline__ void order_items(TreeCounters *ctr, const uint32_t *__restrict__ alist,
+                                            const uint32_t *__restrict__ acnt,
+                                            const int32_t *__restrict__ n_act, int64_t n,
+                                            uint32_t want, uint32_t gap,
+                                            uint2 *__restrict__ items, uint2 *__restrict__ slots) {
   __shared__ uint64_t scan_sh[kOrderThreads / 64];
   __shared__ uint32_t s_g[kOrderChunk];
   __shared__ uint8_t s_n[kOrderChunk];
@@ -1431,6 +1434,88 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_items(
   }
 }
 
+// Walk records of every node: Q = 3S - T I, -T eps^2 (spline: T) and M, in
+// the walk's precision, formed once per evaluation instead of once per
+// staged cell.
+template <class R>
+__device__ __forceinline__ void cell_records(uint32_t v0, uint32_t stride, uint32_t nn,
+                                             const double *__restrict__ mom, double eps2,
+                                             int spline, void *cell) {
+  using R4 = typename Vec4<R>::T;
+  R4 *out = reinterpret_cast<R4 *>(cell);
+  for (uint32_t v = v0; v < nn; v += stride) {
+    const double4 m0 = reinterpret_cast<const double4 *>(mom)[2 * (size_t)v];
+    const double4 m1 = reinterpret_cast<const double4 *>(mom)[2 * (size_t)v + 1];
+    // m0 = {M, Sxx, Syy, Szz}, m1 = {Sxy, Sxz, Syz, -}
+    const double T = m0.y + m0.z + m0.w;
+    out[2 * (size_t)v] = R4{(R)(3.0 * m0.y - T), (R)(3.0 * m0.z - T), (R)(3.0 * m0.w - T),
+                            spline ? (R)T : (R)(-(T * eps2))};
+    out[2 * (size_t)v + 1] = R4{(R)(3.0 * m1.x), (R)(3.0 * m1.y), (R)(3.0 * m1.z), (R)m0.x};
+  }
+}
+
+// Relative-test records of every node: the cell cube enlarged by 20 %
+// about its geometric centre and P = (G M) s^2, s the node's opening size
+// (the cell side, or its refitted size), every operation rounded separately.
+struct RelArgs {
+  const uint8_t *level;
+  const uint32_t *first, *nsys;
+  const uint64_t *skey;
+  const double *cube, *mom, *side;
+  double G;
+  double4 *rel;                  // null: no relative test
+};
+__device__ __forceinline__ void rel_records(uint32_t v0, uint32_t stride, uint32_t nn,
+                                            const RelArgs &A) {
+#pragma clang fp contract(off)
+  for (uint32_t v = v0; v < nn; v += stride) {
+    double g[3];
+    cell_centre(v, A.level[v], A.first, A.nsys, A.skey, A.cube, g);
+    const double s = A.side[v];
+    const double h = dmul(0.6, s);
+    double lo[3], hi[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      lo[k] = dsub(g[k], h);
+      hi[k] = dadd(g[k], h);
+    }
+    const double P = dmul(dmul(A.G, A.mom[8 * (size_t)v]), dmul(s, s));
+    A.rel[2 * (size_t)v] = make_double4(lo[0], lo[1], lo[2], P);
+    A.rel[2 * (size_t)v + 1] = make_double4(hi[0], hi[1], hi[2], 0.0);
+  }
+}
+
+__global__ __launch_bounds__(256) void k_rel_records(const int32_t *__restrict__ gate,
+                                                     const TreeCounters *ctr, RelArgs A) {
+  if (gate && *gate <= 0) return;   // nothing active: skipped
+  rel_records(blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x, ctr->n_nodes, A);
+}
+
+// What the force walk needs besides the boxes, in one launch: eight blocks
+// order its items while the others form the nodes' records (the ordering
+// keeps eight CUs busy for 10 to 30 us, most of it waiting; the records take
+// 4 to 26).  With the marking, scan and compaction that a walk without an
+// active list no longer launches: 1021 stars 187 -> 173 us a force
+// evaluation, 131072 stars 748 -> 731 us a step.
+constexpr int kRecordBlocks = 504;
+
+template <class R>
+__global__ __launch_bounds__(kOrderThreads) void k_walk_prepare(
+    const int32_t *__restrict__ gate, TreeCounters *ctr, const uint32_t *__restrict__ alist,
+    const uint32_t *__restrict__ acnt, const int32_t *__restrict__ n_act, int64_t n, uint32_t want,
+    uint32_t gap, uint2 *__restrict__ items, uint2 *__restrict__ slots,
+    const double *__restrict__ mom, double eps2, int spline, void *cell, RelArgs rel) {
+  if (gate && *gate <= 0) return;   // nothing active: skipped
+  if (blockIdx.x < 8u) {
+    order_items(ctr, alist, acnt, n_act, n, want, gap, items, slots);
+    return;
+  }
+  const uint32_t v0 = (blockIdx.x - 8u) * kOrderThreads + threadIdx.x;
+  constexpr uint32_t kStride = kRecordBlocks * kOrderThreads;
+  cell_records<R>(v0, kStride, ctr->n_nodes, mom, eps2, spline, cell);
+  if (rel.rel) rel_records(v0, kStride, ctr->n_nodes, rel);
+}
+
 __global__ void k_counts_reset(TreeCounters *ctr) {
   if (threadIdx.x == 0) {
     ctr->cum_p2p = 0;
@@ -1485,38 +1570,35 @@ hipError_t launch_active_groups(tg_ctx *c, const int32_t *idx,
   Buffers &b = c->b;
   if (c->n == 0) return fill_u32(&b.ctr->n_active_groups, 0u, 1, c->stream);
   hipError_t e = hipSuccess;
-  if (idx) {   // without a list every particle is marked active below
+  if (idx) {
     e = fill_u8(b.sact, 0, c->n, c->stream, c->gate);
     if (e != hipSuccess) return e;
+    const int g = (int)std::min<int64_t>((c->n + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_mark_active, dim3(g), dim3(256), 0, c->stream, c->gate, idx,
+                       n_act, c->n, b.rank, b.sact);
   }
-  int g = (int)std::min<int64_t>((c->n + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_mark_active, dim3(g), dim3(256), 0, c->stream, c->gate, idx,
-                     n_act, c->n, b.rank, b.sact);
   hipLaunchKernelGGL(k_group_active, dim3(2048), dim3(256), 0, c->stream, c->gate,
-                     b.ctr, b.groups, b.sact, b.spart, acc_old, b.val[0], alpha * alpha,
-                     b.aflag, b.acnt, b.abox, b.arel);
+                     b.ctr, b.groups, idx ? b.sact : nullptr, b.spart, acc_old, b.val[0],
+                     alpha * alpha, b.aflag, b.acnt, b.alist, b.abox, b.arel);
+  if (!idx) return hipGetLastError();
   // the group-start scan buffer is free after the build: reuse it
   e = scan_u32(b.aflag, b.gflag, 0u, &b.ctr->n_groups, &b.ctr->n_active_groups,
                b.scan_part, c->stream, c->gate);
   if (e != hipSuccess) return e;
-  // the split is for the waves that fit, whatever the launch: results do
-  // not depend on waves_per_cu
-  const uint32_t want = (uint32_t)(kItemsPerWave * c->n_cu * walk_per_cu(c));
   hipLaunchKernelGGL(k_compact_groups, dim3(1024), dim3(256), 0, c->stream, c->gate,
                      b.ctr, b.aflag, b.gflag, b.alist);
-  hipLaunchKernelGGL(k_order_items, dim3(8), dim3(kOrderThreads), 0, c->stream, c->gate, b.ctr,
-                     b.alist, b.acnt, idx ? n_act : nullptr, c->n,
-                     want, (uint32_t)c->split_cap, b.items, b.slots);
   return hipGetLastError();
 }
 
-static WalkArgs make_args(tg_ctx *c, double theta) {
+// n_act: the active list's device count (null: every particle is active)
+static WalkArgs make_args(tg_ctx *c, double theta, const int32_t *n_act = nullptr) {
   Buffers &b = c->b;
   WalkArgs A;
   A.ninfo = b.ninfo; A.com = b.com; A.cell = b.cell;
   A.rel = b.rel; A.arel = b.arel;
   A.spart = b.spart; A.root_of = b.root_of;
-  A.groups = b.groups; A.alist = b.alist; A.abox = b.abox; A.sact = b.sact;
+  A.groups = b.groups; A.alist = b.alist; A.abox = b.abox;
+  A.sact = n_act ? b.sact : nullptr;
   A.perm = b.val[0]; A.ctr = b.ctr; A.wtot = b.wtot; A.err = b.err; A.frontier = b.frontier;
   A.fcap = c->cfg.frontier_cap;
   A.th2 = theta * theta;
@@ -1530,68 +1612,10 @@ static WalkArgs make_args(tg_ctx *c, double theta) {
   return A;
 }
 
-// Walk records of every node: Q = 3S - T I, -T eps^2 (spline: T) and M, in
-// the walk's precision, formed once per evaluation instead of once per
-// staged cell.
-template <class R>
-__global__ __launch_bounds__(256) void k_cell_records(const int32_t *__restrict__ gate, const TreeCounters *ctr,
-                                                      const double *__restrict__ mom,
-                                                      double eps2, int spline, void *cell) {
-  if (gate && *gate <= 0) return;   // nothing active: skipped
-  using R4 = typename Vec4<R>::T;
-  R4 *out = reinterpret_cast<R4 *>(cell);
-  const uint32_t nn = ctr->n_nodes;
-  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nn;
-       v += gridDim.x * blockDim.x) {
-    const double4 m0 = reinterpret_cast<const double4 *>(mom)[2 * (size_t)v];
-    const double4 m1 = reinterpret_cast<const double4 *>(mom)[2 * (size_t)v + 1];
-    // m0 = {M, Sxx, Syy, Szz}, m1 = {Sxy, Sxz, Syz, -}
-    const double T = m0.y + m0.z + m0.w;
-    out[2 * (size_t)v] = R4{(R)(3.0 * m0.y - T), (R)(3.0 * m0.z - T), (R)(3.0 * m0.w - T),
-                            spline ? (R)T : (R)(-(T * eps2))};
-    out[2 * (size_t)v + 1] = R4{(R)(3.0 * m1.x), (R)(3.0 * m1.y), (R)(3.0 * m1.z), (R)m0.x};
-  }
-}
-
-// Relative-test records of every node: the cell cube enlarged by 20 %
-// about its geometric centre and P = (G M) s^2, s the node's opening size
-// (the cell side, or its refitted size), every operation rounded separately.
-__global__ __launch_bounds__(256) void k_rel_records(const int32_t *__restrict__ gate,
-                                                     const TreeCounters *ctr,
-                                                     const uint8_t *__restrict__ level,
-                                                     const uint32_t *__restrict__ first,
-                                                     const uint32_t *__restrict__ nsys,
-                                                     const uint64_t *__restrict__ skey,
-                                                     const double *__restrict__ cube,
-                                                     const double *__restrict__ mom,
-                                                     const double *__restrict__ side, double G,
-                                                     double4 *__restrict__ rel) {
-#pragma clang fp contract(off)
-  if (gate && *gate <= 0) return;   // nothing active: skipped
-  const uint32_t nn = ctr->n_nodes;
-  for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nn;
-       v += gridDim.x * blockDim.x) {
-    double g[3];
-    cell_centre(v, level[v], first, nsys, skey, cube, g);
-    const double s = side[v];
-    const double h = dmul(0.6, s);
-    double lo[3], hi[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      lo[k] = dsub(g[k], h);
-      hi[k] = dadd(g[k], h);
-    }
-    const double P = dmul(dmul(G, mom[8 * (size_t)v]), dmul(s, s));
-    rel[2 * (size_t)v] = make_double4(lo[0], lo[1], lo[2], P);
-    rel[2 * (size_t)v + 1] = make_double4(hi[0], hi[1], hi[2], 0.0);
-  }
-}
-
-static hipError_t launch_rel_records(tg_ctx *c) {
+static RelArgs rel_args(tg_ctx *c, bool rel) {
   Buffers &b = c->b;
-  hipLaunchKernelGGL(k_rel_records, dim3(1024), dim3(256), 0, c->stream, c->gate, b.ctr,
-                     b.level, b.first, b.nsys, b.key[0], b.cube, b.mom, b.side, c->cfg.G, b.rel);
-  return hipGetLastError();
+  return RelArgs{b.level, b.first, b.nsys, b.key[0], b.cube, b.mom, b.side, c->cfg.G,
+                 rel ? b.rel : nullptr};
 }
 
 template <bool kRel, bool kSpline>
@@ -1604,28 +1628,27 @@ static void launch_force_kernel(tg_ctx *c, const WalkArgs &A) {
                        c->stream, c->gate, A);
 }
 
-hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta,
+hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta, const int32_t *n_act,
                               double *acc, double *pot, hipEvent_t before,
                               hipEvent_t after, bool rel) {
-  WalkArgs A = make_args(c, theta);
-  A.items = c->b.items; A.item_gap = (uint32_t)c->split_cap;
-  A.slots = c->b.slots; A.wpart = c->b.wpart; A.stride = (uint32_t)c->group_size;
+  Buffers &b = c->b;
+  WalkArgs A = make_args(c, theta, n_act);
+  A.items = b.items; A.item_gap = (uint32_t)c->split_cap;
+  A.slots = b.slots; A.wpart = b.wpart; A.stride = (uint32_t)c->group_size;
   A.starts = (uint32_t)walk_waves(c);
   A.eps2 = eps * eps;
   A.eps = eps;
   A.acc = acc;
   A.pot = pot;
   const int spline = c->soft == TG_SOFT_SPLINE ? 1 : 0;
-  if (c->cfg.precision == TG_MIXED)
-    hipLaunchKernelGGL(k_cell_records<float>, dim3(1024), dim3(256), 0, c->stream, c->gate, c->b.ctr,
-                       c->b.mom, A.eps2, spline, (void *)c->b.cell);
-  else
-    hipLaunchKernelGGL(k_cell_records<double>, dim3(1024), dim3(256), 0, c->stream, c->gate, c->b.ctr,
-                       c->b.mom, A.eps2, spline, (void *)c->b.cell);
-  if (rel) {
-    hipError_t e = launch_rel_records(c);
-    if (e != hipSuccess) return e;
-  }
+  // the split is for the waves that fit, whatever the launch: results do
+  // not depend on waves_per_cu
+  const uint32_t want = (uint32_t)(kItemsPerWave * c->n_cu * walk_per_cu(c));
+  const bool mixed = c->cfg.precision == TG_MIXED;
+  hipLaunchKernelGGL((mixed ? k_walk_prepare<float> : k_walk_prepare<double>),
+                     dim3(8 + kRecordBlocks), dim3(kOrderThreads), 0, c->stream, c->gate, b.ctr,
+                     b.alist, b.acnt, n_act, c->n, want, (uint32_t)c->split_cap, b.items, b.slots,
+                     b.mom, A.eps2, spline, (void *)b.cell, rel_args(c, rel));
   if (before) {
     hipError_t e = hipEventRecord(before, c->stream);
     if (e != hipSuccess) return e;
@@ -1656,10 +1679,9 @@ hipError_t launch_walk_lists(tg_ctx *c, double theta, int pass, int64_t *info,
   (void)info; (void)cap_groups; (void)cap_ids;
   WalkArgs A = make_args(c, theta);
   A.ids = ids;
-  if (rel && pass == 0) {
-    hipError_t e = launch_rel_records(c);
-    if (e != hipSuccess) return e;
-  }
+  if (rel && pass == 0)
+    hipLaunchKernelGGL(k_rel_records, dim3(1024), dim3(256), 0, c->stream, c->gate, c->b.ctr,
+                       rel_args(c, true));
   hipLaunchKernelGGL(k_walk_reset, dim3(1), dim3(64), 0, c->stream, c->b.ctr);
   const dim3 grid(walk_grid(c));
   if (pass == 0 && !rel)

@@ -352,8 +352,9 @@ hipError_t launch_moments(tg_ctx *c, const double *mass, bool gathered, bool ref
 hipError_t launch_active_groups(tg_ctx *c, const int32_t *idx,
                                 const int32_t *n_act, const double *acc_old,
                                 double alpha);
-// rel: relative opening test (needs launch_active_groups with acc_old)
-hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta,
+// n_act: the active list's device count (null: all particles); rel: relative
+// opening test (needs launch_active_groups with acc_old)
+hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta, const int32_t *n_act,
                               double *acc, double *pot, hipEvent_t before,
                               hipEvent_t after, bool rel);
 hipError_t launch_counts_reset(tg_ctx *c);

@@ -306,8 +306,6 @@ static tg_status build_tree_impl(tg_ctx *c, const double *pos, const double *mas
   TG_HIP(launch_gather(c, pos, mass));
   TG_HIP(launch_tree_build(c));
   TG_HIP(launch_groups(c));
-  // a build exists now (read by the device-side rebuild / refit choice)
-  TG_HIP(fill_u32((uint32_t *)(c->b.refit_gates + 2), 1u, 1, c->stream, c->gate));
   c->have_tree = true;
   c->mass_gathered = mass;
   return TG_OK;
@@ -406,7 +404,8 @@ static tg_status tree_forces_impl(tg_ctx *c, double eps, double theta,
     after = c->ev_stop[k];
     c->ev_head += 1;
   }
-  TG_HIP(launch_walk_forces(c, eps, theta, acc, pot, before, after, aold != nullptr));
+  TG_HIP(launch_walk_forces(c, eps, theta, idx ? n_act : nullptr, acc, pot, before, after,
+                            aold != nullptr));
   return TG_OK;
 }
 
