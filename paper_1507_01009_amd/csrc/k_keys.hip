@@ -566,4 +566,219 @@ hipError_t launch_gather(tg_ctx *c, const double *pos, const double *mass) {
   return hipGetLastError();
 }
 
+// ---- systems of at most one tile each --------------------------------
+// Everything up to the sorted particles in one launch, one block per system:
+// bounding cube, keys, stable sort, gather and common digits.  The general
+// path needs 12 launches for this (17 with 42 levels), and at a few thousand
+// particles each of them is 2 to 6 us of launch gaps and memory latency with
+// next to no work.  Here positions stay in registers and the keys in LDS,
+// where a pass moves only 16-bit indices: each wave ranks its own run of
+// indices with ballots as k_sort_pass does, 256 threads turn the waves' counts
+// of two digits each into offsets (16-bit halves: no count exceeds 4096), and
+// the indices are placed; three barriers a pass.  Bound by the latency of
+// these steps: 18 us for 1021 particles and 40 for 4096, where the launches
+// it replaces took 64 and 82 of an evaluation's 173 and 228 us (now 126, 185).
+constexpr int kSysThreads = 1024, kSysWaves = kSysThreads / 64;
+typedef uint16_t __attribute__((may_alias)) Half;   // also accessed as words
+
+template <int kItems, bool kDeep>
+__global__ __launch_bounds__(kSysThreads) void k_sort_systems(
+    const int32_t *__restrict__ gate, const double *__restrict__ pos,
+    const double *__restrict__ mass, const int64_t *__restrict__ sysoff, int64_t n,
+    double *__restrict__ cube, uint64_t *__restrict__ key, uint64_t *__restrict__ klo,
+    uint32_t *__restrict__ val, uint32_t *__restrict__ rank, double4 *__restrict__ spart,
+    uint8_t *__restrict__ d, uint32_t *__restrict__ gflag, uint32_t *err) {
+  if (gate && *gate <= 0) return;   // nothing active: skipped
+  constexpr int kN = kSysThreads * kItems;
+  __shared__ uint64_t hi[kN];
+  __shared__ uint64_t lo[kDeep ? kN : 1];
+  __shared__ uint16_t perm[kN];
+  // the waves' digit counts; after the last pass the inverse of perm
+  __shared__ __align__(16) Half cnt[kSysWaves][kSortDigits];
+  __shared__ __align__(16) Half base[kSortDigits];
+  __shared__ uint32_t wtot[kSortDigits / 128];
+  __shared__ double sh[kSysWaves][6];
+  __shared__ double box[6];
+  static_assert(kN <= kSysWaves * kSortDigits, "the inverse fits the counts");
+  const uint32_t tid = threadIdx.x, w = tid >> 6, lane = tid & 63u;
+  const int s = blockIdx.x;
+  const uint32_t a = (uint32_t)sysoff[s], ns = (uint32_t)(sysoff[s + 1] - sysoff[s]);
+  if (s == 0 && tid < 64u) d[n + tid] = 0;
+  if (s == 0 && tid == 64u) gflag[n] = 0u;
+
+  // positions and masses (thread: particles tid, tid + 1024, ...), bounding cube
+  double x[kItems][3], m[kItems];
+  double l3[3] = {INFINITY, INFINITY, INFINITY}, h3[3] = {-INFINITY, -INFINITY, -INFINITY};
+  bool bad = false, bad_mass = false;
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    const uint32_t i = (uint32_t)(kSysThreads * r) + tid;
+    const bool in = i < ns;
+    const size_t g = (size_t)a + i;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) x[r][k] = in ? pos[3 * g + k] : 0.0;
+    m[r] = in && mass ? mass[g] : 0.0;
+  }
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    if ((uint32_t)(kSysThreads * r) + tid >= ns) continue;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      bad |= !isfinite(x[r][k]);
+      l3[k] = fmin(l3[k], x[r][k]);
+      h3[k] = fmax(h3[k], x[r][k]);
+    }
+    if (mass) bad_mass |= !(m[r] > 0.0) || !isfinite(m[r]);
+  }
+  if (bad) set_err(err, TG_ERR_NONFINITE);
+  if (bad_mass) set_err(err, TG_ERR_MASS);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    l3[k] = wave_min(l3[k]);
+    h3[k] = wave_max(h3[k]);
+  }
+  if (lane == 0)
+    for (int k = 0; k < 3; ++k) { sh[w][k] = l3[k]; sh[w][3 + k] = h3[k]; }
+  __syncthreads();
+  if (tid < 6u) {
+    double v = sh[0][tid];
+    for (int q = 1; q < kSysWaves; ++q) v = tid < 3u ? fmin(v, sh[q][tid]) : fmax(v, sh[q][tid]);
+    box[tid] = v;
+  }
+  __syncthreads();
+  double c[4] = {0.0, 0.0, 0.0, 1.0};
+  if (ns > 0) {
+    double L = 0.0;
+    for (int k = 0; k < 3; ++k) {
+      c[k] = box[k];
+      L = fmax(L, box[3 + k] - box[k]);
+    }
+    c[3] = L == 0.0 ? 1.0 : L;
+  }
+  if (tid == 0)
+    for (int k = 0; k < 4; ++k) cube[4 * s + k] = c[k];
+  const double sigma = (kDeep ? 4398046511104.0 : 2097152.0) / c[3];
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    const uint32_t i = (uint32_t)(kSysThreads * r) + tid;
+    if (i >= ns) continue;
+    if constexpr (kDeep) {
+      keys42(x[r], c, sigma, hi[i], lo[i]);
+    } else {
+      const uint64_t q = 0x1FFFFFull;
+      hi[i] = morton21(quantise(x[r][0], c[0], sigma, q), quantise(x[r][1], c[1], sigma, q),
+                       quantise(x[r][2], c[2], sigma, q));
+    }
+    perm[i] = (uint16_t)i;
+  }
+  __syncthreads();
+
+  // wave w holds the indices [64 kItems w, 64 kItems (w + 1)) in order
+  uint32_t *const cnt2 = reinterpret_cast<uint32_t *>(&cnt[0][0]);
+  for (int pass = kDeep ? -kSortPasses : 0; pass < kSortPasses; ++pass) {
+    const uint64_t *word = kDeep && pass < 0 ? lo : hi;
+    const int shift = kSortBits * (pass < 0 ? pass + kSortPasses : pass);
+    uint32_t p[kItems], dg[kItems], rk[kItems];
+    reinterpret_cast<uint4 *>(cnt[w])[lane] = make_uint4(0, 0, 0, 0);   // the wave's own row
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+      const uint32_t j = 64u * kItems * w + 64u * r + lane;
+      p[r] = j < ns ? perm[j] : 0u;
+      dg[r] = j < ns ? (uint32_t)(word[p[r]] >> shift) & kSortMask : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+      const bool valid = 64u * kItems * w + 64u * r + lane < ns;
+      unsigned long long peers = __ballot(valid);
+#pragma unroll
+      for (int bit = 0; bit < kSortBits; ++bit) {
+        const unsigned long long bb = __ballot((dg[r] >> bit) & 1u);
+        peers &= ((dg[r] >> bit) & 1u) ? bb : ~bb;
+      }
+      const uint32_t lr = lanes_below(peers);
+      const uint32_t b0 = valid ? cnt[w][dg[r]] : 0u;
+      rk[r] = b0 + lr;
+      if (valid && lr == 0) cnt[w][dg[r]] = (Half)(b0 + (uint32_t)__popcll(peers));
+    }
+    __syncthreads();
+    if (w < kSortDigits / 128) {         // digits 2 tid and 2 tid + 1
+      uint32_t run = 0;
+#pragma unroll
+      for (int q = 0; q < kSysWaves; ++q) {
+        const uint32_t v = cnt2[q * (kSortDigits / 2) + tid];
+        cnt2[q * (kSortDigits / 2) + tid] = run;
+        run += v;
+      }
+      const uint32_t even = run & 0xffffu;
+      uint32_t tot;
+      const uint32_t e = wave_excl_scan(even + (run >> 16), tot);
+      reinterpret_cast<uint32_t *>(base)[tid] = e | (e + even) << 16;
+      if (lane == 0) wtot[w] = tot;
+    }
+    __syncthreads();
+    uint32_t wb[kSortDigits / 128];      // digits before each 128
+    wb[0] = 0;
+#pragma unroll
+    for (int q = 1; q < kSortDigits / 128; ++q) wb[q] = wb[q - 1] + wtot[q - 1];
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+      const uint32_t g = dg[r] >> 7;
+      const uint32_t lead = g == 0u ? wb[0] : g == 1u ? wb[1] : g == 2u ? wb[2] : wb[3];
+      if (64u * kItems * w + 64u * r + lane < ns)
+        perm[lead + base[dg[r]] + cnt[w][dg[r]] + rk[r]] = (uint16_t)p[r];
+    }
+    __syncthreads();
+  }
+
+  Half *const inv = &cnt[0][0];
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    const uint32_t j = (uint32_t)(kSysThreads * r) + tid;
+    if (j >= ns) continue;
+    const uint32_t p = perm[j], g = a + j;
+    const uint64_t k = hi[p];
+    key[g] = k;
+    val[g] = a + p;
+    gflag[g] = 0u;
+    uint32_t eq = 0;
+    if (j > 0u) {
+      const uint32_t q = perm[j - 1u];
+      eq = common_digits(hi[q], k);
+      if constexpr (kDeep)
+        if (eq == 21u) eq += common_digits(lo[q], lo[p]);
+    }
+    d[g] = (uint8_t)eq;
+    if constexpr (kDeep) klo[g] = lo[p];
+    inv[p] = (Half)j;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    const uint32_t i = (uint32_t)(kSysThreads * r) + tid;
+    if (i >= ns) continue;
+    const uint32_t g = a + inv[i];
+    rank[a + i] = g;
+    spart[g] = make_double4(x[r][0], x[r][1], x[r][2], m[r]);
+  }
+}
+
+// Taken when no system exceeds a sort tile (4096): the positions and keys of
+// one system have to fit one block.  Largest systems of up to 1024 particles
+// take the kernel with one particle per thread, whose passes have a quarter
+// of the ranking rounds.
+hipError_t launch_sort_systems(tg_ctx *c, const double *pos, const double *mass) {
+  Buffers &b = c->b;
+  const bool deep = c->max_level > kMaxLevel;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(c->S), dim3(kSysThreads), 0, c->stream, c->gate, pos, mass,
+                       b.sysoff, c->n, b.cube, b.key[0], b.klo[0], b.val[0], b.rank, b.spart,
+                       b.lcp, b.gflag, b.err);
+  };
+  if (c->max_sys <= kSysThreads)
+    deep ? go(k_sort_systems<1, true>) : go(k_sort_systems<1, false>);
+  else
+    deep ? go(k_sort_systems<4, true>) : go(k_sort_systems<4, false>);
+  return hipGetLastError();
+}
+
 }  // namespace tg

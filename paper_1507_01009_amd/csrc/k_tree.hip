@@ -46,11 +46,6 @@ __device__ void load_sysoff(int64_t *so, const int64_t *sysoff, int S) {
   __syncthreads();
 }
 
-__device__ __forceinline__ uint32_t common_digits(uint64_t a, uint64_t b) {
-  const uint64_t x = a ^ b;
-  return x == 0 ? 21u : (uint32_t)(__clzll((long long)x) - 1) / 3u;   // bit 63 is 0
-}
-
 // d for [0, n + 64): the common leading digits with the predecessor, 0 at
 // every system start and from n on.  With second key words (skey_lo not
 // null) the digits continue into them when the first words are equal.
@@ -439,9 +434,10 @@ hipError_t launch_tree_build(tg_ctx *c) {
   Buffers &b = c->b;
   const int64_t n = c->n, T = (n + kFT - 1) / kFT;
   const bool deep = c->max_level > kMaxLevel;
-  hipLaunchKernelGGL(k_lcp, dim3((int)std::min<int64_t>((n + 64 + 255) / 256, 4096)),
-                     dim3(256), 0, c->stream, c->gate, b.key[0], deep ? b.klo[0] : nullptr, n,
-                     b.sysoff, c->S, b.lcp, b.gflag);
+  if (!c->one_tile)   // (else k_sort_systems wrote them)
+    hipLaunchKernelGGL(k_lcp, dim3((int)std::min<int64_t>((n + 64 + 255) / 256, 4096)),
+                       dim3(256), 0, c->stream, c->gate, b.key[0], deep ? b.klo[0] : nullptr, n,
+                       b.sysoff, c->S, b.lcp, b.gflag);
   if (deep)
     launch_flat<kMaxLevelDeep>(c, T);
   else

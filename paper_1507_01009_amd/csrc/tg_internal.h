@@ -182,6 +182,8 @@ struct tg_ctx {
   // masses gathered into the sorted particles by the last build (or null)
   const double *mass_gathered = nullptr;
   int64_t n_tiles = 0;
+  int64_t max_sys = 0;             // particles of the layout's largest system
+  bool one_tile = false;           // no system is larger than a sort tile
   bool have_tree = false, have_moments = false;
   bool capturing = false;
   // walk-kernel timing (tg_set_profiling): ring of event pairs
@@ -334,6 +336,8 @@ hipError_t launch_cube_keys(tg_ctx *c, const double *pos);
 hipError_t launch_sort(tg_ctx *c);
 // 42 levels: second key words of the sorted particles (after launch_sort)
 hipError_t launch_keys_lo(tg_ctx *c, const double *pos);
+// cube, keys, sort, gather and common digits of systems of one tile at most
+hipError_t launch_sort_systems(tg_ctx *c, const double *pos, const double *mass);
 hipError_t launch_gather(tg_ctx *c, const double *pos, const double *mass);
 
 // k_tree.hip
@@ -469,6 +473,12 @@ __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t &tot) {
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
   tot = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
   return x - v;
+}
+
+// Equal leading digits (3 bits each) of two key words.
+__device__ __forceinline__ uint32_t common_digits(uint64_t a, uint64_t b) {
+  const uint64_t x = a ^ b;
+  return x == 0 ? 21u : (uint32_t)(__clzll((long long)x) - 1) / 3u;   // bit 63 is 0
 }
 
 // Exclusive scan of one value per thread across the block (multiple of 64

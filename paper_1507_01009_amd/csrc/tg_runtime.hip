@@ -255,9 +255,11 @@ static tg_status set_layout(tg_ctx *c, int64_t n, const int64_t *off, int32_t S)
     return fail(TG_ESTATE, "tg_build_tree: system layout changed during graph capture");
   std::vector<Tile> tiles;
   std::vector<uint32_t> t0(S + 1);
+  int64_t max_sys = 0;
   for (int s = 0; s < S; ++s) {
     t0[s] = (uint32_t)tiles.size();
     const int64_t ns = so[s + 1] - so[s];
+    max_sys = std::max(max_sys, ns);
     const uint32_t nts = (uint32_t)((ns + kSortTile - 1) / kSortTile);
     for (uint32_t k = 0; k < nts; ++k) {
       Tile t;
@@ -283,6 +285,8 @@ static tg_status set_layout(tg_ctx *c, int64_t n, const int64_t *off, int32_t S)
   c->n = n;
   c->S = S;
   c->n_tiles = (int64_t)tiles.size();
+  c->max_sys = max_sys;
+  c->one_tile = n > 0 && max_sys <= kSortTile;
   return TG_OK;
 } TG_HOST_CATCH("set_layout")
 
@@ -300,10 +304,14 @@ static tg_status build_tree_impl(tg_ctx *c, const double *pos, const double *mas
   tg_status st = set_layout(c, n, sys_off, S);
   if (st != TG_OK) return st;
   c->have_tree = c->have_moments = false;
-  TG_HIP(launch_cube_keys(c, pos));
-  TG_HIP(launch_sort(c));
-  TG_HIP(launch_keys_lo(c, pos));
-  TG_HIP(launch_gather(c, pos, mass));
+  if (c->one_tile) {
+    TG_HIP(launch_sort_systems(c, pos, mass));
+  } else {
+    TG_HIP(launch_cube_keys(c, pos));
+    TG_HIP(launch_sort(c));
+    TG_HIP(launch_keys_lo(c, pos));
+    TG_HIP(launch_gather(c, pos, mass));
+  }
   TG_HIP(launch_tree_build(c));
   TG_HIP(launch_groups(c));
   c->have_tree = true;
