@@ -1,6 +1,9 @@
 // Bounding cube per system, 21-bit Morton keys (or 42-bit, as two words),
-// stable LSD radix sort of (key, index), and the gather of positions into
-// sorted order.
+// stable sort of (key, index), and the gather of positions into sorted
+// order.  The sort takes one of three paths with the same result: systems of
+// one tile at most are sorted by one block each, up to 1.5M particles (4M
+// with two key words) sorted runs are merged, and larger sets take the radix
+// passes described here.
 //
 // Work is cut into tiles of kSortTile consecutive particles that never cross
 // a system boundary, so one launch handles every system of a batch.  One
@@ -581,6 +584,71 @@ hipError_t launch_gather(tg_ctx *c, const double *pos, const double *mass) {
 constexpr int kSysThreads = 1024, kSysWaves = kSysThreads / 64;
 typedef uint16_t __attribute__((may_alias)) Half;   // also accessed as words
 
+// Stable sort of the indices perm[0, n) (identity on entry) by the keys hi
+// (and lo) in LDS; the block meets at a barrier before and after.
+template <int kItems, bool kDeep>
+__device__ __forceinline__ void lds_sort(const uint64_t *hi, const uint64_t *lo, uint16_t *perm,
+                                         Half (*cnt)[kSortDigits], Half *base, uint32_t *wtot,
+                                         uint32_t ns) {
+  const uint32_t tid = threadIdx.x, w = tid >> 6, lane = tid & 63u;
+  // wave w holds the indices [64 kItems w, 64 kItems (w + 1)) in order
+  uint32_t *const cnt2 = reinterpret_cast<uint32_t *>(cnt[0]);
+  for (int pass = kDeep ? -kSortPasses : 0; pass < kSortPasses; ++pass) {
+    const uint64_t *word = kDeep && pass < 0 ? lo : hi;
+    const int shift = kSortBits * (pass < 0 ? pass + kSortPasses : pass);
+    uint32_t p[kItems], dg[kItems], rk[kItems];
+    reinterpret_cast<uint4 *>(cnt[w])[lane] = make_uint4(0, 0, 0, 0);   // the wave's own row
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+      const uint32_t j = 64u * kItems * w + 64u * r + lane;
+      p[r] = j < ns ? perm[j] : 0u;
+      dg[r] = j < ns ? (uint32_t)(word[p[r]] >> shift) & kSortMask : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+      const bool valid = 64u * kItems * w + 64u * r + lane < ns;
+      unsigned long long peers = __ballot(valid);
+#pragma unroll
+      for (int bit = 0; bit < kSortBits; ++bit) {
+        const unsigned long long bb = __ballot((dg[r] >> bit) & 1u);
+        peers &= ((dg[r] >> bit) & 1u) ? bb : ~bb;
+      }
+      const uint32_t lr = lanes_below(peers);
+      const uint32_t b0 = valid ? cnt[w][dg[r]] : 0u;
+      rk[r] = b0 + lr;
+      if (valid && lr == 0) cnt[w][dg[r]] = (Half)(b0 + (uint32_t)__popcll(peers));
+    }
+    __syncthreads();
+    if (w < kSortDigits / 128) {         // digits 2 tid and 2 tid + 1
+      uint32_t run = 0;
+#pragma unroll
+      for (int q = 0; q < kSysWaves; ++q) {
+        const uint32_t v = cnt2[q * (kSortDigits / 2) + tid];
+        cnt2[q * (kSortDigits / 2) + tid] = run;
+        run += v;
+      }
+      const uint32_t even = run & 0xffffu;
+      uint32_t tot;
+      const uint32_t e = wave_excl_scan(even + (run >> 16), tot);
+      reinterpret_cast<uint32_t *>(base)[tid] = e | (e + even) << 16;
+      if (lane == 0) wtot[w] = tot;
+    }
+    __syncthreads();
+    uint32_t wb[kSortDigits / 128];      // digits before each 128
+    wb[0] = 0;
+#pragma unroll
+    for (int q = 1; q < kSortDigits / 128; ++q) wb[q] = wb[q - 1] + wtot[q - 1];
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+      const uint32_t g = dg[r] >> 7;
+      const uint32_t lead = g == 0u ? wb[0] : g == 1u ? wb[1] : g == 2u ? wb[2] : wb[3];
+      if (64u * kItems * w + 64u * r + lane < ns)
+        perm[lead + base[dg[r]] + cnt[w][dg[r]] + rk[r]] = (uint16_t)p[r];
+    }
+    __syncthreads();
+  }
+}
+
 template <int kItems, bool kDeep>
 __global__ __launch_bounds__(kSysThreads) void k_sort_systems(
     const int32_t *__restrict__ gate, const double *__restrict__ pos,
@@ -673,62 +741,7 @@ __global__ __launch_bounds__(kSysThreads) void k_sort_systems(
   }
   __syncthreads();
 
-  // wave w holds the indices [64 kItems w, 64 kItems (w + 1)) in order
-  uint32_t *const cnt2 = reinterpret_cast<uint32_t *>(&cnt[0][0]);
-  for (int pass = kDeep ? -kSortPasses : 0; pass < kSortPasses; ++pass) {
-    const uint64_t *word = kDeep && pass < 0 ? lo : hi;
-    const int shift = kSortBits * (pass < 0 ? pass + kSortPasses : pass);
-    uint32_t p[kItems], dg[kItems], rk[kItems];
-    reinterpret_cast<uint4 *>(cnt[w])[lane] = make_uint4(0, 0, 0, 0);   // the wave's own row
-#pragma unroll
-    for (int r = 0; r < kItems; ++r) {
-      const uint32_t j = 64u * kItems * w + 64u * r + lane;
-      p[r] = j < ns ? perm[j] : 0u;
-      dg[r] = j < ns ? (uint32_t)(word[p[r]] >> shift) & kSortMask : 0u;
-    }
-#pragma unroll
-    for (int r = 0; r < kItems; ++r) {
-      const bool valid = 64u * kItems * w + 64u * r + lane < ns;
-      unsigned long long peers = __ballot(valid);
-#pragma unroll
-      for (int bit = 0; bit < kSortBits; ++bit) {
-        const unsigned long long bb = __ballot((dg[r] >> bit) & 1u);
-        peers &= ((dg[r] >> bit) & 1u) ? bb : ~bb;
-      }
-      const uint32_t lr = lanes_below(peers);
-      const uint32_t b0 = valid ? cnt[w][dg[r]] : 0u;
-      rk[r] = b0 + lr;
-      if (valid && lr == 0) cnt[w][dg[r]] = (Half)(b0 + (uint32_t)__popcll(peers));
-    }
-    __syncthreads();
-    if (w < kSortDigits / 128) {         // digits 2 tid and 2 tid + 1
-      uint32_t run = 0;
-#pragma unroll
-      for (int q = 0; q < kSysWaves; ++q) {
-        const uint32_t v = cnt2[q * (kSortDigits / 2) + tid];
-        cnt2[q * (kSortDigits / 2) + tid] = run;
-        run += v;
-      }
-      const uint32_t even = run & 0xffffu;
-      uint32_t tot;
-      const uint32_t e = wave_excl_scan(even + (run >> 16), tot);
-      reinterpret_cast<uint32_t *>(base)[tid] = e | (e + even) << 16;
-      if (lane == 0) wtot[w] = tot;
-    }
-    __syncthreads();
-    uint32_t wb[kSortDigits / 128];      // digits before each 128
-    wb[0] = 0;
-#pragma unroll
-    for (int q = 1; q < kSortDigits / 128; ++q) wb[q] = wb[q - 1] + wtot[q - 1];
-#pragma unroll
-    for (int r = 0; r < kItems; ++r) {
-      const uint32_t g = dg[r] >> 7;
-      const uint32_t lead = g == 0u ? wb[0] : g == 1u ? wb[1] : g == 2u ? wb[2] : wb[3];
-      if (64u * kItems * w + 64u * r + lane < ns)
-        perm[lead + base[dg[r]] + cnt[w][dg[r]] + rk[r]] = (uint16_t)p[r];
-    }
-    __syncthreads();
-  }
+  lds_sort<kItems, kDeep>(hi, lo, perm, &cnt[0], base, wtot, ns);
 
   Half *const inv = &cnt[0][0];
 #pragma unroll
@@ -778,6 +791,289 @@ hipError_t launch_sort_systems(tg_ctx *c, const double *pos, const double *mass)
     deep ? go(k_sort_systems<1, true>) : go(k_sort_systems<1, false>);
   else
     deep ? go(k_sort_systems<4, true>) : go(k_sort_systems<4, false>);
+  return hipGetLastError();
+}
+
+// ---- larger systems: sorted runs, then merges ---------------------------
+// k_sort_runs forms the keys of kRun particles and sorts them in LDS;
+// each round of k_merge_runs then merges groups of kWays runs of a system.
+// A block of the merge moves kMergeChunk consecutive keys of one run: where
+// its first and last key fall in the other runs is found by one wave each
+// (64 probes a step), the keys between are staged in LDS, and every thread
+// counts the ones before its own key.  Own index + counts is the place, and
+// ties go to the earlier run, so the order is that of the stable sort.  A
+// chunk that spans more than kMergeKeys keys of the other runs (a run that
+// lies inside a gap of another) searches them in memory.
+//
+// One radix pass costs 10 to 12 us however few tiles it has (ticket, ranks,
+// look-back, scatter), seven of them and the count 100 us at 131072
+// particles, the runs and three rounds 51.  A round's cost grows with the
+// keys read (each chunk reads its part of kWays runs) and reaches 30 us at
+// 1048576, where five rounds equal the radix passes.  Eight ways were 5% and
+// 16 ways 40% slower at that size and no faster below (more searches per
+// key); runs of 4096 save no round at 131072 and cost 13 us more.
+constexpr int kRun = 2048, kWays = 4, kMergeChunk = 512, kMergeKeys = 6 * kMergeChunk;
+static_assert(kSortTile % kRun == 0 && kRun % kMergeChunk == 0, "chunks never cross runs or tiles");
+
+// Cube of the system with tiles [t0, t1) from their coordinate ranges, in
+// every thread (one barrier).
+template <int kBlock>
+__device__ __forceinline__ void cube_of(const double *__restrict__ part, uint32_t t0, uint32_t t1,
+                                        double (*sh)[6], double *c) {
+  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+  for (uint32_t t = t0 + threadIdx.x; t < t1; t += kBlock)
+    for (int k = 0; k < 3; ++k) {
+      lo[k] = fmin(lo[k], part[6 * (size_t)t + k]);
+      hi[k] = fmax(hi[k], part[6 * (size_t)t + 3 + k]);
+    }
+  const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
+  const uint32_t nw = min((uint32_t)(kBlock / 64), (t1 - t0 + 63u) / 64u);
+  if (w < nw) {
+    for (int k = 0; k < 3; ++k) { lo[k] = wave_min(lo[k]); hi[k] = wave_max(hi[k]); }
+    if (lane == 0)
+      for (int k = 0; k < 3; ++k) { sh[w][k] = lo[k]; sh[w][3 + k] = hi[k]; }
+  }
+  __syncthreads();
+  double L = 0.0;
+  for (int k = 0; k < 3; ++k) {
+    double a = sh[0][k], b = sh[0][3 + k];
+    for (uint32_t q = 1; q < nw; ++q) { a = fmin(a, sh[q][k]); b = fmax(b, sh[q][3 + k]); }
+    c[k] = a;
+    L = fmax(L, b - a);
+  }
+  c[3] = L == 0.0 ? 1.0 : L;
+}
+
+// Half-tiles of keys in sorted order; also writes the cubes.
+template <bool kDeep>
+__global__ __launch_bounds__(kSysThreads) void k_sort_runs(
+    const int32_t *__restrict__ gate, const double *__restrict__ pos,
+    const Tile *__restrict__ tiles, const uint32_t *__restrict__ sys_tile0, int S,
+    const double *__restrict__ part, double *__restrict__ cube, uint64_t *__restrict__ key,
+    uint64_t *__restrict__ klo, uint32_t *__restrict__ val) {
+  if (gate && *gate <= 0) return;   // nothing active: skipped
+  constexpr int kItems = kRun / kSysThreads;
+  __shared__ uint64_t hi[kRun];
+  __shared__ uint64_t lo[kDeep ? kRun : 1];
+  __shared__ uint16_t perm[kRun];
+  __shared__ __align__(16) Half cnt[kSysWaves][kSortDigits];
+  __shared__ __align__(16) Half base[kSortDigits];
+  __shared__ uint32_t wtot[kSortDigits / 128];
+  __shared__ double sh[kSysWaves][6];
+  constexpr uint32_t kPer = kSortTile / kRun;
+  const uint32_t tid = threadIdx.x, tb = blockIdx.x / kPer;
+  const Tile t = tiles[tb];
+  const uint32_t a = t.start + (blockIdx.x % kPer) * kRun;
+  if (blockIdx.x == 0)                 // empty systems
+    for (int s = tid; s < S; s += kSysThreads)
+      if (sys_tile0[s] == sys_tile0[s + 1])
+        for (int k = 0; k < 4; ++k) cube[4 * s + k] = k == 3 ? 1.0 : 0.0;
+  if (a >= t.end) return;
+  const uint32_t ns = min((uint32_t)kRun, t.end - a);
+  double x[kItems][3];
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    const uint32_t i = (uint32_t)(kSysThreads * r) + tid;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) x[r][k] = i < ns ? pos[3 * ((size_t)a + i) + k] : 0.0;
+  }
+  const int s = tile_system(sys_tile0, S, tb);
+  const uint32_t t0 = sys_tile0[s];
+  double c[4];
+  cube_of<kSysThreads>(part, t0, sys_tile0[s + 1], sh, c);
+  if (a == tiles[t0].start && tid < 4u)
+    cube[4 * s + tid] = tid == 0u ? c[0] : tid == 1u ? c[1] : tid == 2u ? c[2] : c[3];
+  const double sigma = (kDeep ? 4398046511104.0 : 2097152.0) / c[3];
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    const uint32_t i = (uint32_t)(kSysThreads * r) + tid;
+    if (i >= ns) continue;
+    if constexpr (kDeep) {
+      keys42(x[r], c, sigma, hi[i], lo[i]);
+    } else {
+      const uint64_t q = 0x1FFFFFull;
+      hi[i] = morton21(quantise(x[r][0], c[0], sigma, q), quantise(x[r][1], c[1], sigma, q),
+                       quantise(x[r][2], c[2], sigma, q));
+    }
+    perm[i] = (uint16_t)i;
+  }
+  __syncthreads();
+  lds_sort<kItems, kDeep>(hi, lo, perm, cnt, base, wtot, ns);
+#pragma unroll
+  for (int r = 0; r < kItems; ++r) {
+    const uint32_t j = (uint32_t)(kSysThreads * r) + tid;
+    if (j >= ns) continue;
+    const uint32_t p = perm[j], g = a + j;
+    key[g] = hi[p];
+    if constexpr (kDeep) klo[g] = lo[p];
+    val[g] = a + p;
+  }
+}
+
+// key k before e, or (or_equal) not after it
+template <bool kDeep>
+__device__ __forceinline__ bool key_before(uint64_t kh, uint64_t kl, uint64_t eh, uint64_t el,
+                                           bool or_equal) {
+  if constexpr (kDeep) {
+    if (kh != eh) return kh < eh;
+    return or_equal ? kl <= el : kl < el;
+  } else {
+    return or_equal ? kh <= eh : kh < eh;
+  }
+}
+
+// Number of keys of run [r0, r0 + m) before e, found by one wave: 64 probes a round.
+template <bool kDeep>
+__device__ __forceinline__ uint32_t wave_bound(const uint64_t *__restrict__ kin,
+                                               const uint64_t *__restrict__ lin, uint32_t r0,
+                                               uint32_t m, uint64_t eh, uint64_t el,
+                                               bool or_equal) {
+  const uint32_t lane = threadIdx.x & 63u;
+  uint32_t lo = 0;
+  while (m > 0) {
+    const uint32_t step = (m + 63u) / 64u;
+    const uint32_t q = r0 + lo + min(step * (lane + 1u), m) - 1u;
+    const bool p = key_before<kDeep>(kin[q], kDeep ? lin[q] : 0ull, eh, el, or_equal);
+    const uint32_t c = (uint32_t)__popcll(__ballot(p));
+    if (c == 64u) return lo + m;
+    lo += c * step;
+    m = min(step, m - c * step) - 1u;
+  }
+  return lo;
+}
+
+// One round: groups of kWays runs of `run` keys (the last of a system shorter).
+template <bool kDeep>
+__global__ __launch_bounds__(kMergeChunk) void k_merge_runs(
+    const int32_t *__restrict__ gate, const Tile *__restrict__ tiles,
+    const uint32_t *__restrict__ sys_tile0, int S, const int64_t *__restrict__ sysoff,
+    uint32_t run, const uint64_t *__restrict__ kin, const uint64_t *__restrict__ lin,
+    const uint32_t *__restrict__ vin, uint64_t *__restrict__ kout, uint64_t *__restrict__ lout,
+    uint32_t *__restrict__ vout, uint32_t *__restrict__ rank) {
+  if (gate && *gate <= 0) return;   // nothing active: skipped
+  __shared__ uint64_t sk[kMergeKeys];
+  __shared__ uint64_t sl[kDeep ? kMergeKeys : 1];
+  __shared__ uint32_t lo_sh[kWays], hi_sh[kWays];
+  constexpr uint32_t kPer = kSortTile / kMergeChunk, kWaves = kMergeChunk / 64;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, tb = blockIdx.x / kPer;
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  const Tile t = tiles[tb];
+  const uint32_t a = t.start + (blockIdx.x % kPer) * kMergeChunk;
+  if (a >= t.end) return;
+  const uint32_t m = min((uint32_t)kMergeChunk, t.end - a);
+  const int s = tile_system(sys_tile0, S, tb);
+  const uint32_t so = (uint32_t)sysoff[s], se = (uint32_t)sysoff[s + 1];
+  const uint32_t mine = (a - so) / run;              // run of the system, of its group of kWays
+  const uint32_t g0 = mine - mine % kWays, own = mine - g0;
+  const uint32_t gs = so + g0 * run;
+  const uint32_t ge = (uint32_t)min<uint64_t>(se, gs + (uint64_t)kWays * run);   // end of the group
+  // the own key, and where the chunk's first and last keys fall in the other runs
+  const uint32_t i = a + min(tid, m - 1u);
+  const uint64_t eh = kin[i], el = kDeep ? lin[i] : 0ull;
+  const uint32_t v = vin[i];
+  const uint64_t fh = kin[a], fl = kDeep ? lin[a] : 0ull;
+  const uint64_t zh = kin[a + m - 1u], zl = kDeep ? lin[a + m - 1u] : 0ull;
+  for (uint32_t q = w; q < 2u * kWays; q += kWaves) {   // a wave per run and end
+    const uint32_t r = q % kWays;
+    const bool last = q >= kWays;
+    const uint32_t r0 = (uint32_t)min<uint64_t>(ge, gs + (uint64_t)r * run), len = min(ge - r0, run);
+    uint32_t x = 0;
+    if (r != own && len > 0u)
+      x = wave_bound<kDeep>(kin, lin, r0, len, last ? zh : fh, last ? zl : fl, r < own);
+    if (lane == 0) (last ? hi_sh : lo_sh)[r] = x;
+  }
+  __syncthreads();
+  uint32_t lo[kWays], len[kWays], off[kWays], tot = 0, longest = 0, dst = i - mine * run - so;
+#pragma unroll
+  for (int r = 0; r < kWays; ++r) {
+    lo[r] = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo_sh[r]);
+    len[r] = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi_sh[r]) - lo[r];
+    off[r] = tot;
+    tot += len[r];
+    longest = max(longest, len[r]);
+    dst += lo[r];
+  }
+  const bool fits = tot <= (uint32_t)kMergeKeys;
+  if (fits) {
+#pragma unroll
+    for (int r = 0; r < kWays; ++r) {
+      const uint32_t g = gs + (uint32_t)r * run + lo[r];
+      for (uint32_t q = tid; q < len[r]; q += kMergeChunk) {
+        sk[off[r] + q] = kin[g + q];
+        if constexpr (kDeep) sl[off[r] + q] = lin[g + q];
+      }
+    }
+    __syncthreads();
+  }
+  if (longest > 0u) {
+    uint32_t p[kWays];
+#pragma unroll
+    for (int r = 0; r < kWays; ++r) p[r] = 0;
+    // the searches of all runs step by step together
+    for (uint32_t step = 1u << (31 - __clz((int)longest)); step > 0u; step >>= 1) {
+#pragma unroll
+      for (int r = 0; r < kWays; ++r) {
+        const uint32_t q = p[r] + step;
+        if (q <= len[r]) {
+          uint64_t kh, kl = 0ull;
+          if (fits) {
+            kh = sk[off[r] + q - 1u];
+            if constexpr (kDeep) kl = sl[off[r] + q - 1u];
+          } else {
+            const uint32_t g = gs + (uint32_t)r * run + lo[r] + q - 1u;
+            kh = kin[g];
+            if constexpr (kDeep) kl = lin[g];
+          }
+          if (key_before<kDeep>(kh, kl, eh, el, (uint32_t)r < own)) p[r] = q;
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kWays; ++r) dst += p[r];
+  }
+  if (tid < m) {
+    dst += gs;
+    kout[dst] = eh;
+    if constexpr (kDeep) lout[dst] = el;
+    vout[dst] = v;
+    if (rank) rank[v] = dst;   // last round: caller index -> sorted position
+  }
+}
+
+// Whether the sort merges runs (else radix passes): the runs and rounds took
+// as long as the radix passes at 1.5M particles with one key word (a step of
+// 131072 stars 740 -> 686 us, 1.5M 5670 -> 5660, 3M 11210 -> 11330) and at
+// 4M with two, where the radix sort runs twice (500000 stars 2605 -> 2428 us,
+// 1.5M 8190 -> 8003, 4M 22.6 ms both).
+bool sort_merges(const tg_ctx *c) {
+  return c->n > 0 && c->n <= (c->max_level > kMaxLevel ? 1 << 22 : 3 << 19);
+}
+
+hipError_t launch_sort_merge(tg_ctx *c, const double *pos) {
+  Buffers &b = c->b;
+  const bool deep = c->max_level > kMaxLevel;
+  const int nt = (int)c->n_tiles;
+  hipLaunchKernelGGL(k_cube_part, dim3(nt), dim3(256), 0, c->stream, c->gate, pos,
+                     b.tiles, b.cube_part, b.err);
+  int rounds = 0;
+  for (int64_t len = kRun; len < c->max_sys; len *= kWays) ++rounds;
+  int at = rounds & 1;                 // the last round ends in the first buffers
+  auto runs = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nt * (kSortTile / kRun)), dim3(kSysThreads), 0, c->stream,
+                       c->gate, pos, b.tiles, b.sys_tile0, c->S, b.cube_part, b.cube, b.key[at],
+                       b.klo[at], b.val[at]);
+  };
+  deep ? runs(k_sort_runs<true>) : runs(k_sort_runs<false>);
+  int64_t len = kRun;
+  for (int q = 0; q < rounds; ++q, at ^= 1, len *= kWays) {
+    auto merge = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(nt * (kSortTile / kMergeChunk)), dim3(kMergeChunk), 0,
+                         c->stream, c->gate, b.tiles, b.sys_tile0, c->S, b.sysoff, (uint32_t)len,
+                         b.key[at], b.klo[at], b.val[at], b.key[at ^ 1], b.klo[at ^ 1],
+                         b.val[at ^ 1], q == rounds - 1 ? b.rank : nullptr);
+    };
+    deep ? merge(k_merge_runs<true>) : merge(k_merge_runs<false>);
+  }
   return hipGetLastError();
 }
 

@@ -338,6 +338,9 @@ hipError_t launch_sort(tg_ctx *c);
 hipError_t launch_keys_lo(tg_ctx *c, const double *pos);
 // cube, keys, sort, gather and common digits of systems of one tile at most
 hipError_t launch_sort_systems(tg_ctx *c, const double *pos, const double *mass);
+// cube, keys and sort by merging sorted runs, where sort_merges
+bool sort_merges(const tg_ctx *c);
+hipError_t launch_sort_merge(tg_ctx *c, const double *pos);
 hipError_t launch_gather(tg_ctx *c, const double *pos, const double *mass);
 
 // k_tree.hip

@@ -306,6 +306,9 @@ static tg_status build_tree_impl(tg_ctx *c, const double *pos, const double *mas
   c->have_tree = c->have_moments = false;
   if (c->one_tile) {
     TG_HIP(launch_sort_systems(c, pos, mass));
+  } else if (sort_merges(c)) {
+    TG_HIP(launch_sort_merge(c, pos));
+    TG_HIP(launch_gather(c, pos, mass));
   } else {
     TG_HIP(launch_cube_keys(c, pos));
     TG_HIP(launch_sort(c));

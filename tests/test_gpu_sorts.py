@@ -1,8 +1,9 @@
-"""Keys, stable sort and tree where the sort takes another path: systems of one
-tile at most (one block sorts each), at the edges of its particles per thread,
-and one particle more than that.  Coincident particles check that equal keys
-keep their order.  Everything is an integer structure or a cube: bit-exact
-against the oracle."""
+"""Keys, stable sort and tree on each path of the sort: systems of one tile at
+most (one block sorts each) at the edges of its particles per thread, merged
+runs at the edges of runs, chunks and rounds, with runs that lie inside one gap
+of another and runs of equal keys, and the radix passes just past the merges.
+Coincident particles check that equal keys keep their order.  Everything is an
+integer structure or a cube: bit-exact against the oracle."""
 import sys
 
 import numpy as np
@@ -55,3 +56,44 @@ def test_batch(sizes, levels):
     say("sort batch", sizes, levels)
     _check(np.concatenate([_cloud(n, 7 + n) for n in sizes if n]), levels,
            [0] + list(np.cumsum(sizes)))
+
+
+@pytest.mark.parametrize("levels", [21, 42])
+@pytest.mark.parametrize("n", [6143, 8192, 8193, 8705, 32768, 32769, 70001])
+def test_merged_runs(n, levels):
+    say("merge", n, levels)
+    _check(_cloud(n, 90 + n), levels)
+
+
+@pytest.mark.parametrize("levels", [21, 42])
+def test_merged_batch(levels):
+    say("merge batch", levels)
+    sizes = (9000, 0, 2048, 2049, 33000)
+    _check(np.concatenate([_cloud(n, 11 + n) for n in sizes if n]), levels,
+           [0] + list(np.cumsum(sizes)))
+
+
+@pytest.mark.parametrize("levels", [21, 42])
+@pytest.mark.parametrize("kind", ["gap", "equal", "sorted"])
+def test_merged_runs_special(kind, levels):
+    say("merge", kind, levels)
+    rng = np.random.default_rng(5)
+    if kind == "gap":        # runs 1 to 3 between two keys of run 0: more than is staged
+        pos = rng.uniform(-1.0, 1.0, (9000, 3))
+        pos[2048:8192] = 0.3 + 1e-5 * rng.uniform(0.0, 1.0, (6144, 3))
+    elif kind == "equal":
+        pos = np.full((9000, 3), 0.25)
+        pos[4000:4500] = rng.uniform(-1.0, 1.0, (500, 3))
+    else:
+        pos = rng.uniform(-1.0, 1.0, (20000, 3))
+        pos = pos[oracle.build_tree(pos, None, 8).perm]
+    _check(pos, levels)
+
+
+@pytest.mark.parametrize("sizes,levels", [(((3 << 19) + 1,), 21), ((1000003, 0, 5, 600001), 21),
+                                          (((1 << 22) + 1,), 42)])
+def test_radix_passes(sizes, levels):
+    say("radix", sizes, levels)
+    pos = np.random.default_rng(3).normal(size=(sum(sizes), 3))
+    off = [0] + list(np.cumsum(sizes)) if len(sizes) > 1 else None
+    _check(pos, levels, off)
