@@ -5,7 +5,7 @@
 // Many targets of one segment (checks of the tree's forces, perturbers on
 // perturbers): blocks of 64 or 128 targets over source tiles in LDS.  Few
 // targets (SMBHs feeling a million stars): one 256-thread block per (target,
-// range of kFewPerBlock sources), threads striding through the range with
+// range of few_span sources), threads striding through the range with
 // coalesced loads, the block's sums combined in a fixed tree order and the
 // per-block partials summed in a second ordered pass.  Anything else
 // (several segments, a handful of pairs): one thread per target and source
@@ -268,22 +268,20 @@ __device__ __forceinline__ void block_csum4(CSum r[4], double (*ss)[256], double
   }
 }
 
-constexpr int kFewPerBlock = 4096;   // sources per block in the few-target path
-
 // grid (blocks per target, targets): block b of target i sums sources
-// [b kFewPerBlock, (b + 1) kFewPerBlock) of i's segment into part[b nt + i].
+// [b span, (b + 1) span) of i's segment into part[b nt + i].
 __global__ __launch_bounds__(256) void k_direct_few(
     const double *__restrict__ spos, const double *__restrict__ sm,
     const double *__restrict__ seps, double seps_all, const double *__restrict__ tpos,
     const double *__restrict__ teps, int64_t nt, const int64_t *__restrict__ sseg,
-    const int64_t *__restrict__ tseg, int nseg, int self_pairs, int soft,
+    const int64_t *__restrict__ tseg, int nseg, int self_pairs, int soft, int span,
     double *__restrict__ part) {
 #pragma clang fp contract(off)
   __shared__ double ss[4][256], sc[4][256];
   const int64_t i = blockIdx.y;
   const int s = seg_of(tseg, nseg, i);
-  const int64_t j0 = sseg[s] + (int64_t)blockIdx.x * kFewPerBlock;
-  const int64_t j1 = min(sseg[s + 1], j0 + kFewPerBlock);
+  const int64_t j0 = sseg[s] + (int64_t)blockIdx.x * span;
+  const int64_t j1 = min(sseg[s + 1], j0 + span);
   const double xi = tpos[3 * i], yi = tpos[3 * i + 1], zi = tpos[3 * i + 2];
   const double ei = teps[i];
   CSum r[4];
@@ -340,10 +338,10 @@ __global__ __launch_bounds__(256) void k_direct_reduce(int64_t nt, int nchunks,
 
 // The stars' drift fused with the SMBH <- star sums of a block substep
 // (one system, at most kDriftSmbhMax SMBHs): block b drifts the stars
-// [b kFewPerBlock, (b + 1) kFewPerBlock) (x <- x + v dt with the operations
-// of k_drift; frozen stars stay) and sums their pull on every SMBH at the
-// drifted positions with the ranges, thread order and block reduction of
-// k_direct_few, so k_direct_reduce turns the partials into the same totals.
+// [b span, (b + 1) span) (x <- x + v dt with the operations of k_drift;
+// frozen stars stay) and sums their pull on every SMBH at the drifted
+// positions with the ranges, thread order and block reduction of
+// k_direct_few, so k_smbh_finish turns the partials into the same totals.
 // The stars' positions are read once instead of twice.
 constexpr int kDriftSmbhMax = 4;
 
@@ -351,13 +349,13 @@ template <int kNB>
 __global__ __launch_bounds__(256) void k_drift_smbh(
     double *__restrict__ pos, const double *__restrict__ vel, const uint8_t *__restrict__ frozen,
     int64_t n, double dt, const double *__restrict__ sm, double seps,
-    const double *__restrict__ bpos, const double *__restrict__ beps, int soft,
+    const double *__restrict__ bpos, const double *__restrict__ beps, int soft, int span,
     double *__restrict__ part) {
 #pragma clang fp contract(off)
   constexpr int nb = kNB;
   __shared__ double ss[4][256], sc[4][256];
-  const int64_t j0 = (int64_t)blockIdx.x * kFewPerBlock;
-  const int64_t j1 = min(n, j0 + kFewPerBlock);
+  const int64_t j0 = (int64_t)blockIdx.x * span;
+  const int64_t j1 = min(n, j0 + span);
   double bx[nb], by[nb], bz[nb], be[nb];
 #pragma unroll
   for (int i = 0; i < nb; ++i) {
@@ -405,34 +403,137 @@ __global__ __launch_bounds__(256) void k_drift_smbh(
 // against 70.
 constexpr int64_t kFewTargets = 127;
 
+// Sources per block: short ranges below 2^20 sources, where long ones leave
+// most of the chip idle (131072 stars on one SMBH: 12.2 us in 32 blocks of
+// 4096, 6.6 in 128 of 1024), if their partial sums fit.
+static int few_span(int64_t part_cap, int64_t n, int64_t nt) {
+  return n < (1 << 20) && (n + 1023) / 1024 * nt * 8 <= part_cap ? 1024 : 4096;
+}
+
 static bool few_path(int64_t part_cap, int64_t n, int64_t nt) {
-  if (!(nt <= kFewTargets && n >= 2 * kFewPerBlock)) return false;
-  const int64_t bpt = (n + kFewPerBlock - 1) / kFewPerBlock;
+  if (!(nt <= kFewTargets && n >= 8192)) return false;
+  const int64_t bpt = (n + 4095) / 4096;
   return bpt * nt * 8 <= part_cap && bpt <= 65535;
+}
+
+// The totals of the stars' partial sums on an SMBH (as k_direct_reduce) plus
+// the pull of the other SMBHs of its segment (as k_direct; formed by another
+// wave meanwhile), one block per SMBH: one launch of 4.6 us where two took 9.
+// With kStep (one segment, one block) the next idle substep's kicks and drift
+// of the SMBHs follow, as k_bh_substep does them (another launch of 4.7 us;
+// 128 substeps of 4.2M stars 29.2 -> 28.6 ms).  Bound by latency: the partial
+// sums' loads and eight steps of the block's tree.
+template <bool kStep>
+__global__ __launch_bounds__(256) void k_smbh_finish(
+    int nb, int nchunks, const double *__restrict__ part, double *bpos,
+    const double *__restrict__ bmass, const double *__restrict__ beps,
+    const int64_t *__restrict__ bseg, int nseg, int soft, double *__restrict__ acc,
+    double *__restrict__ pot, double *__restrict__ vel, double dt, int64_t *__restrict__ kctr) {
+#pragma clang fp contract(off)
+  __shared__ double ss[4][256], sc[4][256], pair[4], a_new[3 * kDriftSmbhMax];
+  for (int i = blockIdx.x; i < nb; i += gridDim.x) {
+    CSum r[4];
+    for (int c = threadIdx.x; c < nchunks; c += 256) {
+      const double *o = part + 8 * ((size_t)c * nb + i);
+      for (int k = 0; k < 4; ++k) {
+        r[k].add(o[2 * k]);
+        r[k].add(o[2 * k + 1]);
+      }
+    }
+    if (threadIdx.x == 192) {
+      int64_t j0 = 0, j1 = nb;
+      if (bseg) {
+        const int s = seg_of(bseg, nseg, i);
+        j0 = bseg[s];
+        j1 = bseg[s + 1];
+      }
+      CSum q[4];
+      for (int64_t j = j0; j < j1; ++j) {
+        if (j == i) continue;
+        const double ep = fmax(beps[j], beps[i]);
+        const double dx = bpos[3 * i] - bpos[3 * j], dy = bpos[3 * i + 1] - bpos[3 * j + 1];
+        const double dz = bpos[3 * i + 2] - bpos[3 * j + 2];
+        double mD1, mD3;
+        pair_terms(dx, dy, dz, ep, bmass[j], soft, mD1, mD3);
+        q[0].add(-mD3 * dx);
+        q[1].add(-mD3 * dy);
+        q[2].add(-mD3 * dz);
+        q[3].add(-mD1);
+      }
+      for (int k = 0; k < 4; ++k) pair[k] = q[k].get();
+    }
+    block_csum4(r, ss, sc);
+    if (threadIdx.x == 0) {
+      for (int k = 0; k < 3; ++k) {
+        const double a = (ss[k][0] + sc[k][0]) + pair[k];
+        acc[3 * i + k] = a;
+        if constexpr (kStep) a_new[3 * i + k] = a;
+      }
+      if (pot) pot[i] = (ss[3][0] + sc[3][0]) + pair[3];
+    }
+    __syncthreads();
+  }
+  if constexpr (kStep) {
+    const int64_t k = kctr[0];
+    const double h = dt * 0.5;
+    const int t = threadIdx.x;
+    if (t < 3 * nb) {
+      double v = vel[t];
+      if (k != 0) v = v + a_new[t] * h;
+      v = v + a_new[t] * h;
+      vel[t] = v;
+      bpos[t] = bpos[t] + v * dt;
+    }
+    __syncthreads();
+    if (t == 0) kctr[0] = k + 1;
+  }
 }
 
 bool drift_smbh_fits(const tg_ctx *c, int64_t n, int32_t nb) {
   return nb >= 1 && nb <= kDriftSmbhMax && few_path(c->b.dpart_cap, n, nb);
 }
 
-hipError_t launch_drift_smbh(tg_ctx *c, double *pos, const double *vel, const uint8_t *frozen,
-                             int64_t n, double dt, const double *mass, double eps,
-                             const double *bpos, const double *beps, int32_t nb,
-                             double *bacc, double *bpot) {
-  const int64_t bpt = (n + kFewPerBlock - 1) / kFewPerBlock;
-  const dim3 g((unsigned)bpt), b(256);
+hipError_t launch_drift_smbh(tg_ctx *c, const tg_system *y, double dt, int64_t *next_k) {
+  const int64_t n = y->n;
+  const int32_t nb = y->n_bh;
+  const int span = few_span(c->b.dpart_cap, n, nb);
+  const int64_t bpt = (n + span - 1) / span;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)bpt), dim3(256), 0, c->stream, y->pos, y->vel,
+                       y->frozen, n, dt, y->mass, y->eps, y->bh_pos, y->bh_eps, c->soft, span,
+                       c->b.dpart);
+  };
   switch (nb) {
-    case 1: hipLaunchKernelGGL(k_drift_smbh<1>, g, b, 0, c->stream, pos, vel, frozen, n, dt, mass,
-                               eps, bpos, beps, c->soft, c->b.dpart); break;
-    case 2: hipLaunchKernelGGL(k_drift_smbh<2>, g, b, 0, c->stream, pos, vel, frozen, n, dt, mass,
-                               eps, bpos, beps, c->soft, c->b.dpart); break;
-    case 3: hipLaunchKernelGGL(k_drift_smbh<3>, g, b, 0, c->stream, pos, vel, frozen, n, dt, mass,
-                               eps, bpos, beps, c->soft, c->b.dpart); break;
-    default: hipLaunchKernelGGL(k_drift_smbh<4>, g, b, 0, c->stream, pos, vel, frozen, n, dt, mass,
-                                eps, bpos, beps, c->soft, c->b.dpart); break;
+    case 1: go(k_drift_smbh<1>); break;
+    case 2: go(k_drift_smbh<2>); break;
+    case 3: go(k_drift_smbh<3>); break;
+    default: go(k_drift_smbh<4>); break;
   }
-  hipLaunchKernelGGL(k_direct_reduce, dim3((unsigned)std::min<int64_t>(nb, 4096)), dim3(256), 0,
-                     c->stream, (int64_t)nb, (int)bpt, 0, c->b.dpart, bacc, bpot);
+  auto finish = [&](auto kernel, int blocks) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, c->stream, nb, (int)bpt, c->b.dpart,
+                       y->bh_pos, y->bh_mass, y->bh_eps, nullptr, 1, c->soft, y->bh_acc,
+                       y->bh_pot, y->bh_vel, dt, next_k);
+  };
+  next_k ? finish(k_smbh_finish<true>, 1) : finish(k_smbh_finish<false>, nb);
+  return hipGetLastError();
+}
+
+// From 64 SMBHs on their mutual pull has a kernel of its own (tiles).
+bool smbh_sums_fit(const tg_ctx *c, int64_t max_stars, int32_t nb) {
+  return nb >= 1 && nb < 64 && few_path(c->b.dpart_cap, max_stars, nb);
+}
+
+hipError_t launch_smbh_sums(tg_ctx *c, const int64_t *dseg, const tg_system *y, int nseg,
+                            int64_t max_stars) {
+  const int32_t nb = y->n_bh;
+  const int span = few_span(c->b.dpart_cap, max_stars, nb);
+  const int64_t bpt = (max_stars + span - 1) / span;
+  hipLaunchKernelGGL(k_direct_few, dim3((unsigned)bpt, (unsigned)nb), dim3(256), 0, c->stream,
+                     y->pos, y->mass, nullptr, y->eps, y->bh_pos, y->bh_eps, (int64_t)nb, dseg,
+                     dseg + (nseg + 1), nseg, 0, c->soft, span, c->b.dpart);
+  hipLaunchKernelGGL(k_smbh_finish<false>, dim3(nb), dim3(256), 0, c->stream, nb, (int)bpt,
+                     c->b.dpart, y->bh_pos, y->bh_mass, y->bh_eps, dseg + (nseg + 1), nseg,
+                     c->soft, y->bh_acc, y->bh_pot, nullptr, 0.0, nullptr);
   return hipGetLastError();
 }
 
@@ -490,10 +591,11 @@ hipError_t launch_direct_env(const DirectEnv &e, const int64_t *dseg, const doub
                              double *acc, double *pot) {
   if (nt == 0) return hipSuccess;
   if (few_path(e.part_cap, max_seg_src, nt)) {
-    const int64_t bpt = (max_seg_src + kFewPerBlock - 1) / kFewPerBlock;
+    const int span = few_span(e.part_cap, max_seg_src, nt);
+    const int64_t bpt = (max_seg_src + span - 1) / span;
     hipLaunchKernelGGL(k_direct_few, dim3((unsigned)bpt, (unsigned)nt), dim3(256), 0,
                        e.stream, spos, sm, seps, seps_all, tpos, teps, nt, dseg,
-                       dseg + (nseg + 1), nseg, self_pairs, e.soft, e.part);
+                       dseg + (nseg + 1), nseg, self_pairs, e.soft, span, e.part);
     hipLaunchKernelGGL(k_direct_reduce, dim3((unsigned)std::min<int64_t>(nt, 4096)),
                        dim3(256), 0, e.stream, nt, (int)bpt, accumulate, e.part, acc, pot);
     return hipGetLastError();

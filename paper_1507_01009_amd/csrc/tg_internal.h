@@ -402,10 +402,12 @@ hipError_t launch_chain_forces(tg_ctx *c, const tg_chain *ch, const int32_t *idx
 // stars' drift fused with their sums on the SMBHs (one system); fits says
 // whether the few-target sum path applies (then the totals are bit-equal)
 bool drift_smbh_fits(const tg_ctx *c, int64_t n, int32_t nb);
-hipError_t launch_drift_smbh(tg_ctx *c, double *pos, const double *vel, const uint8_t *frozen,
-                             int64_t n, double dt, const double *mass, double eps,
-                             const double *bpos, const double *beps, int32_t nb,
-                             double *bacc, double *bpot);
+// (with next_k also the SMBHs' kicks and drift of the next idle substep, *next_k += 1)
+hipError_t launch_drift_smbh(tg_ctx *c, const tg_system *y, double dt, int64_t *next_k);
+// SMBH <- star and SMBH <-> SMBH sums in two launches, where they fit
+bool smbh_sums_fit(const tg_ctx *c, int64_t max_stars, int32_t nb);
+hipError_t launch_smbh_sums(tg_ctx *c, const int64_t *dseg, const tg_system *y, int nseg,
+                            int64_t max_stars);
 hipError_t launch_direct(tg_ctx *c, const int64_t *dseg, const double *spos,
                          const double *sm, const double *seps, double seps_all,
                          int64_t ns, const double *tpos,

@@ -623,15 +623,11 @@ tg_status tg_direct_fp64(tg_ctx *c, const double *spos, const double *sm,
   return TG_OK;
 } TG_HOST_CATCH("tg_direct_fp64")
 
-// Direct sums where every source shares one softening (stars): the same
-// kernels with a broadcast softening.
-static tg_status tg_direct_fp64_eps(tg_ctx *c, const double *spos, const double *sm,
-                             double seps, int64_t ns, const double *tpos,
-                             const double *teps, int64_t nt,
-                             const int64_t *sseg, const int64_t *tseg, int32_t nseg,
-                             double *acc, double *pot) try {
-  if (!c) return fail(TG_EINVAL, "tg_direct_fp64_eps: NULL context");
-  if (nt == 0) return TG_OK;
+// Sums of each system's stars on its SMBHs, where every source shares one
+// softening: the kernels of tg_direct_fp64 with a broadcast softening.
+// pairs_done: the SMBHs' mutual pull came with them.
+static tg_status smbh_star_sums(tg_ctx *c, const tg_system *y, const int64_t *sseg,
+                                const int64_t *tseg, int32_t nseg, bool *pairs_done) try {
   int slot = -1;
   std::vector<int64_t> seg(2 * (nseg + 1));
   for (int s = 0; s <= nseg; ++s) { seg[s] = sseg[s]; seg[nseg + 1 + s] = tseg[s]; }
@@ -641,7 +637,7 @@ static tg_status tg_direct_fp64_eps(tg_ctx *c, const double *spos, const double 
     if (c->dseg_host[k] == seg) slot = k;
   if (slot < 0) {
     if (c->capturing)
-      return fail(TG_ESTATE, "tg_direct_fp64_eps: new segment layout during capture");
+      return fail(TG_ESTATE, "smbh_star_sums: new segment layout during capture");
     if ((int)c->dseg_host.size() < kSegSlots) {
       c->dseg_host.push_back(seg);
       slot = (int)c->dseg_host.size() - 1;
@@ -655,10 +651,15 @@ static tg_status tg_direct_fp64_eps(tg_ctx *c, const double *spos, const double 
                           sizeof(int64_t) * seg.size(), hipMemcpyHostToDevice, c->stream));
     TG_HIP(hipStreamSynchronize(c->stream));
   }
-  TG_HIP(launch_direct(c, c->b.dseg + slot * kSegSlotLen, spos, sm, nullptr, seps, ns,
-                       tpos, teps, nt, nseg, max_src, 0, 0, acc, pot));
+  const int64_t *dseg = c->b.dseg + slot * kSegSlotLen;
+  *pairs_done = smbh_sums_fit(c, max_src, y->n_bh);
+  if (*pairs_done)
+    TG_HIP(launch_smbh_sums(c, dseg, y, nseg, max_src));
+  else
+    TG_HIP(launch_direct(c, dseg, y->pos, y->mass, nullptr, y->eps, y->n, y->bh_pos, y->bh_eps,
+                         y->n_bh, nseg, max_src, 0, 0, y->bh_acc, y->bh_pot));
   return TG_OK;
-} TG_HOST_CATCH("tg_direct_fp64_eps")
+} TG_HOST_CATCH("smbh_star_sums")
 
 // Kick, drift and active set with an optional mask of frozen stars (ghost
 // chain members inside whole steps: no kick, no drift, never active).
@@ -938,7 +939,7 @@ static tg_status check_system(const tg_system *y, const char *who) {
 // tree is rebuilt when the substep counter k is a multiple of it (or no
 // build exists yet) and refitted otherwise; both choices are made on the
 // device, so a captured substep replays correctly.
-static tg_status smbh_sums(tg_ctx *c, const tg_system *y, bool stars_done = false);
+static tg_status smbh_sums(tg_ctx *c, const tg_system *y);
 
 static tg_status forces_impl(tg_ctx *c, const tg_system *y, const int32_t *idx,
                              const int32_t *n_act, const int64_t *k, int32_t rebuild_every) {
@@ -985,28 +986,18 @@ static tg_status forces_impl(tg_ctx *c, const tg_system *y, const int32_t *idx,
   return smbh_sums(c, y);
 }
 
-// SMBH <- star sums over each system's stars (skipped with stars_done: a
-// fused launch already formed them), then SMBH <-> SMBH.
-static tg_status smbh_sums(tg_ctx *c, const tg_system *y, bool stars_done) try {
-  tg_status st = TG_OK;
-  if (y->n_bh > 0) {
-    // SMBHs feel the stars of their own system, then each other
-    std::vector<int64_t> so = c->sysoff_host;
-    std::vector<int64_t> bs(y->n_sys + 1);
-    for (int s = 0; s <= y->n_sys; ++s) bs[s] = y->bh_seg ? y->bh_seg[s] : (s ? y->n_bh : 0);
-    const int nseg = y->n_sys;
-    // star softening: the stars' eps for every star
-    if (!stars_done) {
-      st = tg_direct_fp64_eps(c, y->pos, y->mass, y->eps, y->n, y->bh_pos, y->bh_eps,
-                              y->n_bh, so.data(), bs.data(), nseg, y->bh_acc, y->bh_pot);
-      if (st != TG_OK) return st;
-    }
-    st = tg_direct_fp64(c, y->bh_pos, y->bh_mass, y->bh_eps, y->n_bh, y->bh_pos,
-                        y->bh_eps, y->n_bh, bs.data(), bs.data(), nseg, 1, 1, y->bh_acc,
-                        y->bh_pot);
-    if (st != TG_OK) return st;
-  }
-  return TG_OK;
+// SMBH <- star sums over each system's stars, then SMBH <-> SMBH.
+static tg_status smbh_sums(tg_ctx *c, const tg_system *y) try {
+  if (y->n_bh <= 0) return TG_OK;
+  // SMBHs feel the stars of their own system, then each other
+  std::vector<int64_t> so = c->sysoff_host;
+  std::vector<int64_t> bs(y->n_sys + 1);
+  for (int s = 0; s <= y->n_sys; ++s) bs[s] = y->bh_seg ? y->bh_seg[s] : (s ? y->n_bh : 0);
+  bool pairs_done = false;
+  const tg_status st = smbh_star_sums(c, y, so.data(), bs.data(), y->n_sys, &pairs_done);
+  if (st != TG_OK || pairs_done) return st;
+  return tg_direct_fp64(c, y->bh_pos, y->bh_mass, y->bh_eps, y->n_bh, y->bh_pos, y->bh_eps,
+                        y->n_bh, bs.data(), bs.data(), y->n_sys, 1, 1, y->bh_acc, y->bh_pot);
 } TG_HOST_CATCH("smbh_sums")
 
 tg_status tg_forces(tg_ctx *c, const tg_system *y, const int32_t *idx,
@@ -1128,25 +1119,30 @@ extern "C" {
 // SMBHs' kicks and drift (k advances, the active count becomes 0), the
 // stars' drift and the SMBH sums.  These are exactly the launches of
 // tg_step_block that do any work when both active sets are empty.
-// With one system and a few SMBHs the stars' drift and their sums on the
-// SMBHs are one launch (the SMBHs move first; the sums come out bit for
-// bit as in tg_step_block).
-static tg_status idle_substep(tg_ctx *c, const tg_system *y, const tg_blocks *b, double dt_min) {
+// With one system and a few SMBHs a substep is two launches (the SMBHs move
+// first; the sums come out bit for bit as in tg_step_block): the stars' drift
+// with their sums on the SMBHs, and the totals with the SMBHs' mutual pull
+// and their kicks and drift for the next idle substep.
+static tg_status idle_substeps(tg_ctx *c, const tg_system *y, const tg_blocks *b, double dt_min,
+                               int64_t count) {
   tg_status st;
   const bool fused = y->n_sys == 1 && c->sysoff_host.size() == 2 &&
                      c->sysoff_host[0] == 0 && c->sysoff_host[1] == y->n &&
                      drift_smbh_fits(c, y->n, y->n_bh);
-  if (fused) {
+  for (int64_t i = 0; i < count; ++i) {
+    if (fused) {
+      if (i == 0)
+        TG_HIP(launch_bh_substep(c, y->bh_pos, y->bh_vel, y->bh_acc, y->n_bh, dt_min, b->k,
+                                 b->n_active));
+      TG_HIP(launch_drift_smbh(c, y, dt_min, i + 1 < count ? b->k : nullptr));
+      continue;
+    }
+    if ((st = drift_impl(c, y->pos, y->vel, y->n, dt_min, y->frozen))) return st;
     TG_HIP(launch_bh_substep(c, y->bh_pos, y->bh_vel, y->bh_acc, y->n_bh, dt_min, b->k,
                              b->n_active));
-    TG_HIP(launch_drift_smbh(c, y->pos, y->vel, y->frozen, y->n, dt_min, y->mass, y->eps,
-                             y->bh_pos, y->bh_eps, y->n_bh, y->bh_acc, y->bh_pot));
-    return smbh_sums(c, y, true);
+    if ((st = smbh_sums(c, y))) return st;
   }
-  if ((st = drift_impl(c, y->pos, y->vel, y->n, dt_min, y->frozen))) return st;
-  TG_HIP(launch_bh_substep(c, y->bh_pos, y->bh_vel, y->bh_acc, y->n_bh, dt_min, b->k,
-                           b->n_active));
-  return smbh_sums(c, y);
+  return TG_OK;
 }
 
 tg_status tg_step_blocks(tg_ctx *c, const tg_system *y, const tg_blocks *b, int64_t n_sub,
@@ -1187,10 +1183,7 @@ tg_status tg_step_blocks(tg_ctx *c, const tg_system *y, const tg_blocks *b, int6
     }
     idle = std::min(idle, n_sub - done);
     const double dt_min = std::ldexp(b->dt_max, -(b->nlev - 1));
-    for (int64_t i = 0; i < idle; ++i) {
-      st = idle_substep(c, y, b, dt_min);
-      if (st != TG_OK) return st;
-    }
+    if ((st = idle_substeps(c, y, b, dt_min, idle)) != TG_OK) return st;
     done += idle;
     idle_total += idle;
   }
