@@ -672,7 +672,7 @@ __global__ __launch_bounds__(kSysThreads) void k_sort_systems(
   const int s = blockIdx.x;
   const uint32_t a = (uint32_t)sysoff[s], ns = (uint32_t)(sysoff[s + 1] - sysoff[s]);
   if (s == 0 && tid < 64u) d[n + tid] = 0;
-  if (s == 0 && tid == 64u) gflag[n] = 0u;
+  if (gflag && s == 0 && tid == 64u) gflag[n] = 0u;
 
   // positions and masses (thread: particles tid, tid + 1024, ...), bounding cube
   double x[kItems][3], m[kItems];
@@ -752,7 +752,7 @@ __global__ __launch_bounds__(kSysThreads) void k_sort_systems(
     const uint64_t k = hi[p];
     key[g] = k;
     val[g] = a + p;
-    gflag[g] = 0u;
+    if (gflag) gflag[g] = 0u;
     uint32_t eq = 0;
     if (j > 0u) {
       const uint32_t q = perm[j - 1u];
@@ -785,7 +785,7 @@ hipError_t launch_sort_systems(tg_ctx *c, const double *pos, const double *mass)
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(c->S), dim3(kSysThreads), 0, c->stream, c->gate, pos, mass,
                        b.sysoff, c->n, b.cube, b.key[0], b.klo[0], b.val[0], b.rank, b.spart,
-                       b.lcp, b.gflag, b.err);
+                       b.lcp, flat_groups(c) ? nullptr : b.gflag, b.err);
   };
   if (c->max_sys <= kSysThreads)
     deep ? go(k_sort_systems<1, true>) : go(k_sort_systems<1, false>);

@@ -21,6 +21,8 @@
 // position after it with d < l (searched inside the tile, else taken from
 // a per-tile suffix minimum of the run starts of later tiles).
 //
+// The groups of the walk come with the nodes (see k_flat_flags).
+//
 // Four launches, each of fixed shape for a given N (graph-capturable):
 // k_lcp, k_flat_flags (per 256-particle tile: node levels per particle,
 // bitmaps, counts, first run starts), k_flat_scan (one block per level:
@@ -31,6 +33,9 @@ namespace tg {
 
 constexpr int kFT = 256;                 // particles per tile of the flat build
 constexpr int kHalo = 16;                // >= max leaf size
+constexpr int kGHalo = 128;              // >= max group size
+constexpr int kGWin = kFT + 2 * kGHalo;
+static_assert(kGHalo >= kMaxGroup, "group windows stay inside the halo");
 
 __device__ __forceinline__ int sys_of(const int64_t *so, int S, int64_t i) {
   int lo = 0, hi = S - 1;                // last s with so[s] <= i
@@ -58,7 +63,7 @@ __global__ __launch_bounds__(256) void k_lcp(const int32_t *__restrict__ gate, c
   load_sysoff(so, sysoff, S);
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n + 64;
        i += (int64_t)gridDim.x * blockDim.x) {
-    if (i <= n) gflag[i] = 0u;   // the group-start flags [0, n], cleared for k_group_flags
+    if (gflag && i <= n) gflag[i] = 0u;   // the group-start flags [0, n], cleared for k_group_flags
     uint32_t v = 0;
     if (i > 0 && i < n && so[sys_of(so, S, i)] != i) {
       v = common_digits(skey[i - 1], skey[i]);
@@ -68,13 +73,38 @@ __global__ __launch_bounds__(256) void k_lcp(const int32_t *__restrict__ gate, c
   }
 }
 
+// Least of each of the four bytes.
+__device__ __forceinline__ uint32_t min_bytes(uint32_t a, uint32_t b) {
+  typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+  const uint32_t m = 0x00ff00ffu;
+  const us2 e = __builtin_elementwise_min(__builtin_bit_cast(us2, a & m), __builtin_bit_cast(us2, b & m));
+  const us2 o = __builtin_elementwise_min(__builtin_bit_cast(us2, (a >> 8) & m),
+                                          __builtin_bit_cast(us2, (b >> 8) & m));
+  return __builtin_bit_cast(uint32_t, e) | __builtin_bit_cast(uint32_t, o) << 8;
+}
+
 // Per tile b of kFT particles: lt[i] = lo | top << 8 of the nodes starting
 // at i (0xffff: none); bits[l][4 b + w] = ballot of "a level-l node starts
 // here" of wave w; cnt[l][b] = nodes of level l in the tile; fst[l][b] =
 // first run start of level l in the tile (first i with d[i] < l).  ML is
-// the deepest level.
+// the deepest level.  With ng > 0 row ML + 1 of bits and cnt holds the group
+// starts, and gl[i] the level of the node whose group starts at i (0xff:
+// none).
+//
+// Groups from the digits alone: the run of level l starting at i holds more
+// than n_G particles iff mg = min(d[i+1 .. i+n_G]) >= l, so a group's node
+// at i has level g = max(lo, mg + 1) if such a node starts there and its
+// parent's run is longer than n_G: it is when g > lo, and else its length is
+// counted in the window.  A leaf holding more than n_G is a run of equal keys
+// (n_G >= n_L): its groups start every n_G particles from its start.  The
+// windows are read from a table of minima over 1, 2, 4 .. 128 bytes in LDS,
+// formed by one wave four bytes at a time (by all threads, a byte at a time
+// with barriers: 95 us at 4.2M particles instead of 84; without groups 56).
+// The flags, scan and writing of groups by kernels of their own were four
+// launches, 19 us at 131072 particles and 12 at 1021; this costs 3.
 template <int ML>
-__global__ __launch_bounds__(kFT) void k_flat_flags(const int32_t *__restrict__ gate, int64_t n, int nleaf, int S,
+__global__ __launch_bounds__(kFT) void k_flat_flags(const int32_t *__restrict__ gate, int64_t n, int nleaf,
+                                                    int ng, uint8_t *__restrict__ gl, int S,
                                                     const int64_t *__restrict__ sysoff,
                                                     const uint8_t *__restrict__ d,
                                                     uint16_t *__restrict__ lt,
@@ -134,6 +164,109 @@ __global__ __launch_bounds__(kFT) void k_flat_flags(const int32_t *__restrict__ 
   }
   if (valid) lt[i] = ex ? (uint16_t)(lo | (top << 8)) : (uint16_t)0xffff;
   const int w = tid >> 6, lane = tid & 63;
+  if (ng > 0) {
+    __shared__ uint32_t mw[8][kGWin / 4];     // mn[k][q]: least of 2^k bytes from t0 - kGHalo + q
+    __shared__ unsigned long long wb[kFT / 64];
+    __shared__ int32_t before;                // distance from t0 back to the run's start
+    const unsigned long long below = __ballot(di[0] < ML);   // starts of runs of equal keys
+    if (lane == 0) wb[w] = below;
+    if (tid == 0) before = 0x7fffffff;
+    if (w == 0) {                             // one wave: no barriers between the tables
+      constexpr int kW = kGWin / 4, kPer = kW / 64;
+      static_assert(kW % 64 == 0, "whole words per lane");
+#pragma unroll
+      for (int r = 0; r < kPer; ++r) {
+        const int64_t x = t0 - kGHalo + 4 * (64 * r + lane);   // (word-aligned, n + 64 may not be)
+        uint32_t v = 0;
+        if (x >= 0 && x + 4 <= n + 64) v = *reinterpret_cast<const uint32_t *>(d + x);
+        else
+          for (int k = 0; k < 4; ++k)
+            if (x + k >= 0 && x + k < n + 64) v |= (uint32_t)d[x + k] << (8 * k);
+        mw[0][64 * r + lane] = v;
+      }
+#pragma unroll
+      for (int k = 0; k < 7; ++k) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) {
+          const int q = 64 * r + lane, o = k < 2 ? 1 : 1 << (k - 2);
+          const uint32_t v = mw[k][q], x = q + o < kW ? mw[k][q + o] : 0u;
+          mw[k + 1][q] = min_bytes(v, k < 2 ? __builtin_amdgcn_alignbyte(x, v, 1 << k) : x);
+        }
+      }
+    }
+    __syncthreads();
+    auto mn = [&](int k, int q) -> uint32_t {
+      return reinterpret_cast<const uint8_t *>(mw[k])[q];
+    };
+    if (sd[kHalo] == ML) {                    // (the whole block) equal keys across the tile's start
+      for (int64_t hi = t0; hi > 0 && before == 0x7fffffff; hi -= 16 * kFT) {
+        const int64_t x0 = hi - 16 * (tid + 1);
+        int last = -1;
+        if (x0 >= 0)
+          for (int k = 0; k < 16; ++k)
+            if (d[x0 + k] < ML) last = k;
+        __syncthreads();                      // every thread has read `before`
+        if (last >= 0) atomicMin(&before, (int32_t)min<int64_t>(t0 - (x0 + last), 0x7ffffffe));
+        __syncthreads();
+      }
+    }
+    bool gs = false;
+    uint32_t g_lev = 0xffu;
+    if (valid) {
+      const int q = kGHalo + tid, kb = 31 - __clz(ng);
+      const uint32_t p = di[0], mg = min(mn(kb, q + 1), mn(kb, q + ng - (1 << kb) + 1));
+      const int s = sys_of(so, S, i);
+      const int64_t size = so[s + 1] - so[s];
+      const bool seg = so[s] == i;
+      if (ex) {
+        const uint32_t g = seg && size <= ng ? 0u : max(max(lo, 1u), mg + 1u);
+        if (g > top) {                        // the leaf here holds more than n_G
+          gs = true;
+          g_lev = top;
+        } else {
+          bool big = true;
+          if (!seg && g == lo) {
+            if (p == 0) {
+              big = size > ng;
+            } else {                          // the parent's run around i
+              int f = q + 1, bk = q;
+#pragma unroll
+              for (int k = 7; k >= 0; --k) {
+                if (f + (1 << k) <= kGWin && mn(k, f) >= p) f += 1 << k;
+                if (bk >= (1 << k) && mn(k, bk - (1 << k)) >= p) bk -= 1 << k;
+              }
+              big = (f - q - 1) + (q - bk) + 2 > ng;
+            }
+          }
+          gs = big;
+          if (big) g_lev = g;
+        }
+      } else if (!seg && p == (uint32_t)ML) {   // inside a run of equal keys
+        const unsigned long long m = below & (lane == 63 ? ~0ull : (2ull << lane) - 1ull);
+        int at = m ? 64 * w + 63 - __clzll((long long)m) : -1;
+        for (int v = w - 1; v >= 0 && at < 0; --v)
+          if (wb[v]) at = 64 * v + 63 - __clzll((long long)wb[v]);
+        const int64_t off = at >= 0 ? tid - at : (int64_t)before + tid;
+        gs = off % ng == 0;
+      }
+      gl[i] = (uint8_t)g_lev;
+    }
+    const unsigned long long gm = __ballot(gs);
+    __syncthreads();                          // wb has been read
+    if (lane == 0) {
+      bits[(ML + 1) * wl + 4 * b + w] = gm;
+      wb[w] = (unsigned long long)__popcll(gm);
+    }
+    __syncthreads();
+    if (tid == 0) {
+      uint32_t c = 0;
+      for (int v = 0; v < kFT / 64; ++v) c += (uint32_t)wb[v];
+      cnt[(ML + 1) * tl + b] = c;
+    }
+  }
   // the wave's mask of every level first, then lane l stores level l's
   unsigned long long msk[kL];
 #pragma unroll
@@ -174,7 +307,7 @@ __device__ __forceinline__ int fs_pad(int p) { return p + (p >> 5); }
 __global__ __launch_bounds__(1024) void k_flat_scan(const int32_t *__restrict__ gate, int64_t T, int64_t n,
                                                     uint32_t *__restrict__ cnt,
                                                     uint32_t *__restrict__ fst, int64_t tl,
-                                                    uint32_t *__restrict__ tot) {
+                                                    int levels, uint32_t *__restrict__ tot) {
   if (gate && *gate <= 0) return;   // nothing active: skipped
   __shared__ uint32_t sh[16];
   __shared__ uint32_t buf[kFSSub + kFSSub / 32];
@@ -213,6 +346,7 @@ __global__ __launch_bounds__(1024) void k_flat_scan(const int32_t *__restrict__ 
     __syncthreads();
   }
   if (tid == 0) { c[T] = run; tot[l] = run; }
+  if (l >= levels) return;             // group starts: counts only
   // suffix minimum, chunks from the end; positions past the chunk's m hold
   // the identity
   uint32_t carry = (uint32_t)n;
@@ -292,7 +426,9 @@ __global__ __launch_bounds__(kFT) void k_flat_emit(const int32_t *__restrict__ g
     uint32_t *__restrict__ root_of, uint8_t *__restrict__ level,
     uint8_t *__restrict__ nchild, uint32_t *__restrict__ first,
     uint32_t *__restrict__ count, uint32_t *__restrict__ child,
-    uint32_t *__restrict__ parent, uint32_t *__restrict__ nsys, uint4 *__restrict__ ninfo) {
+    uint32_t *__restrict__ parent, uint32_t *__restrict__ nsys, uint4 *__restrict__ ninfo,
+    uint32_t ng, const uint8_t *__restrict__ gl, uint4 *__restrict__ groups,
+    int32_t *__restrict__ built) {
   if (gate && *gate <= 0) return;   // nothing active: skipped
   __shared__ uint8_t sd[kFT];
   __shared__ uint8_t mn8[kFT / 8], mn64[kFT / 64];
@@ -316,6 +452,10 @@ __global__ __launch_bounds__(kFT) void k_flat_emit(const int32_t *__restrict__ g
     ctr->n_nodes = ovf ? 0u : nn;
     ctr->overflow = ovf ? 1u : 0u;
     if (ovf) set_err(err, TG_ERR_NODES);
+    if (ng > 0u) {
+      ctr->n_groups = ovf ? 0u : tot[kL];
+      *built = 1;   // a build exists now (read by the device-side rebuild / refit choice)
+    }
   }
   if (ovf) return;
   if (b == 0) {
@@ -408,6 +548,11 @@ __global__ __launch_bounds__(kFT) void k_flat_emit(const int32_t *__restrict__ g
     child[id] = ch;
     nchild[id] = (uint8_t)nch;
     ninfo[id] = make_uint4((uint32_t)i, (uint32_t)(e - i), ch, nch);
+    if (ng > 0u && gl[i] == l) {
+      const uint32_t g = rank_of(bits + kL * wl, cnt + kL * tl, i), c = (uint32_t)(e - i);
+      for (uint32_t k = 0; k < c; k += ng)     // one group, or a large leaf's
+        groups[g + k / ng] = make_uint4((uint32_t)i + k, min(ng, c - k), id, (uint32_t)s);
+    }
     }
   }
 }
@@ -417,17 +562,19 @@ static void launch_flat(tg_ctx *c, int64_t T) {
   Buffers &b = c->b;
   const int64_t n = c->n;
   const int64_t wl = 4 * (c->flat_tiles + 1), tl = c->flat_tiles + 1;
+  const int ng = flat_groups(c) ? c->group_size : 0;
+  uint8_t *gl = (uint8_t *)b.gflag;
   if (T > 0)
     hipLaunchKernelGGL(k_flat_flags<ML>, dim3((unsigned)T), dim3(kFT), 0, c->stream, c->gate, n,
-                       c->leaf_size, c->S, b.sysoff, b.lcp, b.fl_lt, b.fl_bits, wl,
+                       c->leaf_size, ng, gl, c->S, b.sysoff, b.lcp, b.fl_lt, b.fl_bits, wl,
                        b.fl_cnt, b.fl_fst, tl);
-  hipLaunchKernelGGL(k_flat_scan, dim3(ML + 1), dim3(1024), 0, c->stream, c->gate, T, n,
-                     b.fl_cnt, b.fl_fst, tl, b.fl_tot);
+  hipLaunchKernelGGL(k_flat_scan, dim3(ng > 0 ? ML + 2 : ML + 1), dim3(1024), 0, c->stream,
+                     c->gate, T, n, b.fl_cnt, b.fl_fst, tl, ML + 1, b.fl_tot);
   hipLaunchKernelGGL(k_flat_emit<ML>, dim3((unsigned)std::max<int64_t>(T, 1)), dim3(kFT), 0,
                      c->stream, c->gate, n, c->S, b.sysoff, b.lcp, b.fl_lt, b.fl_bits, wl,
                      b.fl_cnt, b.fl_fst, tl, b.fl_tot, c->max_nodes, b.ctr, b.err,
                      b.root_of, b.level, b.nchild, b.first, b.count, b.child, b.parent,
-                     b.nsys, b.ninfo);
+                     b.nsys, b.ninfo, (uint32_t)ng, gl, b.groups, b.refit_gates + 2);
 }
 
 hipError_t launch_tree_build(tg_ctx *c) {
@@ -437,7 +584,7 @@ hipError_t launch_tree_build(tg_ctx *c) {
   if (!c->one_tile)   // (else k_sort_systems wrote them)
     hipLaunchKernelGGL(k_lcp, dim3((int)std::min<int64_t>((n + 64 + 255) / 256, 4096)),
                        dim3(256), 0, c->stream, c->gate, b.key[0], deep ? b.klo[0] : nullptr, n,
-                       b.sysoff, c->S, b.lcp, b.gflag);
+                       b.sysoff, c->S, b.lcp, flat_groups(c) ? nullptr : b.gflag);
   if (deep)
     launch_flat<kMaxLevelDeep>(c, T);
   else
@@ -505,7 +652,8 @@ hipError_t launch_groups(tg_ctx *c) {
     const hipError_t e = fill_u32((uint32_t *)(b.refit_gates + 2), 1u, 1, c->stream, c->gate);
     return e != hipSuccess ? e : fill_u32(&b.ctr->n_groups, 0u, 1, c->stream);
   }
-  // the flags were cleared by k_lcp in the build
+  if (flat_groups(c)) return hipSuccess;   // formed with the nodes
+  // the flags were cleared with the common digits
   const int g = 1024;
   hipLaunchKernelGGL(k_group_flags, dim3(g), dim3(256), 0, c->stream, c->gate, b.ctr,
                      (uint32_t)c->group_size, b.nchild, b.first, b.count,

@@ -112,12 +112,12 @@ struct Buffers {
   uint8_t *lcp = nullptr;         // [N + 64] common leading digits with predecessor
   // flat octree build, per 256-particle tile (FT = tiles of max_particles)
   uint16_t *fl_lt = nullptr;      // [N] first | last node level starting at a particle
-  uint64_t *fl_bits = nullptr;    // [levels][4 (FT + 1)] node-start bitmaps
-  uint32_t *fl_cnt = nullptr;     // [levels][FT + 1] nodes per tile -> prefix
+  uint64_t *fl_bits = nullptr;    // [levels + 1][4 (FT + 1)] node-start bitmaps, then group starts
+  uint32_t *fl_cnt = nullptr;     // [levels + 1][FT + 1] nodes (last: groups) per tile -> prefix
   uint32_t *fl_fst = nullptr;     // [levels][FT + 1] first run start -> next after tile
-  uint32_t *fl_tot = nullptr;     // [levels] nodes per level
+  uint32_t *fl_tot = nullptr;     // [levels + 1] nodes per level, groups
   // groups
-  uint32_t *gflag = nullptr;      // [N + 1] group starts / scan
+  uint32_t *gflag = nullptr;      // [N + 1] group starts / scan, or group levels as bytes
   uint4 *groups = nullptr;        // [N]
   uint32_t *aflag = nullptr;      // [N + 1] active-group flags / scan
   uint32_t *alist = nullptr;      // [N] active group ids
@@ -330,6 +330,12 @@ struct CSum {
   }
   __device__ __forceinline__ double get() const { return s + c; }
 };
+
+// k_tree.hip
+// Whether the flat build forms the groups too.  A leaf holding more than n_G
+// has to be a run of equal keys, which n_G >= n_L ensures; smaller groups take
+// the kernels of launch_groups (four more launches of 4.8 us at 131072).
+inline bool flat_groups(const tg_ctx *c) { return c->n > 0 && c->group_size >= c->leaf_size; }
 
 // k_keys.hip
 hipError_t launch_cube_keys(tg_ctx *c, const double *pos);

@@ -163,8 +163,8 @@ tg_status tg_create(const tg_config *cfg_in, void *stream, tg_ctx **out) {
   A(dalloc(&b.lcp, N + 64));
   A(dalloc(&b.fl_lt, std::max<int64_t>(N, 1)));
   const int64_t levels = c->max_level + 1;
-  A(dalloc(&b.fl_bits, levels * 4 * (c->flat_tiles + 1)));
-  A(dalloc(&b.fl_cnt, levels * (c->flat_tiles + 1)));
+  A(dalloc(&b.fl_bits, (levels + 1) * 4 * (c->flat_tiles + 1)));
+  A(dalloc(&b.fl_cnt, (levels + 1) * (c->flat_tiles + 1)));
   A(dalloc(&b.fl_fst, levels * (c->flat_tiles + 1)));
   A(dalloc(&b.fl_tot, levels + 2));
   A(dalloc(&b.gflag, N + 1));
