@@ -38,7 +38,7 @@
 //   P2M 54: 3 sub, 6 for r^2 + eps^2, 3 for D2..D5, 15 for Q x, 6 for W,
 //          2 for D4 W, 3 for the radial coefficient, 12 for the
 //          accelerations, 4 for the potential (Q = 3S - T I, -T eps^2 and M
-//          of every node are formed once per evaluation, k_cell_records).
+//          of every node are formed once per evaluation, cell_records).
 #include <type_traits>
 
 #include "tg_internal.h"
@@ -1045,7 +1045,7 @@ void k_walk_forces(const int32_t *__restrict__ gate, WalkArgs A) {
     }
     __syncthreads();
   }
-  // each workgroup stores its own totals (k_walk_sum adds them up): eight
+  // each workgroup stores its own totals (k_walk_finish adds them up): eight
   // atomics per wave on one line, most of them issued as the queues ran
   // dry, had kept the last waves waiting (the walk took 8% longer)
   if (lane == 0) {

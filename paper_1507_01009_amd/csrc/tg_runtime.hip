@@ -171,7 +171,8 @@ tg_status tg_create(const tg_config *cfg_in, void *stream, tg_ctx **out) {
   A(dalloc(&b.groups, N));
   A(dalloc(&b.aflag, N + 1));
   A(dalloc(&b.alist, N)); A(dalloc(&b.acnt, N));
-  c->split_cap = 2 * kItemsPerWave * waves;
+  // (a part has at least one target of its own: never more parts than particles)
+  c->split_cap = std::min<int64_t>(2 * kItemsPerWave * waves, std::max<int64_t>(N, 1));
   A(dalloc(&b.items, N + 8 * c->split_cap)); A(dalloc(&b.slots, c->split_cap));
   A(dalloc(&b.wpart, c->split_cap * kMaxGroup));
   A(dalloc(&b.abox, 6 * N)); A(dalloc(&b.arel, N));
