@@ -85,8 +85,7 @@ struct WalkArgs {
   const uint2 *items;         // force walk: {group, part | (parts - 1) << 5 | first slot << 10}
   uint32_t item_gap;          // extra entries of each queue's range of items
   const uint2 *slots;         // split groups: {group, parts} at the slot of part 0
-  double4 *wpart;             // partial results of split groups [slot][stride]
-  uint32_t stride;
+  double4 *wpart;             // partial results of split groups [slot][kMaxGroup]
   uint32_t starts;            // blocks that start with an item of their own
   uint32_t *err;
   uint32_t *frontier;
@@ -1023,7 +1022,9 @@ void k_walk_forces(const int32_t *__restrict__ gate, WalkArgs A) {
     S.store_red();
     const double *red = tile.red;
     __syncthreads();
-    double4 *out = A.wpart + (size_t)((item.y >> 10) + part) * A.stride;
+    // rows of kMaxGroup, not of the context's group size: a captured walk is
+    // replayed on trees built with another one
+    double4 *out = A.wpart + (size_t)((item.y >> 10) + part) * kMaxGroup;
     for (int i = (int)lane; i < nt; i += 64) {
       // target i sits at k = i / lt, lane-target i % lt of every slice; sum
       // the slices in slice order (deterministic)
@@ -1085,10 +1086,10 @@ __global__ __launch_bounds__(kFinishThreads) void k_walk_finish(const int32_t *_
       const int nt = active_targets(A, gr, s_tgt[w]);
       wave_sync();
       for (int i = (int)lane; i < nt; i += 64) {
-        const double4 *o = A.wpart + (size_t)s * A.stride + i;
+        const double4 *o = A.wpart + (size_t)s * kMaxGroup + i;
         double4 v = o[0];
         for (uint32_t k = 1; k < sl.y; ++k) {
-          const double4 u = o[(size_t)k * A.stride];
+          const double4 u = o[(size_t)k * kMaxGroup];
           v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
         }
         store_target<kSpline>(A, gr.w, s_tgt[w][i], v.x, v.y, v.z, v.w);
@@ -1607,7 +1608,7 @@ static WalkArgs make_args(tg_ctx *c, double theta, const int32_t *n_act = nullpt
   A.ext_pos = c->ext_pos; A.ext_mass = c->ext_mass; A.ext_eps = c->ext_eps;
   A.ext_seg = c->n_ext > 0 ? c->b.ext_seg : nullptr;
   A.eps = 0.0;
-  A.items = nullptr; A.item_gap = 0; A.slots = nullptr; A.wpart = nullptr; A.stride = 0; A.starts = 0;
+  A.items = nullptr; A.item_gap = 0; A.slots = nullptr; A.wpart = nullptr; A.starts = 0;
   A.wl_count = b.wl_count; A.wl_off = b.wl_off; A.ids = nullptr;
   return A;
 }
@@ -1634,7 +1635,7 @@ hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta, const int32_t
   Buffers &b = c->b;
   WalkArgs A = make_args(c, theta, n_act);
   A.items = b.items; A.item_gap = (uint32_t)c->split_cap;
-  A.slots = b.slots; A.wpart = b.wpart; A.stride = (uint32_t)c->group_size;
+  A.slots = b.slots; A.wpart = b.wpart;
   A.starts = (uint32_t)walk_waves(c);
   A.eps2 = eps * eps;
   A.eps = eps;

@@ -82,3 +82,35 @@ def test_one_context_over_changing_active_sets():
         elif count:      # the active targets' boxes differ, so do the lists: the truncation error
             assert np.median(rel_err(a[idx], full["acc"][idx])) <= 1e-2
     ctx.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_replayed_walk_on_a_tree_of_other_sizes(precision):
+    """A captured evaluation replayed after the tree was built again with larger
+    and smaller groups gives what an eager one gives on that tree."""
+    import torch
+    from paper_1507_01009_amd import binding as B
+    from gpu_helpers import to_dev
+    n = 3001
+    pos, _, m = ics.plummer(n, 41)
+    dp, dm = to_dev(pos), to_dev(m)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        ctx = B.Context(n, leaf_size=8, group_size=16, precision=precision, stream=s)
+        out = torch.zeros((n, 3), dtype=torch.float64, device="cuda")
+        ref = torch.zeros_like(out)
+        ctx.build_tree(dp); ctx.compute_moments(dm); ctx.tree_forces(0.01, 0.5, out)
+        ctx.sync()
+        ctx.graph_begin()
+        ctx.tree_forces(0.01, 0.5, out)
+        graph = ctx.graph_end()
+        for nl, ng in ((8, 128), (8, 16), (16, 100), (4, 64)):
+            say("replayed walk", precision, nl, ng)
+            ctx.set_sizes(nl, ng)
+            ctx.build_tree(dp); ctx.compute_moments(dm); ctx.tree_forces(0.01, 0.5, ref)
+            out.zero_()
+            graph.launch(s)
+            s.synchronize()
+            assert torch.equal(out, ref), (nl, ng)
+        del graph
+        ctx.close()
