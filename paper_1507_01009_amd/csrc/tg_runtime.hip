@@ -564,6 +564,35 @@ tg_status tg_walk_lists(tg_ctx *c, double theta, const int32_t *idx,
   return TG_OK;
 } TG_HOST_CATCH("tg_walk_lists")
 
+// The device copy of a table of source and target offsets.  Tables live in a
+// few device slots keyed by their contents, so a step that uses several can
+// still be graph-captured once each has been seen eagerly.
+static tg_status segment_table(tg_ctx *c, const std::vector<int64_t> &seg, const char *who,
+                               const int64_t **out) {
+  int slot = -1;
+  for (int k = 0; k < (int)c->dseg_host.size(); ++k)
+    if (c->dseg_host[k] == seg) slot = k;
+  if (slot < 0) {
+    if (c->capturing)
+      return fail(TG_ESTATE, std::string(who) + ": new segment layout during capture");
+    if ((int)c->dseg_host.size() < kSegSlots) {
+      c->dseg_host.push_back(seg);
+      slot = (int)c->dseg_host.size() - 1;
+    } else {
+      slot = c->dseg_next;
+      c->dseg_next = (c->dseg_next + 1) % kSegSlots;
+      c->dseg_host[slot] = seg;
+      ++c->layout_gen;          // an evicted slot is overwritten
+    }
+    TG_HIP(hipMemcpyAsync(c->b.dseg + slot * kSegSlotLen, seg.data(),
+                          sizeof(int64_t) * seg.size(), hipMemcpyHostToDevice,
+                          c->stream));
+    TG_HIP(hipStreamSynchronize(c->stream));
+  }
+  *out = c->b.dseg + slot * kSegSlotLen;
+  return TG_OK;
+}
+
 tg_status tg_direct_fp64(tg_ctx *c, const double *spos, const double *sm,
                          const double *seps, int64_t ns, const double *tpos,
                          const double *teps, int64_t nt, const int64_t *sseg,
@@ -595,30 +624,9 @@ tg_status tg_direct_fp64(tg_ctx *c, const double *spos, const double *sm,
   }
   int64_t max_src = 0;
   for (int s = 0; s < ns_eff; ++s) max_src = std::max(max_src, seg[s + 1] - seg[s]);
-  // segment tables live in a few device slots keyed by their contents, so
-  // a step that uses several tables can still be graph-captured once each
-  // table has been seen eagerly
-  int slot = -1;
-  for (int k = 0; k < (int)c->dseg_host.size(); ++k)
-    if (c->dseg_host[k] == seg) slot = k;
-  if (slot < 0) {
-    if (c->capturing)
-      return fail(TG_ESTATE, "tg_direct_fp64: new segment layout during capture");
-    if ((int)c->dseg_host.size() < kSegSlots) {
-      c->dseg_host.push_back(seg);
-      slot = (int)c->dseg_host.size() - 1;
-    } else {
-      slot = c->dseg_next;
-      c->dseg_next = (c->dseg_next + 1) % kSegSlots;
-      c->dseg_host[slot] = seg;
-      ++c->layout_gen;          // an evicted slot is overwritten
-    }
-    TG_HIP(hipMemcpyAsync(c->b.dseg + slot * kSegSlotLen, seg.data(),
-                          sizeof(int64_t) * seg.size(), hipMemcpyHostToDevice,
-                          c->stream));
-    TG_HIP(hipStreamSynchronize(c->stream));
-  }
-  const int64_t *dseg = c->b.dseg + slot * kSegSlotLen;
+  const int64_t *dseg;
+  const tg_status st = segment_table(c, seg, "tg_direct_fp64", &dseg);
+  if (st != TG_OK) return st;
   TG_HIP(launch_direct(c, dseg, spos, sm, seps, 0.0, ns, tpos, teps, nt, ns_eff,
                        max_src, self_pairs, accumulate, acc, pot));
   return TG_OK;
@@ -629,36 +637,23 @@ tg_status tg_direct_fp64(tg_ctx *c, const double *spos, const double *sm,
 // pairs_done: the SMBHs' mutual pull came with them.
 static tg_status smbh_star_sums(tg_ctx *c, const tg_system *y, const int64_t *sseg,
                                 const int64_t *tseg, int32_t nseg, bool *pairs_done) try {
-  int slot = -1;
-  std::vector<int64_t> seg(2 * (nseg + 1));
-  for (int s = 0; s <= nseg; ++s) { seg[s] = sseg[s]; seg[nseg + 1 + s] = tseg[s]; }
+  std::vector<int64_t> seg(sseg, sseg + nseg + 1);
+  seg.insert(seg.end(), tseg, tseg + nseg + 1);
   int64_t max_src = 0;
   for (int s = 0; s < nseg; ++s) max_src = std::max(max_src, seg[s + 1] - seg[s]);
-  for (int k = 0; k < (int)c->dseg_host.size(); ++k)
-    if (c->dseg_host[k] == seg) slot = k;
-  if (slot < 0) {
-    if (c->capturing)
-      return fail(TG_ESTATE, "smbh_star_sums: new segment layout during capture");
-    if ((int)c->dseg_host.size() < kSegSlots) {
-      c->dseg_host.push_back(seg);
-      slot = (int)c->dseg_host.size() - 1;
-    } else {
-      slot = c->dseg_next;
-      c->dseg_next = (c->dseg_next + 1) % kSegSlots;
-      c->dseg_host[slot] = seg;
-      ++c->layout_gen;          // an evicted slot is overwritten
-    }
-    TG_HIP(hipMemcpyAsync(c->b.dseg + slot * kSegSlotLen, seg.data(),
-                          sizeof(int64_t) * seg.size(), hipMemcpyHostToDevice, c->stream));
-    TG_HIP(hipStreamSynchronize(c->stream));
-  }
-  const int64_t *dseg = c->b.dseg + slot * kSegSlotLen;
+  const int64_t *dseg;
+  const tg_status st = segment_table(c, seg, "smbh_star_sums", &dseg);
+  if (st != TG_OK) return st;
   *pairs_done = smbh_sums_fit(c, max_src, y->n_bh);
-  if (*pairs_done)
+  if (*pairs_done) {
     TG_HIP(launch_smbh_sums(c, dseg, y, nseg, max_src));
-  else
-    TG_HIP(launch_direct(c, dseg, y->pos, y->mass, nullptr, y->eps, y->n, y->bh_pos, y->bh_eps,
-                         y->n_bh, nseg, max_src, 0, 0, y->bh_acc, y->bh_pot));
+    // the table of the SMBHs on each other, as tg_direct_fp64 would keep it:
+    // a caller may capture that call after an eager evaluation
+    std::copy(tseg, tseg + nseg + 1, seg.begin());
+    return segment_table(c, seg, "tg_direct_fp64", &dseg);
+  }
+  TG_HIP(launch_direct(c, dseg, y->pos, y->mass, nullptr, y->eps, y->n, y->bh_pos, y->bh_eps,
+                       y->n_bh, nseg, max_src, 0, 0, y->bh_acc, y->bh_pot));
   return TG_OK;
 } TG_HOST_CATCH("smbh_star_sums")
 

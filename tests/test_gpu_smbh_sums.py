@@ -86,3 +86,25 @@ def test_idle_substeps_equal_single_ones(nb):
     assert idle > 20
     for x, y in zip(*out):
         assert torch.equal(x, y)
+
+
+def test_mutual_sums_captured_after_an_evaluation():
+    """An eager evaluation makes the SMBHs' own segment table known, also where their
+    mutual pull comes with the stars' sums: the direct call on them can be captured."""
+    import torch
+    say("captured mutual sums")
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        ctx, d, _, seg = _system(9001, 2)
+        ctx.forces(d["sys"])
+        ctx.sync()
+        acc, ref = torch.zeros_like(d["bacc"]), torch.zeros_like(d["bacc"])
+        ctx.graph_begin()
+        ctx.direct_fp64(d["bpos"], d["bmass"], d["beps"], d["bpos"], d["beps"], acc, self_pairs=True)
+        graph = ctx.graph_end()
+        ctx.direct_fp64(d["bpos"], d["bmass"], d["beps"], d["bpos"], d["beps"], ref, self_pairs=True)
+        graph.launch(s)
+        s.synchronize()
+        assert torch.equal(acc, ref) and bool((acc != 0).any())
+        del graph
+        ctx.close()
