@@ -1,0 +1,89 @@
+// Which kernels form the FP64 direct sums, and how they split the sources: a
+// function of the sizes alone (no HIP in here, so a host program can check
+// it).
+#ifndef TG_DIRECT_PLAN_H
+#define TG_DIRECT_PLAN_H
+
+#include <algorithm>
+#include <cstdint>
+
+namespace tg {
+
+enum class DirectPath { kFew, kTile, kPlain };
+
+struct DirectPlan {
+  DirectPath path;
+  int lane_targets;    // tiles: targets to a lane
+  int64_t chunk;       // sources of one partial sum
+  int64_t nchunks;     // partial sums of a target (1: written as the result)
+  bool block_reduce;   // a block per target adds them up (else a thread)
+};
+
+constexpr int kTileSrc = 256;            // sources of a tile in LDS
+
+// Up to kFewTargets targets of one segment: 262144 sources on 64 targets take
+// 47 us against 73 in the tiled kernel (half of whose lanes idle there), on
+// 128 targets 83 against 70.  Several segments have no tiled kernel, and the
+// plain one gives neighbouring lanes targets of different segments: 64
+// systems of 20000 stars with two SMBHs each 24 us in 640 blocks against 155,
+// 256 systems of 8192 with one each 22 against 189.
+constexpr int64_t kFewTargets = 127, kFewTargetsSeg = 4096;
+
+// Sources per block: short ranges below 2^20 sources, where long ones leave
+// most of the chip idle (131072 stars on one SMBH: 12.2 us in 32 blocks of
+// 4096, 6.6 in 128 of 1024), if their partial sums fit.
+inline int few_span(int64_t part_cap, int64_t n, int64_t nt) {
+  return n < (1 << 20) && (n + 1023) / 1024 * nt * 8 <= part_cap ? 1024 : 4096;
+}
+
+// Whether sums of (at most) n sources of a segment on nt targets in all take
+// the few-target kernel (part_cap doubles of partial sums).
+inline bool few_path(int64_t part_cap, int64_t n, int64_t nt, int nseg) {
+  if (nt > (nseg == 1 ? kFewTargets : kFewTargetsSeg) || n < 8192) return false;
+  const int64_t bpt = (n + 4095) / 4096;
+  return bpt * nt * 8 <= part_cap && bpt <= 65535;
+}
+
+// The tiled kernel's split: chunks of whole tiles, enough for kTileBlocks
+// blocks (eight per CU, two rounds of those resident) where the partial sums
+// fit.  One target to a lane where two would give less than a block per CU
+// (1000 targets on 1000 sources: 19.5 against 26.7 us).
+constexpr int64_t kTileBlocks = 2048;
+
+// n: sources of the longest segment; nt >= 1 targets in all.
+inline DirectPlan direct_plan(int64_t part_cap, int64_t n, int64_t nt, int nseg) {
+  if (few_path(part_cap, n, nt, nseg)) {
+    const int64_t span = few_span(part_cap, n, nt);
+    return {DirectPath::kFew, 1, span, (n + span - 1) / span, true};
+  }
+  // one segment: tiles, from a wave of targets and of sources on (fewer pairs
+  // than that are one launch of the plain kernel either way)
+  if (nseg == 1 && nt >= 64 && n >= 64) {
+    const int64_t tiles = (n + kTileSrc - 1) / kTileSrc;
+    const bool two = (nt + 127) / 128 * tiles >= 256;
+    const int64_t bx = two ? (nt + 127) / 128 : (nt + 63) / 64;
+    int64_t nchunks = std::min((kTileBlocks + bx - 1) / bx, tiles);
+    nchunks = std::max<int64_t>(1, std::min(nchunks, part_cap / (8 * nt)));
+    const int64_t chunk = (tiles + nchunks - 1) / nchunks * kTileSrc;
+    nchunks = (n + chunk - 1) / chunk;
+    // a block per target for many chunks (300 targets: 800 chunks)
+    return {DirectPath::kTile, two ? 2 : 1, chunk, nchunks, nchunks > 64};
+  }
+  // aim for >= 2^16 independent (target, chunk) sums; with part_cap >= 2^19
+  // doubles the partials of nt < 2^16 targets always fit at some chunk
+  int64_t nchunks = 1, chunk = std::max<int64_t>(n, 1);
+  if (nt < 65536 && n > 256) {
+    const int64_t want = (65536 + nt - 1) / nt;
+    chunk = std::max<int64_t>(256, (n + want - 1) / want);
+    nchunks = (n + chunk - 1) / chunk;
+    while (nchunks > 1 && nchunks * nt * 8 > part_cap) {
+      chunk *= 2;
+      nchunks = (n + chunk - 1) / chunk;
+    }
+  }
+  return {DirectPath::kPlain, 1, chunk, nchunks, true};
+}
+
+}  // namespace tg
+
+#endif

@@ -8,8 +8,8 @@
 // range of few_span sources), threads striding through the range with
 // coalesced loads, the block's sums combined in a fixed tree order and the
 // per-block partials summed in a second ordered pass.  Anything else
-// (several segments, a handful of pairs): one thread per target and source
-// chunk.  Every sum is compensated
+// (more targets of several segments, a handful of pairs): one thread per
+// target and source chunk.  direct_plan.h holds the rules.  Every sum is compensated
 // (error-free TwoSum with a running correction), so the result does not
 // depend on the split beyond the last bit and is deterministic.  Every
 // operation is rounded on its own (no FMA contraction): the TwoSum steps
@@ -17,6 +17,7 @@
 // the unfused ones bit for bit.
 #include <type_traits>
 
+#include "direct_plan.h"
 #include "tg_internal.h"
 
 namespace tg {
@@ -119,8 +120,6 @@ __global__ void k_direct(const double *__restrict__ spos, const double *__restri
 // (5.0e11, 5.2e11); two reach 6.1e11 (2.0e11 with one thread per target and
 // every source read from memory by every thread).  8191 targets on 262144
 // sources: 13.9 -> 3.9 ms.
-constexpr int kTileSrc = 256;
-
 template <int kT, bool kSelf, bool kSoft>
 __global__ __launch_bounds__(256) void k_direct_tile(
     const double *__restrict__ spos, const double *__restrict__ sm,
@@ -395,27 +394,6 @@ __global__ __launch_bounds__(256) void k_drift_smbh(
   }
 }
 
-// Whether sums of n sources on nt targets take the few-target path of
-// launch_direct (part_cap doubles of partials; the star sums on the SMBHs
-// that take it may be fused with the drift).
-// Up to kFewTargets targets: 262144 sources on 64 targets take 47 us against
-// 73 in the tiled kernel (half of whose lanes idle there), on 128 targets 83
-// against 70.
-constexpr int64_t kFewTargets = 127;
-
-// Sources per block: short ranges below 2^20 sources, where long ones leave
-// most of the chip idle (131072 stars on one SMBH: 12.2 us in 32 blocks of
-// 4096, 6.6 in 128 of 1024), if their partial sums fit.
-static int few_span(int64_t part_cap, int64_t n, int64_t nt) {
-  return n < (1 << 20) && (n + 1023) / 1024 * nt * 8 <= part_cap ? 1024 : 4096;
-}
-
-static bool few_path(int64_t part_cap, int64_t n, int64_t nt) {
-  if (!(nt <= kFewTargets && n >= 8192)) return false;
-  const int64_t bpt = (n + 4095) / 4096;
-  return bpt * nt * 8 <= part_cap && bpt <= 65535;
-}
-
 // The totals of the stars' partial sums on an SMBH (as k_direct_reduce) plus
 // the pull of the other SMBHs of its segment (as k_direct; formed by another
 // wave meanwhile), one block per SMBH: one launch of 4.6 us where two took 9.
@@ -490,7 +468,7 @@ __global__ __launch_bounds__(256) void k_smbh_finish(
 }
 
 bool drift_smbh_fits(const tg_ctx *c, int64_t n, int32_t nb) {
-  return nb >= 1 && nb <= kDriftSmbhMax && few_path(c->b.dpart_cap, n, nb);
+  return nb >= 1 && nb <= kDriftSmbhMax && few_path(c->b.dpart_cap, n, nb, 1);
 }
 
 hipError_t launch_drift_smbh(tg_ctx *c, const tg_system *y, double dt, int64_t *next_k) {
@@ -519,8 +497,8 @@ hipError_t launch_drift_smbh(tg_ctx *c, const tg_system *y, double dt, int64_t *
 }
 
 // From 64 SMBHs on their mutual pull has a kernel of its own (tiles).
-bool smbh_sums_fit(const tg_ctx *c, int64_t max_stars, int32_t nb) {
-  return nb >= 1 && nb < 64 && few_path(c->b.dpart_cap, max_stars, nb);
+bool smbh_sums_fit(const tg_ctx *c, int64_t max_stars, int32_t nb, int nseg) {
+  return nb >= 1 && nb < 64 && few_path(c->b.dpart_cap, max_stars, nb, nseg);
 }
 
 hipError_t launch_smbh_sums(tg_ctx *c, const int64_t *dseg, const tg_system *y, int nseg,
@@ -547,27 +525,21 @@ static void launch_tile_kernel(const DirectEnv &e, const double *spos, const dou
                      seps, seps_all, ns, tpos, teps, nt, chunk, accumulate, acc, pot, e.part);
 }
 
-// The tiled kernel's split: chunks of whole tiles, enough for kTileBlocks
-// blocks (eight per CU, two rounds of those resident) where the partial sums
-// fit.  One target to a lane where two would give less than a block per CU
-// (1000 targets on 1000 sources: 19.5 against 26.7 us).
-constexpr int64_t kTileBlocks = 2048;
+static void launch_reduce(const DirectEnv &e, int64_t nt, int64_t nchunks, int accumulate,
+                          double *acc, double *pot) {
+  hipLaunchKernelGGL(k_direct_reduce, dim3((unsigned)std::min<int64_t>(nt, 4096)), dim3(256), 0,
+                     e.stream, nt, (int)nchunks, accumulate, e.part, acc, pot);
+}
 
-static hipError_t launch_tiles(const DirectEnv &e, const double *spos, const double *sm,
-                               const double *seps, double seps_all, int64_t ns,
+static hipError_t launch_tiles(const DirectEnv &e, const DirectPlan &p, const double *spos,
+                               const double *sm, const double *seps, double seps_all, int64_t ns,
                                const double *tpos, const double *teps, int64_t nt,
                                int self_pairs, int accumulate, double *acc, double *pot) {
-  const int64_t tiles = (ns + kTileSrc - 1) / kTileSrc;
-  const bool two = (nt + 127) / 128 * tiles >= 256;
-  const int64_t bx = two ? (nt + 127) / 128 : (nt + 63) / 64;
-  int64_t nchunks = std::min((kTileBlocks + bx - 1) / bx, tiles);
-  nchunks = std::max<int64_t>(1, std::min(nchunks, e.part_cap / (8 * nt)));
-  const int64_t chunk = (tiles + nchunks - 1) / nchunks * kTileSrc;
-  nchunks = (ns + chunk - 1) / chunk;
   auto go = [&](auto self, auto soft) {
     constexpr bool kSelf = decltype(self)::value, kSoft = decltype(soft)::value;
-    (two ? launch_tile_kernel<2, kSelf, kSoft> : launch_tile_kernel<1, kSelf, kSoft>)(
-        e, spos, sm, seps, seps_all, ns, tpos, teps, nt, nchunks, chunk, accumulate, acc, pot);
+    (p.lane_targets == 2 ? launch_tile_kernel<2, kSelf, kSoft>
+                         : launch_tile_kernel<1, kSelf, kSoft>)(
+        e, spos, sm, seps, seps_all, ns, tpos, teps, nt, p.nchunks, p.chunk, accumulate, acc, pot);
   };
   const std::true_type yes;
   const std::false_type no;
@@ -575,12 +547,11 @@ static hipError_t launch_tiles(const DirectEnv &e, const double *spos, const dou
   else if (self_pairs) go(yes, no);
   else if (e.soft) go(no, yes);
   else go(no, no);
-  if (nchunks > 64)       // a block per target (300 targets: 800 chunks)
-    hipLaunchKernelGGL(k_direct_reduce, dim3((unsigned)std::min<int64_t>(nt, 4096)), dim3(256), 0,
-                       e.stream, nt, (int)nchunks, accumulate, e.part, acc, pot);
-  else if (nchunks > 1)
+  if (p.nchunks > 1 && p.block_reduce)
+    launch_reduce(e, nt, p.nchunks, accumulate, acc, pot);
+  else if (p.nchunks > 1)
     hipLaunchKernelGGL(k_direct_chunks, dim3((unsigned)((nt + 63) / 64)), dim3(64), 0, e.stream,
-                       nt, (int)nchunks, accumulate, e.part, acc, pot);
+                       nt, (int)p.nchunks, accumulate, e.part, acc, pot);
   return hipGetLastError();
 }
 
@@ -590,44 +561,24 @@ hipError_t launch_direct_env(const DirectEnv &e, const int64_t *dseg, const doub
                              int64_t max_seg_src, int self_pairs, int accumulate,
                              double *acc, double *pot) {
   if (nt == 0) return hipSuccess;
-  if (few_path(e.part_cap, max_seg_src, nt)) {
-    const int span = few_span(e.part_cap, max_seg_src, nt);
-    const int64_t bpt = (max_seg_src + span - 1) / span;
-    hipLaunchKernelGGL(k_direct_few, dim3((unsigned)bpt, (unsigned)nt), dim3(256), 0,
+  const DirectPlan p = direct_plan(e.part_cap, max_seg_src, nt, nseg);
+  if (p.path == DirectPath::kTile)
+    return launch_tiles(e, p, spos, sm, seps, seps_all, max_seg_src, tpos, teps, nt, self_pairs,
+                        accumulate, acc, pot);
+  if (p.path == DirectPath::kFew) {
+    hipLaunchKernelGGL(k_direct_few, dim3((unsigned)p.nchunks, (unsigned)nt), dim3(256), 0,
                        e.stream, spos, sm, seps, seps_all, tpos, teps, nt, dseg,
-                       dseg + (nseg + 1), nseg, self_pairs, e.soft, span, e.part);
-    hipLaunchKernelGGL(k_direct_reduce, dim3((unsigned)std::min<int64_t>(nt, 4096)),
-                       dim3(256), 0, e.stream, nt, (int)bpt, accumulate, e.part, acc, pot);
+                       dseg + (nseg + 1), nseg, self_pairs, e.soft, (int)p.chunk, e.part);
+    launch_reduce(e, nt, p.nchunks, accumulate, acc, pot);
     return hipGetLastError();
   }
-  // one segment: tiles, from a wave of targets and of sources on (fewer pairs
-  // than that are one launch of the kernel below either way)
-  if (nseg == 1 && nt >= 64 && max_seg_src >= 64)
-    return launch_tiles(e, spos, sm, seps, seps_all, max_seg_src, tpos, teps, nt, self_pairs,
-                        accumulate, acc, pot);
-  // aim for >= 2^16 independent (target, chunk) sums; with part_cap >= 2^19
-  // doubles the partials of nt < 2^16 targets always fit at some chunk
-  int64_t nchunks = 1, chunk = std::max<int64_t>(max_seg_src, 1);
-  if (nt < 65536 && max_seg_src > 256) {
-    int64_t want = (65536 + nt - 1) / nt;
-    chunk = std::max<int64_t>(256, (max_seg_src + want - 1) / want);
-    nchunks = (max_seg_src + chunk - 1) / chunk;
-    while (nchunks > 1 && nchunks * nt * 8 > e.part_cap) {
-      chunk *= 2;
-      nchunks = (max_seg_src + chunk - 1) / chunk;
-    }
-  }
-  const int64_t total = nt * nchunks;
+  const int64_t total = nt * p.nchunks;
   const int g = (int)std::min<int64_t>((total + 255) / 256, 8192);
   hipLaunchKernelGGL(k_direct, dim3(g), dim3(256), 0, e.stream, spos, sm, seps,
                      seps_all, tpos, teps, nt, dseg, dseg + (nseg + 1), nseg,
-                     chunk, (int)nchunks, self_pairs, accumulate, e.soft, acc, pot,
+                     p.chunk, (int)p.nchunks, self_pairs, accumulate, e.soft, acc, pot,
                      e.part);
-  if (nchunks > 1) {
-    const int g2 = (int)std::min<int64_t>(nt, 4096);
-    hipLaunchKernelGGL(k_direct_reduce, dim3(g2), dim3(256), 0, e.stream, nt,
-                       (int)nchunks, accumulate, e.part, acc, pot);
-  }
+  if (p.nchunks > 1) launch_reduce(e, nt, p.nchunks, accumulate, acc, pot);
   return hipGetLastError();
 }
 

@@ -411,7 +411,7 @@ bool drift_smbh_fits(const tg_ctx *c, int64_t n, int32_t nb);
 // (with next_k also the SMBHs' kicks and drift of the next idle substep, *next_k += 1)
 hipError_t launch_drift_smbh(tg_ctx *c, const tg_system *y, double dt, int64_t *next_k);
 // SMBH <- star and SMBH <-> SMBH sums in two launches, where they fit
-bool smbh_sums_fit(const tg_ctx *c, int64_t max_stars, int32_t nb);
+bool smbh_sums_fit(const tg_ctx *c, int64_t max_stars, int32_t nb, int nseg);
 hipError_t launch_smbh_sums(tg_ctx *c, const int64_t *dseg, const tg_system *y, int nseg,
                             int64_t max_stars);
 hipError_t launch_direct(tg_ctx *c, const int64_t *dseg, const double *spos,

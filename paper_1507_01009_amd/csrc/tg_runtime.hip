@@ -644,7 +644,7 @@ static tg_status smbh_star_sums(tg_ctx *c, const tg_system *y, const int64_t *ss
   const int64_t *dseg;
   const tg_status st = segment_table(c, seg, "smbh_star_sums", &dseg);
   if (st != TG_OK) return st;
-  *pairs_done = smbh_sums_fit(c, max_src, y->n_bh);
+  *pairs_done = smbh_sums_fit(c, max_src, y->n_bh, nseg);
   if (*pairs_done) {
     TG_HIP(launch_smbh_sums(c, dseg, y, nseg, max_src));
     // the table of the SMBHs on each other, as tg_direct_fp64 would keep it:

@@ -108,3 +108,52 @@ def test_coincident_unsoftened_pairs_as_the_formula():
     b = (a[0], a[1], a[2], a[0], a[2])
     acc, pot = _run(b, self_pairs=True)
     assert np.all(np.isfinite(acc)) and np.all(np.isfinite(pot))
+
+
+def _segmented(sizes, per, seed):
+    rng = np.random.default_rng(seed)
+    off, tof = np.concatenate([[0], np.cumsum(sizes)]), per * np.arange(len(sizes) + 1)
+    a = (rng.normal(size=(off[-1], 3)) ** 3, rng.uniform(0.5, 1.5, off[-1]) / off[-1],
+         rng.choice([0.0, 1e-3], off[-1]), rng.normal(size=(tof[-1], 3)),
+         rng.choice([0.0, 0.01], tof[-1]))
+    return a, [int(x) for x in off], [int(x) for x in tof]
+
+
+@pytest.mark.parametrize("sizes,per", [((8192,) + (300, 0, 9000) * 21, 2),      # 128 targets
+                                       ((8191, 100) * 70, 1), ((20000, 1), 65)])
+def test_many_targets_of_several_segments(sizes, per):
+    """From 128 targets in all, with segments long enough for the few-target
+    kernel and without, empty and short segments between."""
+    say("direct segments", len(sizes), per)
+    a, so, to = _segmented(sizes, per, len(sizes))
+    acc, pot = _run(a, src_seg=so, tgt_seg=to)
+    for s in range(len(sizes)):
+        i, j = slice(to[s], to[s + 1]), slice(so[s], so[s + 1])
+        ra, rp, sa, sp = _extended((a[0][j], a[1][j], a[2][j], a[3][i], a[4][i]), False)
+        assert np.all(np.abs(acc[i] - ra) <= TOL * sa) and np.all(np.abs(pot[i] - rp) <= TOL * sp)
+
+
+def test_time_of_many_targets_of_several_segments():
+    """64 systems with two targets each take about as long as 63 such systems
+    (126 targets; a thread per target and chunk took six times as long)."""
+    import torch
+    from paper_1507_01009_amd import binding as B
+    ctx = B.Context(1)
+    us = []
+    for systems in (63, 64):
+        say("direct segments, time", systems)
+        a, so, to = _segmented((20000,) * systems, 2, 1)
+        d = [to_dev(x) for x in a]
+        acc = torch.zeros((2 * systems, 3), dtype=torch.float64, device="cuda")
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        best = 1e9
+        for rep in range(8):
+            ev[0].record()
+            for _ in range(20):
+                ctx.direct_fp64(*d, acc, src_seg=so, tgt_seg=to)
+            ev[1].record()
+            ev[1].synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]) * 50.0)
+        us.append(best)
+    say("  %.1f and %.1f us" % tuple(us))
+    assert us[1] <= 2.5 * us[0]
