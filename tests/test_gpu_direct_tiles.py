@@ -81,6 +81,17 @@ def test_tiles_match_extended_precision(nt, ns, own):
     assert np.all(np.abs(pot - rp) <= TOL * sp)
 
 
+@pytest.mark.parametrize("nt,ns,own", [(1, 1, True), (1, 1, False), (2, 2, True), (63, 63, True),
+                                       (63, 1000, False), (3, 8191, False), (700, 63, False)])
+def test_a_thread_per_target(nt, ns, own):
+    """The plain kernel, below the sizes of the others: no source, one, and chunks."""
+    say("direct plain", nt, ns, own)
+    a = _inputs(nt, ns, own, nt + ns)
+    acc, pot = _run(a, self_pairs=own)
+    ra, rp, sa, sp = _extended(a, own)
+    assert np.all(np.abs(acc - ra) <= TOL * sa) and np.all(np.abs(pot - rp) <= TOL * sp)
+
+
 @pytest.mark.parametrize("nt,ns", [(100, 3000), (500, 5001)])
 def test_tiles_spline_and_accumulation(nt, ns):
     say("direct tiles spline", nt, ns)
