@@ -29,11 +29,14 @@ constexpr int kTileSrc = 256;            // sources of a tile in LDS
 // 256 systems of 8192 with one each 22 against 189.
 constexpr int64_t kFewTargets = 127, kFewTargetsSeg = 4096;
 
-// Sources per block: short ranges below 2^20 sources, where long ones leave
-// most of the chip idle (131072 stars on one SMBH: 12.2 us in 32 blocks of
-// 4096, 6.6 in 128 of 1024), if their partial sums fit.
+// Sources per block: 4096, or 1024 where that leaves much of the chip idle,
+// up to 320 blocks over all targets, and the partial sums fit.  Measured, in us
+// with 1024 and with 4096: 131072 sources on one target 9.2 and 12.8 (32
+// blocks of 4096), 500000 on two 14.8 and 16.8 (246), 50000 on 24 12.4 and
+// 14.7 (312); beyond the line 250000 on six 18.3 and 17.1 (372), on 24 42.0
+// and 23.3 (1488).
 inline int few_span(int64_t part_cap, int64_t n, int64_t nt) {
-  return n < (1 << 20) && (n + 1023) / 1024 * nt * 8 <= part_cap ? 1024 : 4096;
+  return (n + 4095) / 4096 * nt <= 320 && (n + 1023) / 1024 * nt * 8 <= part_cap ? 1024 : 4096;
 }
 
 // Whether sums of (at most) n sources of a segment on nt targets in all take

@@ -77,3 +77,12 @@ def test_splits_cover_and_fit(plan):
     (262144, 64, 1, FEW), (262144, 8191, 1, TILE), (100, 63, 1, PLAIN), (63, 1000, 1, PLAIN)])
 def test_lines(plan, n, nt, nseg, path):
     assert plan([(CAP, n, nt, nseg)])[0][0] == path
+
+
+@pytest.mark.parametrize("n,nt,span", [(131072, 1, 1024), (1 << 20, 1, 1024), (1 << 22, 1, 4096),
+                                       (500000, 2, 1024), (50000, 24, 1024), (20000, 64, 1024), (250000, 6, 4096),
+                                       (250000, 24, 4096), (131072, 48, 4096), (8192, 127, 1024)])
+def test_few_target_ranges(plan, n, nt, span):
+    """Ranges of 1024 sources only where ranges of 4096 leave much of the chip idle."""
+    path, _, chunk, _, _ = plan([(CAP, n, nt, 1)])[0]
+    assert (path, chunk) == (FEW, span)
