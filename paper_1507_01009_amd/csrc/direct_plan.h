@@ -21,28 +21,33 @@ struct DirectPlan {
 
 constexpr int kTileSrc = 256;            // sources of a tile in LDS
 
-// Up to kFewTargets targets of one segment: 262144 sources on 64 targets take
-// 47 us against 73 in the tiled kernel (half of whose lanes idle there), on
-// 128 targets 83 against 70.  Several segments have no tiled kernel, and the
-// plain one gives neighbouring lanes targets of different segments: 64
-// systems of 20000 stars with two SMBHs each 24 us in 640 blocks against 155,
-// 256 systems of 8192 with one each 22 against 189.
-constexpr int64_t kFewTargets = 127, kFewTargetsSeg = 4096;
+// The few-target kernel takes up to 4096 targets of several segments, which
+// have no tiled kernel, and the plain one gives neighbouring lanes targets of
+// different segments: 64 systems of 20000 stars with two SMBHs each 24 us in
+// 640 blocks against 155, 256 systems of 8192 with one each 22 against 189.
+// Of one segment it takes up to kFewTargets targets (a tile costs its block of
+// 128 whatever it holds: on 262144 sources 64 targets 48 us against 66, 96
+// targets 67 against 69, 128 targets 86 against 69), and more as long as there
+// are few pairs, which leave most of the chip without a tile: 128 targets on
+// 8192 sources 11.4 us against 19.2, 192 on 32768 23.7 against 28.5; at the
+// line 128 on 65536 30.2 against 29.0, 512 on 16384 30.4 against 29.0.
+constexpr int64_t kFewTargets = 88, kFewTargetsMax = 4096, kFewPairs = (int64_t)1 << 23;
 
 // Sources per block: 4096, or 1024 where that leaves much of the chip idle,
-// up to 320 blocks over all targets, and the partial sums fit.  Measured, in us
+// up to 384 blocks over all targets, and the partial sums fit.  Measured, in us
 // with 1024 and with 4096: 131072 sources on one target 9.2 and 12.8 (32
-// blocks of 4096), 500000 on two 14.8 and 16.8 (246), 50000 on 24 12.4 and
-// 14.7 (312); beyond the line 250000 on six 18.3 and 17.1 (372), on 24 42.0
-// and 23.3 (1488).
+// blocks of 4096), 500000 on two 14.8 and 16.8 (246), at the line 250000 on
+// six 18.3 and 17.1 (372) and 131072 on twelve 13.2 and 14.5 (384), beyond it
+// 500000 on four 21.4 and 19.9 (492), 250000 on 24 42.0 and 23.3 (1488).
 inline int few_span(int64_t part_cap, int64_t n, int64_t nt) {
-  return (n + 4095) / 4096 * nt <= 320 && (n + 1023) / 1024 * nt * 8 <= part_cap ? 1024 : 4096;
+  return (n + 4095) / 4096 * nt <= 384 && (n + 1023) / 1024 * nt * 8 <= part_cap ? 1024 : 4096;
 }
 
 // Whether sums of (at most) n sources of a segment on nt targets in all take
 // the few-target kernel (part_cap doubles of partial sums).
 inline bool few_path(int64_t part_cap, int64_t n, int64_t nt, int nseg) {
-  if (nt > (nseg == 1 ? kFewTargets : kFewTargetsSeg) || n < 8192) return false;
+  if (nt > kFewTargetsMax || n < 8192) return false;
+  if (nseg == 1 && nt > kFewTargets && nt * n >= kFewPairs) return false;
   const int64_t bpt = (n + 4095) / 4096;
   return bpt * nt * 8 <= part_cap && bpt <= 65535;
 }
@@ -69,8 +74,11 @@ inline DirectPlan direct_plan(int64_t part_cap, int64_t n, int64_t nt, int nseg)
     nchunks = std::max<int64_t>(1, std::min(nchunks, part_cap / (8 * nt)));
     const int64_t chunk = (tiles + nchunks - 1) / nchunks * kTileSrc;
     nchunks = (n + chunk - 1) / chunk;
-    // a block per target for many chunks (300 targets: 800 chunks)
-    return {DirectPath::kTile, two ? 2 : 1, chunk, nchunks, nchunks > 64};
+    // a block per target for many chunks, which one thread would add up one
+    // after another (64 targets: 16 chunks 21.2 us with threads and 19.0 with
+    // blocks, 32 chunks 26.2 and 19.0, 64 chunks 36.5 and 19.0; 8191 targets:
+    // 16 chunks 69.5 and 84.5)
+    return {DirectPath::kTile, two ? 2 : 1, chunk, nchunks, nchunks > 16};
   }
   // aim for >= 2^16 independent (target, chunk) sums; with part_cap >= 2^19
   // doubles the partials of nt < 2^16 targets always fit at some chunk

@@ -80,9 +80,25 @@ def test_lines(plan, n, nt, nseg, path):
 
 
 @pytest.mark.parametrize("n,nt,span", [(131072, 1, 1024), (1 << 20, 1, 1024), (1 << 22, 1, 4096),
-                                       (500000, 2, 1024), (50000, 24, 1024), (20000, 64, 1024), (250000, 6, 4096),
+                                       (500000, 2, 1024), (50000, 24, 1024), (20000, 64, 1024), (131072, 12, 1024), (131072, 13, 4096),
                                        (250000, 24, 4096), (131072, 48, 4096), (8192, 127, 1024)])
 def test_few_target_ranges(plan, n, nt, span):
     """Ranges of 1024 sources only where ranges of 4096 leave much of the chip idle."""
     path, _, chunk, _, _ = plan([(CAP, n, nt, 1)])[0]
     assert (path, chunk) == (FEW, span)
+
+
+@pytest.mark.parametrize("n,nt,path", [(8192, 128, FEW), (20000, 200, FEW), (65535, 128, FEW),
+                                       (65536, 128, TILE), (262144, 88, FEW), (262144, 89, TILE), (8192, 1023, FEW),
+                                       (8192, 1024, TILE), (1 << 22, 64, FEW), (4096, 128, TILE)])
+def test_line_of_one_segment(plan, n, nt, path):
+    """Above 88 targets of one segment the tiles from 2^23 pairs on."""
+    assert plan([(CAP, n, nt, 1)])[0][0] == path
+
+
+@pytest.mark.parametrize("n,nt,block", [(8000, 64, True), (4096, 64, False), (4352, 64, True),
+                                        (4000, 8191, False), (262144, 300, True)])
+def test_who_adds_the_chunks(plan, n, nt, block):
+    """A thread per target up to 16 chunks, a block beyond."""
+    path, _, _, k, b = plan([(CAP, n, nt, 1)])[0]
+    assert path == TILE and bool(b) == block == (k > 16)

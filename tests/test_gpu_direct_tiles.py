@@ -144,27 +144,54 @@ def test_many_targets_of_several_segments(sizes, per):
         assert np.all(np.abs(acc[i] - ra) <= TOL * sa) and np.all(np.abs(pot[i] - rp) <= TOL * sp)
 
 
+def _time(ctx, a, **kw):
+    """Least time of a call in us, from windows of 20 calls."""
+    import torch
+    d = [to_dev(x) for x in a]
+    acc = torch.zeros((a[3].shape[0], 3), dtype=torch.float64, device="cuda")
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    best = 1e9
+    for _ in range(8):
+        ev[0].record()
+        for _ in range(20):
+            ctx.direct_fp64(*d, acc, **kw)
+        ev[1].record()
+        ev[1].synchronize()
+        best = min(best, ev[0].elapsed_time(ev[1]) * 50.0)
+    return best
+
+
 def test_time_of_many_targets_of_several_segments():
     """64 systems with two targets each take about as long as 63 such systems
     (126 targets; a thread per target and chunk took six times as long)."""
-    import torch
     from paper_1507_01009_amd import binding as B
     ctx = B.Context(1)
     us = []
     for systems in (63, 64):
         say("direct segments, time", systems)
         a, so, to = _segmented((20000,) * systems, 2, 1)
-        d = [to_dev(x) for x in a]
-        acc = torch.zeros((2 * systems, 3), dtype=torch.float64, device="cuda")
-        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
-        best = 1e9
-        for rep in range(8):
-            ev[0].record()
-            for _ in range(20):
-                ctx.direct_fp64(*d, acc, src_seg=so, tgt_seg=to)
-            ev[1].record()
-            ev[1].synchronize()
-            best = min(best, ev[0].elapsed_time(ev[1]) * 50.0)
-        us.append(best)
+        us.append(_time(ctx, a, src_seg=so, tgt_seg=to))
     say("  %.1f and %.1f us" % tuple(us))
     assert us[1] <= 2.5 * us[0]
+
+
+def test_time_of_a_hundred_targets_on_few_sources():
+    """128 targets on 8192 sources take about as long as 60 (tiles, whose 32
+    chunks a thread per target added up, took 2.7 times as long)."""
+    from paper_1507_01009_amd import binding as B
+    ctx = B.Context(1)
+    us = [_time(ctx, _inputs(nt, 8192, False, nt)) for nt in (60, 128)]
+    say("direct few sources, time  %.1f and %.1f us" % tuple(us))
+    assert us[1] <= 1.8 * us[0]
+
+
+@pytest.mark.parametrize("nt,ns", [(65, 8192), (128, 65535), (128, 65536), (700, 9000),
+                                   (64, 4097), (200, 8191)])
+def test_lines_of_one_segment(nt, ns):
+    """Both sides of the lines between the few-target blocks, the tiles, and the
+    two ways to add up the tiles' chunks."""
+    say("direct lines", nt, ns)
+    a = _inputs(nt, ns, False, nt + ns)
+    acc, pot = _run(a)
+    ra, rp, sa, sp = _extended(a, False)
+    assert np.all(np.abs(acc - ra) <= TOL * sa) and np.all(np.abs(pot - rp) <= TOL * sp)
