@@ -58,6 +58,14 @@ inline bool few_path(int64_t part_cap, int64_t n, int64_t nt, int nseg) {
 // (1000 targets on 1000 sources: 19.5 against 26.7 us).
 constexpr int64_t kTileBlocks = 2048;
 
+// More targets than one round of tile blocks holds (four to a CU), on few
+// sources: two or three of the four waves of such a block have little to do or
+// nothing, and a thread per target is faster.  In us by tiles and by threads:
+// a million targets on 64 sources 203 and 144, on 80 213 and 178, on 100 241
+// and 227; 200000 on 64 53 and 43, on 80 54 and 53, on 100 64 and 65; a round
+// or less, 131072 on 64, 24.6 and 25.1, on 100 31 and 38.
+constexpr int64_t kTileRound = 1 << 17, kTileMinSrc = 64, kTileMinSrcMany = 96;
+
 // n: sources of the longest segment; nt >= 1 targets in all.
 inline DirectPlan direct_plan(int64_t part_cap, int64_t n, int64_t nt, int nseg) {
   if (few_path(part_cap, n, nt, nseg)) {
@@ -66,7 +74,7 @@ inline DirectPlan direct_plan(int64_t part_cap, int64_t n, int64_t nt, int nseg)
   }
   // one segment: tiles, from a wave of targets and of sources on (fewer pairs
   // than that are one launch of the plain kernel either way)
-  if (nseg == 1 && nt >= 64 && n >= 64) {
+  if (nseg == 1 && nt >= 64 && n >= (nt > kTileRound ? kTileMinSrcMany : kTileMinSrc)) {
     const int64_t tiles = (n + kTileSrc - 1) / kTileSrc;
     const bool two = (nt + 127) / 128 * tiles >= 256;
     const int64_t bx = two ? (nt + 127) / 128 : (nt + 63) / 64;

@@ -102,3 +102,10 @@ def test_who_adds_the_chunks(plan, n, nt, block):
     """A thread per target up to 16 chunks, a block beyond."""
     path, _, _, k, b = plan([(CAP, n, nt, 1)])[0]
     assert path == TILE and bool(b) == block == (k > 16)
+
+
+@pytest.mark.parametrize("n,nt,path", [(64, 131072, TILE), (64, 131073, PLAIN), (95, 1000000, PLAIN),
+                                       (96, 1000000, TILE), (64, 64, TILE)])
+def test_line_of_many_targets(plan, n, nt, path):
+    """A thread each for more targets than a round of tile blocks, on few sources."""
+    assert plan([(CAP, n, nt, 1)])[0][0] == path

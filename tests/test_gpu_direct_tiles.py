@@ -195,3 +195,16 @@ def test_lines_of_one_segment(nt, ns):
     acc, pot = _run(a)
     ra, rp, sa, sp = _extended(a, False)
     assert np.all(np.abs(acc - ra) <= TOL * sa) and np.all(np.abs(pot - rp) <= TOL * sp)
+
+
+@pytest.mark.parametrize("nt,ns", [(131073, 65), (131072, 95), (131080, 96)])
+def test_many_targets_on_few_sources(nt, ns):
+    """Both sides of the line between tiles and a thread per target: the first and
+    last blocks' targets."""
+    say("direct many targets", nt, ns)
+    a = _inputs(nt, ns, False, nt + ns)
+    acc, pot = _run(a)
+    pick = np.r_[0:130, nt // 2:nt // 2 + 130, nt - 130:nt]
+    ra, rp, sa, sp = _extended((a[0], a[1], a[2], a[3][pick], a[4][pick]), False)
+    assert np.all(np.abs(acc[pick] - ra) <= TOL * sa) and np.all(np.abs(pot[pick] - rp) <= TOL * sp)
+    assert np.all(np.isfinite(acc)) and np.all(np.isfinite(pot))
