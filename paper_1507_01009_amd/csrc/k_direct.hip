@@ -258,20 +258,22 @@ __global__ __launch_bounds__(64) void k_direct_chunks(int64_t nt, int nchunks, i
   }
 }
 
-// Compensated sums of a 256-thread block combined in a fixed tree order;
-// thread 0 returns with the totals in ss[k][0] + sc[k][0].
-__device__ __forceinline__ void block_csum4(CSum r[4], double (*ss)[256], double (*sc)[256]) {
-  for (int k = 0; k < 4; ++k) { ss[k][threadIdx.x] = r[k].s; sc[k][threadIdx.x] = r[k].c; }
+// Compensated sums of 256 threads (t: the number among them) combined in a
+// fixed tree order; thread 0 returns with the totals in ss[k][0] + sc[k][0].
+// Every thread of the block is here.
+__device__ __forceinline__ void block_csum4(CSum r[4], double (*ss)[256], double (*sc)[256],
+                                            int t = threadIdx.x) {
+  for (int k = 0; k < 4; ++k) { ss[k][t] = r[k].s; sc[k][t] = r[k].c; }
   __syncthreads();
   for (int h = 128; h > 0; h >>= 1) {
-    if ((int)threadIdx.x < h) {
+    if (t < h) {
       for (int k = 0; k < 4; ++k) {
         CSum x;
-        x.s = ss[k][threadIdx.x];
-        x.c = sc[k][threadIdx.x] + sc[k][threadIdx.x + h];
-        x.add(ss[k][threadIdx.x + h]);
-        ss[k][threadIdx.x] = x.s;
-        sc[k][threadIdx.x] = x.c;
+        x.s = ss[k][t];
+        x.c = sc[k][t] + sc[k][t + h];
+        x.add(ss[k][t + h]);
+        ss[k][t] = x.s;
+        sc[k][t] = x.c;
       }
     }
     __syncthreads();
@@ -407,74 +409,77 @@ __global__ __launch_bounds__(256) void k_drift_smbh(
 
 // The totals of the stars' partial sums on an SMBH (as k_direct_reduce) plus
 // the pull of the other SMBHs of its segment (as k_direct; formed by another
-// wave meanwhile), one block per SMBH: one launch of 4.6 us where two took 9.
-// With kStep (one segment, one block) the next idle substep's kicks and drift
-// of the SMBHs follow, as k_bh_substep does them (another launch of 4.7 us;
-// 128 substeps of 4.2M stars 29.2 -> 28.6 ms).  Bound by latency: the partial
-// sums' loads and eight steps of the block's tree.
-template <bool kStep>
-__global__ __launch_bounds__(256) void k_smbh_finish(
+// wave meanwhile), 256 threads per SMBH: one launch of 4.6 us where two took 9.
+// A block takes kG SMBHs.  With kStep (one segment, all kG of its SMBHs in one
+// block) the next idle substep's kicks and drift of the SMBHs follow, as
+// k_bh_substep does them (another launch of 4.7 us).  Bound by latency: the
+// partial sums' loads and eight steps of the sums' tree, so the SMBHs of a
+// block are taken side by side (one after another, four SMBHs took 17.1 us,
+// now 8.8; idle substeps of 20000 stars with four 29.4 -> 23.0 us).
+template <int kG, bool kStep>
+__global__ __launch_bounds__(256 * kG) void k_smbh_finish(
     int nb, int nchunks, const double *__restrict__ part, double *bpos,
     const double *__restrict__ bmass, const double *__restrict__ beps,
     const int64_t *__restrict__ bseg, int nseg, int soft, double *__restrict__ acc,
     double *__restrict__ pot, double *__restrict__ vel, double dt, int64_t *__restrict__ kctr) {
 #pragma clang fp contract(off)
-  __shared__ double ss[4][256], sc[4][256], pair[4], a_new[3 * kDriftSmbhMax];
-  for (int i = blockIdx.x; i < nb; i += gridDim.x) {
-    CSum r[4];
-    for (int c = threadIdx.x; c < nchunks; c += 256) {
-      const double *o = part + 8 * ((size_t)c * nb + i);
-      for (int k = 0; k < 4; ++k) {
-        r[k].add(o[2 * k]);
-        r[k].add(o[2 * k + 1]);
-      }
+  __shared__ double ss[kG][4][256], sc[kG][4][256], pair[kG][4], a_new[3 * kG];
+  const int g = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 8));
+  const int t = threadIdx.x & 255;
+  const int i = blockIdx.x * kG + g;      // < nb: the grid has nb / kG blocks
+  CSum r[4];
+  for (int c = t; c < nchunks; c += 256) {
+    const double *o = part + 8 * ((size_t)c * nb + i);
+    for (int k = 0; k < 4; ++k) {
+      r[k].add(o[2 * k]);
+      r[k].add(o[2 * k + 1]);
     }
-    if (threadIdx.x == 192) {
-      int64_t j0 = 0, j1 = nb;
-      if (bseg) {
-        const int s = seg_of(bseg, nseg, i);
-        j0 = bseg[s];
-        j1 = bseg[s + 1];
-      }
-      CSum q[4];
-      for (int64_t j = j0; j < j1; ++j) {
-        if (j == i) continue;
-        const double ep = fmax(beps[j], beps[i]);
-        const double dx = bpos[3 * i] - bpos[3 * j], dy = bpos[3 * i + 1] - bpos[3 * j + 1];
-        const double dz = bpos[3 * i + 2] - bpos[3 * j + 2];
-        double mD1, mD3;
-        pair_terms(dx, dy, dz, ep, bmass[j], soft, mD1, mD3);
-        q[0].add(-mD3 * dx);
-        q[1].add(-mD3 * dy);
-        q[2].add(-mD3 * dz);
-        q[3].add(-mD1);
-      }
-      for (int k = 0; k < 4; ++k) pair[k] = q[k].get();
+  }
+  if (t == 192) {
+    int64_t j0 = 0, j1 = nb;
+    if (bseg) {
+      const int s = seg_of(bseg, nseg, i);
+      j0 = bseg[s];
+      j1 = bseg[s + 1];
     }
-    block_csum4(r, ss, sc);
-    if (threadIdx.x == 0) {
-      for (int k = 0; k < 3; ++k) {
-        const double a = (ss[k][0] + sc[k][0]) + pair[k];
-        acc[3 * i + k] = a;
-        if constexpr (kStep) a_new[3 * i + k] = a;
-      }
-      if (pot) pot[i] = (ss[3][0] + sc[3][0]) + pair[3];
+    CSum q[4];
+    for (int64_t j = j0; j < j1; ++j) {
+      if (j == i) continue;
+      const double ep = fmax(beps[j], beps[i]);
+      const double dx = bpos[3 * i] - bpos[3 * j], dy = bpos[3 * i + 1] - bpos[3 * j + 1];
+      const double dz = bpos[3 * i + 2] - bpos[3 * j + 2];
+      double mD1, mD3;
+      pair_terms(dx, dy, dz, ep, bmass[j], soft, mD1, mD3);
+      q[0].add(-mD3 * dx);
+      q[1].add(-mD3 * dy);
+      q[2].add(-mD3 * dz);
+      q[3].add(-mD1);
     }
-    __syncthreads();
+    for (int k = 0; k < 4; ++k) pair[g][k] = q[k].get();
+  }
+  block_csum4(r, ss[g], sc[g], t);
+  if (t == 0) {
+    for (int k = 0; k < 3; ++k) {
+      const double a = (ss[g][k][0] + sc[g][k][0]) + pair[g][k];
+      acc[3 * i + k] = a;
+      if constexpr (kStep) a_new[3 * g + k] = a;
+    }
+    if (pot) pot[i] = (ss[g][3][0] + sc[g][3][0]) + pair[g][3];
   }
   if constexpr (kStep) {
+    __syncthreads();                      // the positions have been read
     const int64_t k = kctr[0];
     const double h = dt * 0.5;
-    const int t = threadIdx.x;
-    if (t < 3 * nb) {
-      double v = vel[t];
-      if (k != 0) v = v + a_new[t] * h;
-      v = v + a_new[t] * h;
-      vel[t] = v;
-      bpos[t] = bpos[t] + v * dt;
+    const int e = threadIdx.x;
+    if (e < 3 * kG) {
+      double v = vel[e];
+      if (k != 0) v = v + a_new[e] * h;
+      v = v + a_new[e] * h;
+      vel[e] = v;
+      bpos[e] = bpos[e] + v * dt;
     }
     __syncthreads();
-    if (t == 0) kctr[0] = k + 1;
+    if (e == 0) kctr[0] = k + 1;
   }
 }
 
@@ -498,12 +503,16 @@ hipError_t launch_drift_smbh(tg_ctx *c, const tg_system *y, double dt, int64_t *
     case 3: go(k_drift_smbh<3>); break;
     default: go(k_drift_smbh<4>); break;
   }
-  auto finish = [&](auto kernel, int blocks) {
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, c->stream, nb, (int)bpt, c->b.dpart,
-                       y->bh_pos, y->bh_mass, y->bh_eps, nullptr, 1, c->soft, y->bh_acc,
-                       y->bh_pot, y->bh_vel, dt, next_k);
+  auto finish = [&](auto kernel, int per) {
+    hipLaunchKernelGGL(kernel, dim3(nb / per), dim3(256 * per), 0, c->stream, nb, (int)bpt,
+                       c->b.dpart, y->bh_pos, y->bh_mass, y->bh_eps, nullptr, 1, c->soft,
+                       y->bh_acc, y->bh_pot, y->bh_vel, dt, next_k);
   };
-  next_k ? finish(k_smbh_finish<true>, 1) : finish(k_smbh_finish<false>, nb);
+  if (!next_k) finish(k_smbh_finish<1, false>, 1);
+  else if (nb == 1) finish(k_smbh_finish<1, true>, 1);
+  else if (nb == 2) finish(k_smbh_finish<2, true>, 2);
+  else if (nb == 3) finish(k_smbh_finish<3, true>, 3);
+  else finish(k_smbh_finish<4, true>, 4);
   return hipGetLastError();
 }
 
@@ -520,7 +529,7 @@ hipError_t launch_smbh_sums(tg_ctx *c, const int64_t *dseg, const tg_system *y, 
   hipLaunchKernelGGL(k_direct_few, dim3((unsigned)bpt, (unsigned)nb), dim3(256), 0, c->stream,
                      y->pos, y->mass, nullptr, y->eps, y->bh_pos, y->bh_eps, (int64_t)nb, dseg,
                      dseg + (nseg + 1), nseg, 0, c->soft, span, c->b.dpart);
-  hipLaunchKernelGGL(k_smbh_finish<false>, dim3(nb), dim3(256), 0, c->stream, nb, (int)bpt,
+  hipLaunchKernelGGL((k_smbh_finish<1, false>), dim3(nb), dim3(256), 0, c->stream, nb, (int)bpt,
                      c->b.dpart, y->bh_pos, y->bh_mass, y->bh_eps, dseg + (nseg + 1), nseg,
                      c->soft, y->bh_acc, y->bh_pot, nullptr, 0.0, nullptr);
   return hipGetLastError();
