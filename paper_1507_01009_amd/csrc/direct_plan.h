@@ -34,13 +34,16 @@ constexpr int kTileSrc = 256;            // sources of a tile in LDS
 constexpr int64_t kFewTargets = 88, kFewTargetsMax = 4096, kFewPairs = (int64_t)1 << 23;
 
 // Sources per block: 4096, or 1024 where that leaves much of the chip idle,
-// up to 384 blocks over all targets, and the partial sums fit.  Measured, in us
+// up to 384 blocks over all targets, and a target's partial sums are at most
+// four to a thread of the second pass (2^20 sources) and fit.  Measured, in us
 // with 1024 and with 4096: 131072 sources on one target 9.2 and 12.8 (32
 // blocks of 4096), 500000 on two 14.8 and 16.8 (246), at the line 250000 on
 // six 18.3 and 17.1 (372) and 131072 on twelve 13.2 and 14.5 (384), beyond it
 // 500000 on four 21.4 and 19.9 (492), 250000 on 24 42.0 and 23.3 (1488).
 inline int few_span(int64_t part_cap, int64_t n, int64_t nt) {
-  return (n + 4095) / 4096 * nt <= 384 && (n + 1023) / 1024 * nt * 8 <= part_cap ? 1024 : 4096;
+  const bool idle = (n + 4095) / 4096 * nt <= 384;
+  const bool fits = n <= (1 << 20) && (n + 1023) / 1024 * nt * 8 <= part_cap;
+  return idle && fits ? 1024 : 4096;
 }
 
 // Whether sums of (at most) n sources of a segment on nt targets in all take

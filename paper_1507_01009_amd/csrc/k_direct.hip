@@ -354,11 +354,16 @@ __global__ __launch_bounds__(256) void k_direct_reduce(int64_t nt, int nchunks,
 // frozen stars stay) and sums their pull on every SMBH at the drifted
 // positions with the ranges, thread order and block reduction of
 // k_direct_few, so k_smbh_finish turns the partials into the same totals.
-// The stars' positions are read once instead of twice.
+// The stars' positions are read once instead of twice.  Bound by memory (4.2M
+// stars and two SMBHs 55.7 us, 6.1 TB/s).  The waves per SIMD are asked for:
+// 4.2M stars are 1025 blocks, and with two SMBHs the compiler took two
+// registers too many for five of them to a CU, so that the last one ran alone
+// (63.4 us).
 constexpr int kDriftSmbhMax = 4;
 
 template <int kNB>
-__global__ __launch_bounds__(256) void k_drift_smbh(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kNB == 1 ? 7 : kNB == 2 ? 5 : 3)))
+void k_drift_smbh(
     double *__restrict__ pos, const double *__restrict__ vel, const uint8_t *__restrict__ frozen,
     int64_t n, double dt, const double *__restrict__ sm, double seps,
     const double *__restrict__ bpos, const double *__restrict__ beps, int soft, int span,

@@ -79,7 +79,7 @@ def test_lines(plan, n, nt, nseg, path):
     assert plan([(CAP, n, nt, nseg)])[0][0] == path
 
 
-@pytest.mark.parametrize("n,nt,span", [(131072, 1, 1024), (1 << 20, 1, 1024), (1 << 22, 1, 4096),
+@pytest.mark.parametrize("n,nt,span", [(131072, 1, 1024), (1 << 20, 1, 1024), ((1 << 20) + 1, 1, 4096),
                                        (500000, 2, 1024), (50000, 24, 1024), (20000, 64, 1024), (131072, 12, 1024), (131072, 13, 4096),
                                        (250000, 24, 4096), (131072, 48, 4096), (8192, 127, 1024)])
 def test_few_target_ranges(plan, n, nt, span):
