@@ -1,0 +1,124 @@
+"""External point masses of the walk: terms formed with the targets' results up to
+16 masses of a system, by a kernel of their own beyond, against the same sums in
+extended precision on top of the walk without them."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_1507_01009_amd import ics
+from gpu_helpers import to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+def _terms(x, eps, pos, mass, soft):
+    """(acc, pot, sums of magnitudes) of the masses on x, long double, G = 1."""
+    d = x.astype(np.longdouble)[:, None, :] - pos.astype(np.longdouble)[None]
+    h = np.maximum(eps[1], eps[0]).astype(np.longdouble)
+    r = np.sqrt((d * d).sum(-1))
+    if soft == "plummer":
+        D1 = 1.0 / np.sqrt(r * r + h * h)
+        p0, p1 = D1, D1 ** 3
+    else:
+        u = r / h
+        p0 = np.where(u < 1, (7 / np.longdouble(5) + u ** 2 * (-2 / np.longdouble(3) + 3 * u ** 2 / 10 - u ** 3 / 10)) / h,
+                      np.where(u < 2, (8 / np.longdouble(5) + u ** 2 * (-4 / np.longdouble(3) + u - 3 * u ** 2 / 10
+                                       + u ** 3 / 30) - 1 / (15 * u)) / h, 1 / r))
+        p1 = np.where(u < 1, (4 / np.longdouble(3) + u ** 2 * (-6 / np.longdouble(5) + u / 2)) / h ** 3,
+                      np.where(u < 2, (8 / np.longdouble(3) - 3 * u + 6 * u ** 2 / 5 - u ** 3 / 6
+                                       - 1 / (15 * u ** 3)) / h ** 3, 1 / r ** 3))
+    w = (mass * p1)[..., None] * d
+    return -w.sum(1), -(mass * p0).sum(1), np.abs(w).sum(1), (mass * p0).sum(1)
+
+
+# A term: below 24 roundings of 2^-53 (with Plummer softening: difference,
+# r^2, root, division, cube, products), the spline's polynomials at their worst
+# some hundred (their pieces cancel by a factor of ten at most inside 2 h); the
+# sum of k terms k more; then the tree's part, a product with G and an addition
+def _tol(k, soft):
+    return ((30 if soft == "plummer" else 200) + k) * 2.0 ** -53
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("sizes,counts,every,soft", [
+    ((1021,), (16,), 1, "plummer"), ((1021,), (17,), 1, "plummer"), ((1021,), (17,), 1, "spline"),
+    ((63, 0, 700, 5000), (3, 5, 0, 40), 1, "plummer"), ((9001,), (300,), 7, "plummer"),
+    ((9001,), (300,), 7, "spline"), ((40, 4200), (1000, 24), 1, "plummer"), ((1,), (20,), 1, "plummer")])
+def test_externals_match_extended_precision(sizes, counts, every, soft, precision):
+    import torch
+    from paper_1507_01009_amd import binding as B
+    say("externals", sizes, counts, every, soft, precision)
+    n = sum(sizes)
+    rng = np.random.default_rng(n + sum(counts))
+    pos = np.concatenate([ics.plummer(max(s, 2), 3)[0][:s] for s in sizes])
+    m = rng.uniform(0.5, 1.5, n) / n
+    ep, em = rng.normal(size=(sum(counts), 3)), rng.uniform(0.1, 0.2, sum(counts))
+    ee = rng.choice([0.0, 0.02, 0.3], sum(counts))
+    act = np.arange(0, n, every, dtype=np.int32)
+    idx, na = (None, None) if every == 1 else (to_dev(act), to_dev(np.array([len(act)], np.int32)))
+    off = [0] + [int(x) for x in np.cumsum(sizes)]
+    seg = [0] + [int(x) for x in np.cumsum(counts)]
+    ctx = B.Context(n, max_systems=len(sizes), precision=precision)
+    ctx.set_softening(soft)
+    ctx.build_tree(to_dev(pos), off)
+    ctx.compute_moments(to_dev(m))
+    dev = [to_dev(ep), to_dev(em), to_dev(ee)]
+    out = []
+    for on in (False, True):
+        if on:
+            ctx.set_external(*dev, seg=seg)
+        acc = torch.full((n, 3), 7.0, dtype=torch.float64, device="cuda")
+        pot = torch.full((n,), 7.0, dtype=torch.float64, device="cuda")
+        ctx.tree_forces(0.05, 0.5, acc, pot, idx, na)
+        only = torch.full_like(acc, 7.0)
+        ctx.tree_forces(0.05, 0.5, only, None, idx, na)
+        ctx.sync()
+        assert torch.equal(acc, only)
+        out.append((acc.cpu().numpy(), pot.cpu().numpy()))
+    (a0, p0), (a1, p1) = out
+    rest = np.setdiff1d(np.arange(n), act)
+    assert np.all(a1[rest] == 7.0) and np.all(p1[rest] == 7.0)
+    for s in range(len(sizes)):
+        i = act[(act >= off[s]) & (act < off[s + 1])]
+        e = slice(seg[s], seg[s + 1])
+        ra, rp, sa, sp = _terms(pos[i], (0.05, ee[e]), ep[e], em[e], soft)
+        t = _tol(counts[s], soft)
+        assert np.all(np.abs(a1[i] - (a0[i] + ra)) <= t * (np.abs(a0[i]) + sa))
+        assert np.all(np.abs(p1[i] - (p0[i] + rp)) <= t * (np.abs(p0[i]) + sp))
+    ctx.close()
+
+
+def test_time_of_many_externals():
+    """A thousand masses take a few times the evaluation without them (as one
+    chain of terms after another for each split group, nine times)."""
+    import torch
+    from paper_1507_01009_amd import binding as B
+    n = 4096
+    ctx = B.Context(n, precision=B.TG_MIXED)
+    ctx.build_tree(to_dev(ics.plummer(n, 3)[0]))
+    ctx.compute_moments(to_dev(np.full(n, 1.0 / n)))
+    acc = torch.zeros((n, 3), dtype=torch.float64, device="cuda")
+    us = []
+    for k in (1, 1000):
+        say("externals, time", k)
+        rng = np.random.default_rng(k)
+        dev = [to_dev(rng.normal(size=(k, 3))), to_dev(np.full(k, 1e-3)), to_dev(np.full(k, 0.01))]
+        ctx.set_external(*dev)
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        best = 1e9
+        for _ in range(8):
+            ev[0].record()
+            for _ in range(10):
+                ctx.tree_forces(0.01, 0.5, acc)
+            ev[1].record()
+            ev[1].synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]) * 100.0)
+        us.append(best)
+    say("  %.1f and %.1f us" % tuple(us))
+    assert us[1] <= 4.0 * us[0]
