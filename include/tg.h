@@ -646,10 +646,10 @@ tg_status tg_autotune(tg_ctx *ctx, const double *pos_dev,
 
 /* ---- measurement ---------------------------------------------------------
  * With profiling on, every tg_tree_forces outside graph capture records a
- * pair of HIP events on the context's stream around its walk kernel (the
- * group walk with its P2P/P2M sums).  tg_get_profile waits for them and
- * returns the summed kernel time in ms and the number of walks since
- * profiling was last switched on. */
+ * pair of HIP events on the context's stream around its walk: the group walk
+ * with its P2P/P2M sums, the totals of split groups and the terms of external
+ * masses.  tg_get_profile waits for them and returns the summed time in ms
+ * and the number of walks since profiling was last switched on. */
 tg_status tg_set_profiling(tg_ctx *ctx, int32_t on);
 tg_status tg_get_profile(tg_ctx *ctx, double *walk_ms, int64_t *n_walks);
 

@@ -1727,10 +1727,6 @@ hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta, const int32_t
     if (rel) launch_force_kernel<true, false>(c, A);
     else launch_force_kernel<false, false>(c, A);
   }
-  if (after) {
-    hipError_t e = hipEventRecord(after, c->stream);
-    if (e != hipSuccess) return e;
-  }
   if (spline)
     hipLaunchKernelGGL(k_walk_finish<true>, dim3(kFinishBlocks), dim3(kFinishThreads), 0, c->stream,
                        c->gate, A, walk_blocks(c));
@@ -1741,6 +1737,10 @@ hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta, const int32_t
     const dim3 grid((unsigned)std::min<int64_t>((c->n + 63) / 64, 16384));
     hipLaunchKernelGGL((spline ? k_externals<true> : k_externals<false>), grid, dim3(256), 0,
                        c->stream, c->gate, X, c->n, b.sysoff, c->S);
+  }
+  if (after) {                     // the walk's results are whole
+    hipError_t e = hipEventRecord(after, c->stream);
+    if (e != hipSuccess) return e;
   }
   return hipGetLastError();
 }

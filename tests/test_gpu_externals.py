@@ -122,3 +122,37 @@ def test_time_of_many_externals():
         us.append(best)
     say("  %.1f and %.1f us" % tuple(us))
     assert us[1] <= 4.0 * us[0]
+
+
+@pytest.mark.parametrize("n", [1021, 30000])
+def test_walk_timer_holds_every_part(n):
+    """The walk's timer includes what external masses add to an evaluation,
+    wherever their terms are formed."""
+    import torch
+    from paper_1507_01009_amd import binding as B
+    ctx = B.Context(n)
+    ctx.build_tree(to_dev(ics.plummer(n, 3)[0]))
+    ctx.compute_moments(to_dev(np.full(n, 1.0 / n)))
+    acc = torch.zeros((n, 3), dtype=torch.float64, device="cuda")
+    timer, call = [], []
+    for k in (1, 1000):
+        say("walk timer", n, k)
+        rng = np.random.default_rng(k)
+        dev = [to_dev(rng.normal(size=(k, 3))), to_dev(np.full(k, 1e-3)), to_dev(np.full(k, 0.01))]
+        ctx.set_external(*dev)
+        ctx.tree_forces(0.01, 0.5, acc)
+        ctx.set_profiling(True)
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        ev[0].record()
+        for _ in range(50):
+            ctx.tree_forces(0.01, 0.5, acc)
+        ev[1].record()
+        ev[1].synchronize()
+        call.append(ev[0].elapsed_time(ev[1]) / 50)
+        ms, walks = ctx.get_profile()
+        ctx.set_profiling(False)
+        assert walks == 50
+        timer.append(ms / walks)
+    say("  timer %.4f %.4f ms, call %.4f %.4f ms" % (*timer, *call))
+    assert timer[1] - timer[0] >= 0.6 * (call[1] - call[0])
+    assert timer[1] <= 1.1 * call[1]
