@@ -55,3 +55,20 @@ def test_many_systems_smaller_than_a_group():
     sizes = np.random.default_rng(2).integers(0, 200, 60)
     pos = np.concatenate([ics.plummer(max(int(m), 2), 5 + k)[0][:m] for k, m in enumerate(sizes)])
     _check(pos, 8, 64, 21, [0] + list(np.cumsum(sizes)))
+
+
+@pytest.mark.parametrize("levels", [21, 42])
+@pytest.mark.parametrize("nl,ng", [(8, 4), (16, 3)])
+@pytest.mark.parametrize("n", [1, 5, 900, 1025, 4096])
+def test_groups_below_a_leaf_in_one_block_systems(n, nl, ng, levels):
+    """Smaller groups than leaves where a block sorts a system: the group
+    starts are cleared by the sort."""
+    say("groups below a leaf", n, nl, ng, levels)
+    _check(ics.plummer(max(n, 2), n + ng)[0][:n], nl, ng, levels)
+
+
+def test_groups_below_a_leaf_in_a_batch_of_small_systems():
+    say("groups below a leaf, batch")
+    sizes = np.random.default_rng(3).integers(0, 1500, 20)
+    pos = np.concatenate([ics.plummer(max(int(m), 2), 9 + k)[0][:m] for k, m in enumerate(sizes)])
+    _check(pos, 8, 4, 21, [0] + list(np.cumsum(sizes)))
