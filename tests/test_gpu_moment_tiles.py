@@ -72,3 +72,33 @@ def test_systems_across_tiles():
     off = np.array([0, 1, 700, 701, 701, 5000, n])
     pos = np.random.default_rng(7).normal(size=(n, 3)) ** 3
     _check(pos, np.full(n, 1e-3), 8, off)
+
+
+@pytest.mark.parametrize("n", [16896, 16897, 24001, 32768])
+def test_candidates_read_again_with_42_levels(n):
+    """More candidates of nodes beyond their tile than are kept, with 42 levels
+    from 34 tiles on.  Where no leaf reaches level 21, the tree and its moments
+    are those of 21 levels, bit for bit; below it, where pairs fall together
+    to the last levels, masses and centres are the oracle's."""
+    say("moment tiles, 42 levels", n)
+    pos, _, _ = ics.plummer(n, 90 + n)
+    mass = np.random.default_rng(n).uniform(0.5, 1.5, n) / n
+    a = gpu_run(pos, mass, 0.01, 0.5, 8, 64)["tree"]
+    b = gpu_run(pos, mass, 0.01, 0.5, 8, 64, key_levels=42)["tree"]
+    assert a["level"].max() < 21
+    for k in ("level", "first", "count", "child", "com", "mom"):
+        assert np.array_equal(a[k], b[k]), k
+    # leaves of one particle: the pairs make chains of nodes down to their level
+    rng = np.random.default_rng(n + 1)
+    h = n // 8
+    pos[n - h:] = pos[:h] + 1e-9 * rng.normal(size=(h, 3))
+    g = gpu_run(pos, mass, 0.01, 0.5, 1, 64, key_levels=42, max_nodes=60 * n)["tree"]
+    t = oracle.build_tree(pos, None, 1, levels=42)
+    sp, sm = oracle.sorted_arrays(t, pos, mass)
+    mom = oracle.moments(t, sp, sm)
+    assert t.level.max() > 21 and np.array_equal(g["nchild"], t.nchild)
+    # at most eight children a level over 42 levels, each sum rounded to 2^-53
+    # of its magnitude (of the centre: the largest coordinate)
+    tol = 8 * 42 * 2.0 ** -53
+    assert np.max(np.abs(g["mom"][:, 0] / mom[:, 0] - 1.0)) <= tol
+    assert np.max(np.abs(g["com"][:, :3] - mom[:, 1:4])) <= 2 * tol * np.abs(pos).max()
