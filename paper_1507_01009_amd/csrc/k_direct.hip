@@ -31,17 +31,14 @@ __device__ __forceinline__ int seg_of(const int64_t *off, int nseg, int64_t i) {
   return lo;
 }
 
-// 1 / sqrt(x) to about one unit in the last place: the hardware estimate and
-// one third-order step.  A rounded square root and division (1 / sqrt(x),
-// also about one unit) cost some 25 instructions more per pair; they stay
-// for everything but positive normal numbers (x = 0 of unsoftened coincident
-// pairs, subnormals, infinities, NaN).
+// 1 / sqrt(x) to about one unit in the last place: rsqrt_dp.  A rounded square
+// root and division (1 / sqrt(x), also about one unit) cost some 25
+// instructions more per pair; they stay for everything but positive normal
+// numbers (x = 0 of unsoftened coincident pairs, subnormals, infinities, NaN).
 __device__ __forceinline__ double inv_sqrt(double x) {
   constexpr int kPositiveNormal = 0x100;
   if (__builtin_expect(!__builtin_amdgcn_class(x, kPositiveNormal), 0)) return 1.0 / sqrt(x);
-  const double y = __builtin_amdgcn_rsq(x);
-  const double e = fma(-(x * y), y, 1.0);
-  return fma(y * e, fma(0.375, e, 0.5), y);
+  return rsqrt_dp(x);
 }
 
 // m/r and m/r^3 with the pair's softening ep (soft: cubic spline, h = ep).
@@ -130,7 +127,7 @@ __global__ void k_direct(const double *__restrict__ spos, const double *__restri
 // 65536 x 65536), with three and four the lanes' sums leave too few waves
 // (5.0e11, 5.2e11); two reach 6.1e11 (2.0e11 with one thread per target and
 // every source read from memory by every thread).  8191 targets on 262144
-// sources: 13.9 -> 3.9 ms.
+// sources: 13.9 -> 3.7 ms.
 template <int kT, bool kSelf, bool kSoft>
 __global__ __launch_bounds__(256) void k_direct_tile(
     const double *__restrict__ spos, const double *__restrict__ sm,

@@ -156,17 +156,6 @@ __device__ __forceinline__ bool mac_rel(const double lo[3], const double hi[3], 
   return near && apart;
 }
 
-// 1/sqrt(x) in double: hardware estimate, then one third-order Householder
-// step y <- y (1 + e/2 + 3e^2/8), e = 1 - x y^2.
-__device__ __forceinline__ double rsqrt_dp(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  double t = x * y;
-  double e = fma(-t, y, 1.0);
-  double p = fma(0.375, e, 0.5);
-  return fma(y * e, p, y);
-}
-
-
 // ---------------------------------------------------------------- terms
 template <class R> struct Vec4;
 template <> struct Vec4<float> { using T = float4; };

@@ -291,6 +291,16 @@ __device__ __forceinline__ double cell_centre(uint32_t v, int l, const uint32_t 
   return s;
 }
 
+// 1/sqrt(x) in double: hardware estimate, then one third-order Householder
+// step y <- y (1 + e/2 + 3e^2/8), e = 1 - x y^2.
+__device__ __forceinline__ double rsqrt_dp(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  double t = x * y;
+  double e = fma(-t, y, 1.0);
+  double p = fma(0.375, e, 0.5);
+  return fma(y * e, p, y);
+}
+
 // Cubic-spline softening (the Monaghan-Lattanzio kernel with support 2h,
 // h = the pair's softening): psi and psi_1 of a pair at distance r, in
 // double with correctly rounded divisions and square roots, for the SMBH
