@@ -97,7 +97,10 @@ void tg_default_config(tg_config *cfg);
 
 /* Create a context on the current HIP device, working on `stream`
  * (a hipStream_t; NULL = the default stream).  Allocates every device
- * buffer for the capacities in *cfg.  Errors: TG_EINVAL, TG_ENOMEM, TG_EHIP. */
+ * buffer for the capacities in *cfg, also those of features that are not
+ * used: partial sums of the walk are 4 KiB for each of 8192 items (fewer
+ * below 8192 particles), 33.5 MB on 256 compute units.
+ * Errors: TG_EINVAL, TG_ENOMEM, TG_EHIP. */
 tg_status tg_create(const tg_config *cfg, void *stream, tg_ctx **out);
 
 /* Free the context and its device memory (waits for its stream first). */

@@ -978,7 +978,7 @@ __device__ __forceinline__ void store_target(const WalkArgs &A, uint32_t sys, ui
 }
 
 // One wave takes one item at a time: a group, or one of the parts of a group
-// that was split to give every wave several items of about the same work.
+// that was split to give every wave an item of about the same work.
 // Each part makes the whole walk and evaluates every parts-th tile, so
 // lists, tiles and the sums inside a tile are those of the unsplit group;
 // the parts' FP64 totals are added in order by k_walk_finish.
@@ -1606,9 +1606,15 @@ static int walk_waves(const tg_ctx *c) {
   return std::max(1, c->n_cu * std::min(c->waves_per_cu, walk_per_cu(c)));
 }
 
-// Its launch.  The FP64 kernel fits a ninth wave into a CU: with many groups
-// per wave that is 2% faster (1M cusp 7.30 against 7.48 ms a step), with few
-// the SIMDs holding three waves end last (131072 stars 1.14 against 1.11 ms).
+// Its launch.  The FP64 kernel fits a ninth wave into a CU (three by its 167
+// registers into a SIMD, nine by 16 KB of LDS each).  An evaluation with eight
+// and with as many as fit, in us: 100003 stars 904 and 907, 131072 1017 and
+// 1025, 200000 1427 and 1412, 350000 2424 and 2380, 524287 3607 and 3528, 1M
+// 7201 and 7032; with few groups the SIMDs holding three waves end last.  The
+// rule goes by the particles, since only the device knows the active ones:
+// with 30% of 300000 active 996 and 1013 us, of 1M 2956 and 2907; with 10%
+// 604 and 598, 1362 and 1364; with 0.3% 342 and 339, 556 and 551.  Above the
+// line none of these is slower, below it either may be by 1 or 2%.
 static int walk_blocks(const tg_ctx *c) {
   return c->n >= (1 << 19) ? walk_grid(c) : walk_waves(c);
 }

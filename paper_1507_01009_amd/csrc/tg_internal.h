@@ -46,9 +46,12 @@ constexpr int kScanBlocks = 256;
 constexpr int kMaxWavesPerCU = 16;
 // The force walk splits groups into parts of at least kMinPart targets' work,
 // at most kMaxParts, until there are about kItemsPerWave items for each
-// resident wave.  (131072 stars: the walk takes 522 us with one item per wave
-// to fill, 537 with two, 592 with four, 585 unsplit; 1021 stars: 114 us
-// unsplit, 34 split, the same with 8 and 16 parts.)
+// resident wave.  A KDK step unsplit, with one, two and four items per wave to
+// fill, in us (medians of one run, spread 2%), mixed precision: 1021 stars 243,
+// 206, 207, 209; 20000 457, 280, 296, 303; 65536 551, 458, 460, 503; 131072
+// 685, 674, 670, 712; 250007 999, 1004, 1029, 1078.  FP64: 20000 512, 346, 349,
+// 365; 65536 754, 693, 643, 686; 131072 1037, 1030, 1030, 1083.  8 and 16
+// parts are alike (1021 stars).
 constexpr int kItemsPerWave = 1, kMaxParts = 8, kMinPart = 2;
 constexpr int kMaxExternal = 1024;               // SMBHs / external point masses
 constexpr int kMaxChain = 256;                   // chain members
