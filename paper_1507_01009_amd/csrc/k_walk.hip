@@ -982,9 +982,19 @@ __device__ __forceinline__ void store_target(const WalkArgs &A, uint32_t sys, ui
 // Each part makes the whole walk and evaluates every parts-th tile, so
 // lists, tiles and the sums inside a tile are those of the unsplit group;
 // the parts' FP64 totals are added in order by k_walk_finish.
-template <bool kMixed, bool kRel, bool kSpline>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kMixed ? TG_WALK_WAVES_MIXED : TG_WALK_WAVES_FP64)))
+//
+// kEven (FP64, Plummer): at most two waves on a SIMD.  The kernel needs 167
+// registers, so a SIMD takes three of its waves: of the eight that a CU is
+// given three can fall to one SIMD and one to another, and a walk of few
+// groups ends with those.  From 169 registers on (the compiler rounds up to
+// what the attribute says) they are two to each.  A walk in us without and with
+// it: 65536 stars 548 and 497, 80000 632 and 571, 100000 (slope 1.5) 738 and
+// 674, 131072 851 and 846, 160000 1006 and 1017, 250000 1528 and 1536.
+template <bool kMixed, bool kRel, bool kSpline, bool kEven>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kMixed ? TG_WALK_WAVES_MIXED : TG_WALK_WAVES_FP64,
+                                                                    kEven ? TG_WALK_WAVES_FP64 : 8)))
 void k_walk_forces(const int32_t *__restrict__ gate, WalkArgs A) {
+  static_assert(!kEven || (!kMixed && !kSpline), "the others fill a SIMD evenly");
   if (gate && *gate <= 0) return;   // nothing active: skipped
   __shared__ uint32_t s_tgt[kMaxGroup];
   __shared__ uint32_t s_m[kMCap];
@@ -1608,16 +1618,18 @@ static int walk_waves(const tg_ctx *c) {
 
 // Its launch.  The FP64 kernel fits a ninth wave into a CU (three by its 167
 // registers into a SIMD, nine by 16 KB of LDS each).  An evaluation with eight
-// and with as many as fit, in us: 100003 stars 904 and 907, 131072 1017 and
-// 1025, 200000 1427 and 1412, 350000 2424 and 2380, 524287 3607 and 3528, 1M
-// 7201 and 7032; with few groups the SIMDs holding three waves end last.  The
-// rule goes by the particles, since only the device knows the active ones:
-// with 30% of 300000 active 996 and 1013 us, of 1M 2956 and 2907; with 10%
-// 604 and 598, 1362 and 1364; with 0.3% 342 and 339, 556 and 551.  Above the
-// line none of these is slower, below it either may be by 1 or 2%.
+// and with as many as fit, in us: 200000 stars 1427 and 1412, 350000 2424 and
+// 2380, 524287 3607 and 3528, 1M 7201 and 7032.  The rule goes by the
+// particles, since only the device knows the active ones: with 30% of 300000
+// active 996 and 1013 us, of 1M 2956 and 2907; with 10% 604 and 598, 1362 and
+// 1364; with 0.3% 342 and 339, 556 and 551.  Above the line none of these is
+// slower, below it either may be by 1 or 2%.
 static int walk_blocks(const tg_ctx *c) {
   return c->n >= (1 << 19) ? walk_grid(c) : walk_waves(c);
 }
+// Particles below which an FP64 walk has its waves two to each SIMD: between
+// 131072, where that is 1% faster, and 160000, where it is 1% slower.
+constexpr int64_t kEvenBelow = 9 << 14;
 
 hipError_t launch_active_groups(tg_ctx *c, const int32_t *idx,
                                 const int32_t *n_act, const double *acc_old,
@@ -1675,12 +1687,13 @@ static RelArgs rel_args(tg_ctx *c, bool rel) {
 
 template <bool kRel, bool kSpline>
 static void launch_force_kernel(tg_ctx *c, const WalkArgs &A) {
-  if (c->cfg.precision == TG_MIXED)
-    hipLaunchKernelGGL((k_walk_forces<true, kRel, kSpline>), dim3(walk_blocks(c)), dim3(64), 0,
-                       c->stream, c->gate, A);
-  else
-    hipLaunchKernelGGL((k_walk_forces<false, kRel, kSpline>), dim3(walk_blocks(c)), dim3(64), 0,
-                       c->stream, c->gate, A);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(walk_blocks(c)), dim3(64), 0, c->stream, c->gate, A);
+  };
+  if (c->cfg.precision == TG_MIXED) return go(k_walk_forces<true, kRel, kSpline, false>);
+  if constexpr (!kSpline)              // (with the spline two waves fill a SIMD anyway)
+    if (c->n < kEvenBelow) return go(k_walk_forces<false, kRel, false, true>);
+  go(k_walk_forces<false, kRel, kSpline, false>);
 }
 
 hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta, const int32_t *n_act,

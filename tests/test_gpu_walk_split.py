@@ -114,3 +114,22 @@ def test_replayed_walk_on_a_tree_of_other_sizes(precision):
             assert torch.equal(out, ref), (nl, ng)
         del graph
         ctx.close()
+
+
+@pytest.mark.parametrize("alpha", [None, 1e-3])
+def test_fp64_walks_on_both_sides_of_the_even_line(alpha):
+    """147456 particles take the FP64 kernel without the limit on a SIMD's
+    waves, one fewer the other: the same terms and tiles."""
+    n = 147455
+    say("even", n, alpha)
+    pos, _, m = ics.plummer(n, 77)
+    old = None if alpha is None else np.full((n, 3), 0.3)
+    a = gpu_run(pos, m, 0.01, 0.5, 8, 64, alpha=alpha, acc_old=old)
+    far = np.full((1, 3), 50.0)
+    b = gpu_run(np.concatenate([pos, far]), np.append(m, 1.0), 0.01, 0.5, 8, 64,
+                sys_off=np.array([0, n, n + 1]), alpha=alpha,
+                acc_old=None if old is None else np.concatenate([old, far]))
+    e = rel_err(b["acc"][:n], a["acc"]).max()
+    say("  acc %.3g" % e)
+    assert e <= TOL
+    assert (a["counts"]["n_p2p"], a["counts"]["n_p2m"]) == (b["counts"]["n_p2p"], b["counts"]["n_p2m"])
