@@ -63,6 +63,8 @@ namespace tg {
 #define TG_WALK_WAVES_FP64 2
 #endif
 
+constexpr uint32_t kAllParts = 1u << 31;    // of an item: all parts, by one wave
+
 constexpr int kTile = 128;                  // source tile entries (a flush uses <= 128)
 constexpr int kMCap = 128 + 64;             // P2M cell list (LDS): < one flush + one append
 constexpr int kQCap = 128 + 64 * 8;         // P2P particle queue (LDS); overflow goes leaf by leaf
@@ -82,7 +84,7 @@ struct WalkArgs {
   const uint32_t *perm;
   TreeCounters *ctr;
   unsigned long long *wtot;   // force walk: per workgroup {P2P, P2M, targets, groups}
-  const uint2 *items;         // force walk: {group, part | (parts - 1) << 5 | first slot << 10}
+  const uint2 *items;         // force walk: {group, part | (parts - 1) << 5 | first slot << 10 | all}
   uint32_t item_gap;          // extra entries of each queue's range of items
   const uint2 *slots;         // split groups: {group, parts} at the slot of part 0
   double4 *wpart;             // partial results of split groups [slot][kMaxGroup]
@@ -351,7 +353,9 @@ template <> union __align__(16) TileMem<false> {
 };
 
 // ------------------------------------------- one wave's tiles and targets
-template <bool kMixed, bool kSpline>
+// (kWhole only keeps the functions of that form's kernels apart from the
+// others', whose inlining they would change)
+template <bool kMixed, bool kSpline, bool kWhole>
 struct Eval {
   using R = typename std::conditional<kMixed, float, double>::type;
   using R4 = typename Vec4<R>::T;
@@ -652,10 +656,12 @@ struct Eval {
 
 // ------------------------------------------------------- force-mode sink
 // The lists of a group; an item that is one of several parts of a group
-// evaluates every parts-th tile.
-template <bool kMixed, bool kSpline>
-struct ForceSink : Eval<kMixed, kSpline> {
-  using E = Eval<kMixed, kSpline>;
+// evaluates every parts-th tile.  With kWhole an item may also be a split
+// group as a whole (all): its tiles go to the parts' sums in turn, so that
+// each sum is the one that the part alone would form.
+template <bool kMixed, bool kSpline, bool kWhole>
+struct ForceSink : Eval<kMixed, kSpline, kWhole> {
+  using E = Eval<kMixed, kSpline, kWhole>;
   using E::F; using E::g0; using E::gn; using E::own0; using E::own1;
   using E::flush_p2m; using E::flush_p2p; using E::flush_own;
   uint32_t *s_m;
@@ -663,11 +669,42 @@ struct ForceSink : Eval<kMixed, kSpline> {
   uint32_t nm, nq;
   unsigned long long cells, parts;   // wave-uniform totals
   int turn, parts_;                  // tiles until this item's next one; the group's parts
+  bool all;                          // kWhole: turn is the next tile's part
+  double (*sum)[E::kMaxT][4];        // kWhole: [part], in an array of its own (scratch memory)
 
   __device__ bool my_turn() {
+    if constexpr (kWhole)
+      if (all) return true;
     const bool mine = turn == 0;
     turn = mine ? parts_ - 1 : turn - 1;
     return mine;
+  }
+
+  // kWhole: no sums yet; a tile's sums (the only ones in hax ..) to its part's;
+  // part p's sums to hax ..
+  __device__ void start_parts() {
+    for (int p = 0; p < parts_; ++p)
+#pragma unroll
+      for (int k = 0; k < E::kMaxT; ++k) sum[p][k][0] = sum[p][k][1] = sum[p][k][2] = sum[p][k][3] = 0.0;
+  }
+  __device__ void tile_done() {
+    if constexpr (kWhole) {
+      if (!all) return;
+#pragma unroll
+      for (int k = 0; k < E::kMaxT; ++k) {
+        double *o = sum[turn][k];
+        o[0] += this->hax[k]; o[1] += this->hay[k]; o[2] += this->haz[k]; o[3] += this->hph[k];
+        this->hax[k] = this->hay[k] = this->haz[k] = this->hph[k] = 0.0;
+      }
+      turn = turn + 1 == parts_ ? 0 : turn + 1;
+    }
+  }
+  __device__ void take_part(int p) {
+#pragma unroll
+    for (int k = 0; k < E::kMaxT; ++k) {
+      const double *o = sum[p][k];
+      this->hax[k] = o[0]; this->hay[k] = o[1]; this->haz[k] = o[2]; this->hph[k] = o[3];
+    }
   }
 
   // Queue the particles [lf, lf + lc), flushing whenever a tile is full.
@@ -692,14 +729,14 @@ struct ForceSink : Eval<kMixed, kSpline> {
     cells += c;
     wave_sync();
     if (nm >= (uint32_t)F) {          // nm < F + 64 <= 2 F: one flush
-      if (my_turn()) flush_p2m(A, s_m + (nm - F), F);
+      if (my_turn()) { flush_p2m(A, s_m + (nm - F), F); tile_done(); }
       nm -= F;
     }
   }
 
   __device__ void drain_q(const WalkArgs &A) {
     while (nq >= (uint32_t)F) {
-      if (my_turn()) flush_p2p(A, s_q + (nq - F), F);
+      if (my_turn()) { flush_p2p(A, s_q + (nq - F), F); tile_done(); }
       nq -= F;
     }
   }
@@ -744,14 +781,14 @@ struct ForceSink : Eval<kMixed, kSpline> {
   }
 
   __device__ void finish(const WalkArgs &A) {
-    if (nm > 0 && my_turn()) flush_p2m(A, s_m, (int)nm);
+    if (nm > 0 && my_turn()) { flush_p2m(A, s_m, (int)nm); tile_done(); }
     nm = 0;
     // the queue's rest (nq < F) and the own particles share the last tiles
     const uint32_t no = this->own_count();
     uint32_t o = 0;
     while (nq + (no - o) > 0u) {
       const uint32_t k = min(no - o, (uint32_t)F - nq);
-      if (my_turn()) flush_own(A, s_q, (int)nq, o, (int)k);
+      if (my_turn()) { flush_own(A, s_q, (int)nq, o, (int)k); tile_done(); }
       nq = 0;
       o += k;
     }
@@ -983,24 +1020,35 @@ __device__ __forceinline__ void store_target(const WalkArgs &A, uint32_t sys, ui
 // lists, tiles and the sums inside a tile are those of the unsplit group;
 // the parts' FP64 totals are added in order by k_walk_finish.
 //
-// kEven (FP64, Plummer): at most two waves on a SIMD.  The kernel needs 167
+// kEven (form; FP64, Plummer): at most two waves on a SIMD.  The kernel needs 167
 // registers, so a SIMD takes three of its waves: of the eight that a CU is
 // given three can fall to one SIMD and one to another, and a walk of few
 // groups ends with those.  From 169 registers on (the compiler rounds up to
 // what the attribute says) they are two to each.  A walk in us without and with
 // it: 65536 stars 548 and 497, 80000 632 and 571, 100000 (slope 1.5) 738 and
 // 674, 131072 851 and 846, 160000 1006 and 1017, 250000 1528 and 1536.
-template <bool kMixed, bool kRel, bool kSpline, bool kEven>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kMixed ? TG_WALK_WAVES_MIXED : TG_WALK_WAVES_FP64,
-                                                                    kEven ? TG_WALK_WAVES_FP64 : 8)))
+//
+// kWhole (form): for contexts that ask for at most four waves per CU.  Where
+// these have several groups each, nothing is gained by parts, and what they
+// repeat is lost; but results may not depend on the waves, so one wave walks a
+// split group once and keeps the parts' sums apart (in scratch memory, of which
+// a tile reads and writes one part's).  A walk in us before groups were split,
+// with parts alone and with this, mixed precision: 20000 stars on one wave per
+// CU 519, 867 and 537, on two 376, 486 and 374; 50000 on one 1280, 1572 and
+// 1302, on four 423, 487 and 440; 100000 on one 2647, 2780 and 2622.
+enum WalkForm { kFull, kEven, kWhole };
+template <bool kMixed, bool kRel, bool kSpline, WalkForm kForm>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
+    kForm == kWhole ? 1 : kMixed ? TG_WALK_WAVES_MIXED : TG_WALK_WAVES_FP64,
+    kForm == kEven ? TG_WALK_WAVES_FP64 : 8)))
 void k_walk_forces(const int32_t *__restrict__ gate, WalkArgs A) {
-  static_assert(!kEven || (!kMixed && !kSpline), "the others fill a SIMD evenly");
+  static_assert(kForm != kEven || (!kMixed && !kSpline), "the others fill a SIMD evenly");
   if (gate && *gate <= 0) return;   // nothing active: skipped
   __shared__ uint32_t s_tgt[kMaxGroup];
   __shared__ uint32_t s_m[kMCap];
   __shared__ uint32_t s_q[kQCap];
   __shared__ TileMem<kMixed> tile;
-  using Sink = ForceSink<kMixed, kSpline>;
+  using Sink = ForceSink<kMixed, kSpline, kForm == kWhole>;
   const unsigned lane = lane_id();
   const uint32_t n_groups = A.ctr->n_active_groups;
   unsigned long long tot_p2p = 0, tot_p2m = 0, tot_t = 0, tot_g = 0;
@@ -1021,27 +1069,41 @@ void k_walk_forces(const int32_t *__restrict__ gate, WalkArgs A) {
     S.s_m = s_m; S.s_q = s_q; S.tile = &tile;
     S.nm = 0; S.nq = 0; S.cells = 0; S.parts = 0;
     S.turn = (int)part; S.parts_ = (int)parts;
+    [[maybe_unused]] double sums[kForm == kWhole ? kMaxParts : 1][Sink::E::kMaxT][4];
+    if constexpr (kForm == kWhole) {
+      S.all = (item.y & kAllParts) != 0u;
+      S.sum = sums;
+      if (S.all) S.start_parts();
+    }
     S.init(A, gr, lo, hi, s_tgt, nt);
     const bool ok = traverse<kRel>(A, S, blockIdx.x, A.root_of[gr.w], lo, hi,
                                    kRel ? A.arel[g] : 0.0);
-    S.store_red();
-    const double *red = tile.red;
-    __syncthreads();
     // rows of kMaxGroup, not of the context's group size: a captured walk is
     // replayed on trees built with another one
-    double4 *out = A.wpart + (size_t)((item.y >> 10) + part) * kMaxGroup;
-    for (int i = (int)lane; i < nt; i += 64) {
-      // target i sits at k = i / lt, lane-target i % lt of every slice; sum
-      // the slices in slice order (deterministic)
-      const int k = i / S.lt, jj = i % S.lt;
-      double ax = 0.0, ay = 0.0, az = 0.0, ph = 0.0;
-      for (int q = 0; q < S.slices; ++q) {
-        const double *o = red + 4 * (64 * k + q * S.lt + jj);
-        ax += o[0]; ay += o[1]; az += o[2]; ph += o[3];
+    const uint32_t slot0 = (kForm == kWhole ? item.y & ~kAllParts : item.y) >> 10;
+    double4 *out = A.wpart + (size_t)(slot0 + part) * kMaxGroup;
+    const uint32_t rows = kForm == kWhole && S.all ? parts : 1u;
+    for (uint32_t r = 0; r < rows; ++r, out += kMaxGroup) {
+      if constexpr (kForm == kWhole) {
+        if (S.all) S.take_part((int)r);
+        if (r > 0u) __syncthreads();   // the row before has been summed
       }
-      if (!ok) ax = ay = az = ph = __longlong_as_double(0x7ff8000000000000ll);
-      if (parts > 1u) out[i] = make_double4(ax, ay, az, ph);
-      else store_target<kSpline>(A, gr.w, s_tgt[i], ax, ay, az, ph);
+      S.store_red();
+      const double *red = tile.red;
+      __syncthreads();
+      for (int i = (int)lane; i < nt; i += 64) {
+        // target i sits at k = i / lt, lane-target i % lt of every slice; sum
+        // the slices in slice order (deterministic)
+        const int k = i / S.lt, jj = i % S.lt;
+        double ax = 0.0, ay = 0.0, az = 0.0, ph = 0.0;
+        for (int q = 0; q < S.slices; ++q) {
+          const double *o = red + 4 * (64 * k + q * S.lt + jj);
+          ax += o[0]; ay += o[1]; az += o[2]; ph += o[3];
+        }
+        if (!ok) ax = ay = az = ph = __longlong_as_double(0x7ff8000000000000ll);
+        if (parts > 1u) out[i] = make_double4(ax, ay, az, ph);
+        else store_target<kSpline>(A, gr.w, s_tgt[i], ax, ay, az, ph);
+      }
     }
     if (part == 0u) {
       tot_p2m += S.cells * (unsigned long long)nt;
@@ -1374,7 +1436,7 @@ __device__ __forceinline__ uint64_t block_exclusive_scan64(uint64_t v, uint64_t 
 __device__ __forceinline__ void order_items(TreeCounters *ctr, const uint32_t *__restrict__ alist,
                                             const uint32_t *__restrict__ acnt,
                                             const int32_t *__restrict__ n_act, int64_t n,
-                                            uint32_t want, uint32_t gap,
+                                            uint32_t want, uint32_t gap, uint32_t whole,
                                             uint2 *__restrict__ items, uint2 *__restrict__ slots) {
   __shared__ uint64_t scan_sh[kOrderThreads / 64];
   __shared__ uint32_t s_g[kOrderChunk];
@@ -1388,6 +1450,7 @@ __device__ __forceinline__ void order_items(TreeCounters *ctr, const uint32_t *_
   const uint32_t targets = (uint32_t)(n_act ? min((int64_t)n_act[0], n) : n);
   const uint32_t per = max((uint32_t)kMinPart, (targets + want - 1u) / want);
   auto parts_of = [&](uint32_t nt) { return min((uint32_t)kMaxParts, (nt + per - 1u) / per); };
+  const bool one = G >= whole;      // a split group is one item
   // the range's items of each class and slots
   uint32_t cnt[kSizeClasses + 1] = {};
   for (uint32_t p0 = lo + tid; p0 < hi; p0 += kOrderChunk) {
@@ -1402,7 +1465,7 @@ __device__ __forceinline__ void order_items(TreeCounters *ctr, const uint32_t *_
       if (p0 + j * kOrderThreads >= hi) continue;
       const uint32_t k = size_class(nt[j]), np = parts_of(nt[j]);
 #pragma unroll
-      for (uint32_t q = 0; q < kSizeClasses; ++q) cnt[q] += k == q ? np : 0u;
+      for (uint32_t q = 0; q < kSizeClasses; ++q) cnt[q] += k == q ? (one ? min(np, 1u) : np) : 0u;
       cnt[kSizeClasses] += np > 1u ? np : 0u;
     }
   }
@@ -1457,7 +1520,7 @@ __device__ __forceinline__ void order_items(TreeCounters *ctr, const uint32_t *_
     for (uint32_t j = 0; j < kOrderItems; ++j) {
       if (r0 + j >= m) break;
       const uint32_t nt = s_n[r0 + j], np = parts_of(nt);
-      mine += (uint64_t)np << (16u * size_class(nt));
+      mine += (uint64_t)(one ? min(np, 1u) : np) << (16u * size_class(nt));
       my_slots += np > 1u ? np : 0u;
     }
     uint64_t tot;
@@ -1475,12 +1538,13 @@ __device__ __forceinline__ void order_items(TreeCounters *ctr, const uint32_t *_
 #pragma unroll
       for (uint32_t q = 1; q < kSizeClasses; ++q) dst = k == q ? at[q] : dst;
 #pragma unroll
-      for (uint32_t q = 0; q < kSizeClasses; ++q) at[q] += k == q ? np : 0u;
+      for (uint32_t q = 0; q < kSizeClasses; ++q) at[q] += k == q ? (one ? min(np, 1u) : np) : 0u;
       if (np == 1u) {
         items[dst] = make_uint2(g, 0u);
       } else {
         for (uint32_t e = 0; e < np; ++e) {
-          items[dst + e] = make_uint2(g, e | (np - 1u) << 5 | s0 << 10);
+          if (e == 0u || !one)
+            items[dst + e] = make_uint2(g, e | (np - 1u) << 5 | s0 << 10 | (one ? kAllParts : 0u));
           slots[s0 + e] = make_uint2(g, e == 0u ? np : 0u);
         }
         s0 += np;
@@ -1562,11 +1626,11 @@ template <class R>
 __global__ __launch_bounds__(kOrderThreads) void k_walk_prepare(
     const int32_t *__restrict__ gate, TreeCounters *ctr, const uint32_t *__restrict__ alist,
     const uint32_t *__restrict__ acnt, const int32_t *__restrict__ n_act, int64_t n, uint32_t want,
-    uint32_t gap, uint2 *__restrict__ items, uint2 *__restrict__ slots,
+    uint32_t gap, uint32_t whole, uint2 *__restrict__ items, uint2 *__restrict__ slots,
     const double *__restrict__ mom, double eps2, int spline, void *cell, RelArgs rel) {
   if (gate && *gate <= 0) return;   // nothing active: skipped
   if (blockIdx.x < 8u) {
-    order_items(ctr, alist, acnt, n_act, n, want, gap, items, slots);
+    order_items(ctr, alist, acnt, n_act, n, want, gap, whole, items, slots);
     return;
   }
   const uint32_t v0 = (blockIdx.x - 8u) * kOrderThreads + threadIdx.x;
@@ -1630,6 +1694,17 @@ static int walk_blocks(const tg_ctx *c) {
 // Particles below which an FP64 walk has its waves two to each SIMD: between
 // 131072, where that is 1% faster, and 160000, where it is 1% slower.
 constexpr int64_t kEvenBelow = 9 << 14;
+// Whether split groups are taken as a whole where there are enough groups for
+// the context's waves, and from how many on: 5/4 of the waves with one wave per
+// CU, twice as many with four.  A walk in us by parts and as a whole, mixed
+// precision: with one wave 4096 stars (300 groups) 223 and 226, 6000 311 and
+// 261; with two (512 waves) 10000 273 and 280, 14000 356 and 338; with four
+// 30000 357 and 396, 40000 (2000) 428 and 414; with six the parts are faster or
+// alike (50000 stars 411 unsplit and 372, 100000 587 and 600).
+static bool walk_whole(const tg_ctx *c) { return c->waves_per_cu <= 4; }
+static uint32_t whole_from(const tg_ctx *c, uint32_t waves) {
+  return waves + waves / 4u * (uint32_t)c->waves_per_cu;
+}
 
 hipError_t launch_active_groups(tg_ctx *c, const int32_t *idx,
                                 const int32_t *n_act, const double *acc_old,
@@ -1686,14 +1761,18 @@ static RelArgs rel_args(tg_ctx *c, bool rel) {
 }
 
 template <bool kRel, bool kSpline>
-static void launch_force_kernel(tg_ctx *c, const WalkArgs &A) {
+static void launch_force_kernel(tg_ctx *c, const WalkArgs &A, bool whole) {
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(walk_blocks(c)), dim3(64), 0, c->stream, c->gate, A);
   };
-  if (c->cfg.precision == TG_MIXED) return go(k_walk_forces<true, kRel, kSpline, false>);
+  const bool mixed = c->cfg.precision == TG_MIXED;
+  if (whole)
+    return mixed ? go(k_walk_forces<true, kRel, kSpline, kWhole>)
+                 : go(k_walk_forces<false, kRel, kSpline, kWhole>);
+  if (mixed) return go(k_walk_forces<true, kRel, kSpline, kFull>);
   if constexpr (!kSpline)              // (with the spline two waves fill a SIMD anyway)
-    if (c->n < kEvenBelow) return go(k_walk_forces<false, kRel, false, true>);
-  go(k_walk_forces<false, kRel, kSpline, false>);
+    if (c->n < kEvenBelow) return go(k_walk_forces<false, kRel, false, kEven>);
+  go(k_walk_forces<false, kRel, kSpline, kFull>);
 }
 
 hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta, const int32_t *n_act,
@@ -1722,18 +1801,19 @@ hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta, const int32_t
   const bool mixed = c->cfg.precision == TG_MIXED;
   hipLaunchKernelGGL((mixed ? k_walk_prepare<float> : k_walk_prepare<double>),
                      dim3(8 + kRecordBlocks), dim3(kOrderThreads), 0, c->stream, c->gate, b.ctr,
-                     b.alist, b.acnt, n_act, c->n, want, (uint32_t)c->split_cap, b.items, b.slots,
+                     b.alist, b.acnt, n_act, c->n, want, (uint32_t)c->split_cap,
+                     walk_whole(c) ? whole_from(c, A.starts) : ~0u, b.items, b.slots,
                      b.mom, A.eps2, spline, (void *)b.cell, rel_args(c, rel));
   if (before) {
     hipError_t e = hipEventRecord(before, c->stream);
     if (e != hipSuccess) return e;
   }
   if (spline) {
-    if (rel) launch_force_kernel<true, true>(c, A);
-    else launch_force_kernel<false, true>(c, A);
+    if (rel) launch_force_kernel<true, true>(c, A, walk_whole(c));
+    else launch_force_kernel<false, true>(c, A, walk_whole(c));
   } else {
-    if (rel) launch_force_kernel<true, false>(c, A);
-    else launch_force_kernel<false, false>(c, A);
+    if (rel) launch_force_kernel<true, false>(c, A, walk_whole(c));
+    else launch_force_kernel<false, false>(c, A, walk_whole(c));
   }
   if (spline)
     hipLaunchKernelGGL(k_walk_finish<true>, dim3(kFinishBlocks), dim3(kFinishThreads), 0, c->stream,

@@ -133,3 +133,53 @@ def test_fp64_walks_on_both_sides_of_the_even_line(alpha):
     say("  acc %.3g" % e)
     assert e <= TOL
     assert (a["counts"]["n_p2p"], a["counts"]["n_p2m"]) == (b["counts"]["n_p2p"], b["counts"]["n_p2m"])
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("soft,alpha", [(None, None), ("spline", None), (None, 1e-3), ("spline", 1e-3)])
+@pytest.mark.parametrize("n,ng,every", [(9000, 64, 1), (20000, 128, 3), (33000, 64, 1)])
+def test_few_waves_give_the_same_bits(n, ng, every, soft, alpha, precision):
+    """One, two and four waves per CU, which take split groups as a whole where
+    each has several (20000 stars: 900 groups, 256 waves), against all waves."""
+    say("few waves", n, ng, every, soft, alpha, precision)
+    pos, _, m = ics.plummer(n, 500 + n)
+    act = None if every == 1 else np.arange(0, n, every, dtype=np.int32)
+    old = None if alpha is None else np.random.default_rng(n).normal(size=(n, 3))
+    runs = [gpu_run(pos, m, 0.01, 0.5, 8, ng, active=act, precision=precision, softening=soft,
+                    alpha=alpha, acc_old=old, waves_per_cu=w) for w in (0, 1, 2, 4)]
+    for r in runs[1:]:
+        assert np.array_equal(r["acc"], runs[0]["acc"], equal_nan=True)
+        assert np.array_equal(r["pot"], runs[0]["pot"], equal_nan=True)
+        assert r["counts"] == runs[0]["counts"]
+
+
+def test_time_with_one_wave_per_cu():
+    """One wave per CU takes some three times as long on 20000 stars as all
+    waves (five times where it takes the parts of a group one by one, each
+    with the whole traversal)."""
+    import torch
+    from paper_1507_01009_amd import binding as B
+    from gpu_helpers import to_dev
+    n = 20000
+    pos, _, m = ics.plummer(n, 3)
+    dp, dm = to_dev(pos), to_dev(m)
+    acc = torch.zeros((n, 3), dtype=torch.float64, device="cuda")
+    us = []
+    for w in (0, 1):
+        say("few waves, time", w)
+        ctx = B.Context(n, precision=B.TG_MIXED, waves_per_cu=w)
+        ctx.build_tree(dp)
+        ctx.compute_moments(dm)
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        best = 1e9
+        for _ in range(8):
+            ev[0].record()
+            for _ in range(10):
+                ctx.tree_forces(0.01, 0.5, acc)
+            ev[1].record()
+            ev[1].synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]) * 100.0)
+        us.append(best)
+        ctx.close()
+    say("  %.1f and %.1f us" % tuple(us))
+    assert us[1] <= 4.0 * us[0]
