@@ -1020,13 +1020,15 @@ __device__ __forceinline__ void store_target(const WalkArgs &A, uint32_t sys, ui
 // lists, tiles and the sums inside a tile are those of the unsplit group;
 // the parts' FP64 totals are added in order by k_walk_finish.
 //
-// kEven (form; FP64, Plummer): at most two waves on a SIMD.  The kernel needs 167
-// registers, so a SIMD takes three of its waves: of the eight that a CU is
-// given three can fall to one SIMD and one to another, and a walk of few
-// groups ends with those.  From 169 registers on (the compiler rounds up to
-// what the attribute says) they are two to each.  A walk in us without and with
-// it: 65536 stars 548 and 497, 80000 632 and 571, 100000 (slope 1.5) 738 and
-// 674, 131072 851 and 846, 160000 1006 and 1017, 250000 1528 and 1536.
+// kEven (form; FP64, Plummer): at most two waves on a SIMD.  The kernel needs
+// 167 registers, so a SIMD takes three of its waves: of the eight that a CU is
+// given three can fall to one SIMD and one to another, and a walk of few groups
+// ends with those.  With 169 registers or more they are two to each, so this
+// form names a higher one as overwritten.  (Asked for by the attribute, two
+// waves at most change the schedule as well, and small walks take up to 20%
+// longer.)  A walk in us without and with it: 1000 stars 51 and 51, 24000 245
+// and 241, 50000 444 and 376, 65536 554 and 486, 80000 634 and 557, 100000 720
+// and 662, 131072 867 and 837, 160000 1024 and 1029.
 //
 // kWhole (form): for contexts that ask for at most four waves per CU.  Where
 // these have several groups each, nothing is gained by parts, and what they
@@ -1038,11 +1040,10 @@ __device__ __forceinline__ void store_target(const WalkArgs &A, uint32_t sys, ui
 // 1302, on four 423, 487 and 440; 100000 on one 2647, 2780 and 2622.
 enum WalkForm { kFull, kEven, kWhole };
 template <bool kMixed, bool kRel, bool kSpline, WalkForm kForm>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
-    kForm == kWhole ? 1 : kMixed ? TG_WALK_WAVES_MIXED : TG_WALK_WAVES_FP64,
-    kForm == kEven ? TG_WALK_WAVES_FP64 : 8)))
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kMixed ? TG_WALK_WAVES_MIXED : TG_WALK_WAVES_FP64)))
 void k_walk_forces(const int32_t *__restrict__ gate, WalkArgs A) {
   static_assert(kForm != kEven || (!kMixed && !kSpline), "the others fill a SIMD evenly");
+  if constexpr (kForm == kEven) asm volatile("" ::: "v170");
   if (gate && *gate <= 0) return;   // nothing active: skipped
   __shared__ uint32_t s_tgt[kMaxGroup];
   __shared__ uint32_t s_m[kMCap];
@@ -1692,7 +1693,7 @@ static int walk_blocks(const tg_ctx *c) {
   return c->n >= (1 << 19) ? walk_grid(c) : walk_waves(c);
 }
 // Particles below which an FP64 walk has its waves two to each SIMD: between
-// 131072, where that is 1% faster, and 160000, where it is 1% slower.
+// 131072, where that is 3% faster, and 160000, where it is alike.
 constexpr int64_t kEvenBelow = 9 << 14;
 // Whether split groups are taken as a whole where there are enough groups for
 // the context's waves, and from how many on: 5/4 of the waves with one wave per
