@@ -1020,7 +1020,7 @@ __device__ __forceinline__ void store_target(const WalkArgs &A, uint32_t sys, ui
 // lists, tiles and the sums inside a tile are those of the unsplit group;
 // the parts' FP64 totals are added in order by k_walk_finish.
 //
-// kEven (form; FP64, Plummer): at most two waves on a SIMD.  The kernel needs
+// kFormEven (FP64, Plummer): at most two waves on a SIMD.  The kernel needs
 // 167 registers, so a SIMD takes three of its waves: of the eight that a CU is
 // given three can fall to one SIMD and one to another, and a walk of few groups
 // ends with those.  With 169 registers or more they are two to each, so this
@@ -1030,7 +1030,7 @@ __device__ __forceinline__ void store_target(const WalkArgs &A, uint32_t sys, ui
 // and 241, 50000 444 and 376, 65536 554 and 486, 80000 634 and 557, 100000 720
 // and 662, 131072 867 and 837, 160000 1024 and 1029.
 //
-// kWhole (form): for contexts that ask for at most four waves per CU.  Where
+// kFormWhole: for contexts that ask for at most four waves per CU.  Where
 // these have several groups each, nothing is gained by parts, and what they
 // repeat is lost; but results may not depend on the waves, so one wave walks a
 // split group once and keeps the parts' sums apart (in scratch memory, of which
@@ -1038,18 +1038,18 @@ __device__ __forceinline__ void store_target(const WalkArgs &A, uint32_t sys, ui
 // with parts alone and with this, mixed precision: 20000 stars on one wave per
 // CU 519, 867 and 537, on two 376, 486 and 374; 50000 on one 1280, 1572 and
 // 1302, on four 423, 487 and 440; 100000 on one 2647, 2780 and 2622.
-enum WalkForm { kFull, kEven, kWhole };
-template <bool kMixed, bool kRel, bool kSpline, WalkForm kForm>
+constexpr int kFormFull = 0, kFormEven = 1, kFormWhole = 2;
+template <bool kMixed, bool kRel, bool kSpline, int kForm>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kMixed ? TG_WALK_WAVES_MIXED : TG_WALK_WAVES_FP64)))
 void k_walk_forces(const int32_t *__restrict__ gate, WalkArgs A) {
-  static_assert(kForm != kEven || (!kMixed && !kSpline), "the others fill a SIMD evenly");
-  if constexpr (kForm == kEven) asm volatile("" ::: "v170");
+  static_assert(kForm != kFormEven || (!kMixed && !kSpline), "the others fill a SIMD evenly");
+  if constexpr (kForm == kFormEven) asm volatile("" ::: "v170");
   if (gate && *gate <= 0) return;   // nothing active: skipped
   __shared__ uint32_t s_tgt[kMaxGroup];
   __shared__ uint32_t s_m[kMCap];
   __shared__ uint32_t s_q[kQCap];
   __shared__ TileMem<kMixed> tile;
-  using Sink = ForceSink<kMixed, kSpline, kForm == kWhole>;
+  using Sink = ForceSink<kMixed, kSpline, kForm == kFormWhole>;
   const unsigned lane = lane_id();
   const uint32_t n_groups = A.ctr->n_active_groups;
   unsigned long long tot_p2p = 0, tot_p2m = 0, tot_t = 0, tot_g = 0;
@@ -1070,8 +1070,8 @@ void k_walk_forces(const int32_t *__restrict__ gate, WalkArgs A) {
     S.s_m = s_m; S.s_q = s_q; S.tile = &tile;
     S.nm = 0; S.nq = 0; S.cells = 0; S.parts = 0;
     S.turn = (int)part; S.parts_ = (int)parts;
-    [[maybe_unused]] double sums[kForm == kWhole ? kMaxParts : 1][Sink::E::kMaxT][4];
-    if constexpr (kForm == kWhole) {
+    [[maybe_unused]] double sums[kForm == kFormWhole ? kMaxParts : 1][Sink::E::kMaxT][4];
+    if constexpr (kForm == kFormWhole) {
       S.all = (item.y & kAllParts) != 0u;
       S.sum = sums;
       if (S.all) S.start_parts();
@@ -1081,11 +1081,11 @@ void k_walk_forces(const int32_t *__restrict__ gate, WalkArgs A) {
                                    kRel ? A.arel[g] : 0.0);
     // rows of kMaxGroup, not of the context's group size: a captured walk is
     // replayed on trees built with another one
-    const uint32_t slot0 = (kForm == kWhole ? item.y & ~kAllParts : item.y) >> 10;
+    const uint32_t slot0 = (kForm == kFormWhole ? item.y & ~kAllParts : item.y) >> 10;
     double4 *out = A.wpart + (size_t)(slot0 + part) * kMaxGroup;
-    const uint32_t rows = kForm == kWhole && S.all ? parts : 1u;
+    const uint32_t rows = kForm == kFormWhole && S.all ? parts : 1u;
     for (uint32_t r = 0; r < rows; ++r, out += kMaxGroup) {
-      if constexpr (kForm == kWhole) {
+      if constexpr (kForm == kFormWhole) {
         if (S.all) S.take_part((int)r);
         if (r > 0u) __syncthreads();   // the row before has been summed
       }
@@ -1434,6 +1434,7 @@ __device__ __forceinline__ uint64_t block_exclusive_scan64(uint64_t v, uint64_t 
   return base + x - v;
 }
 
+template <bool kWhole>
 __device__ __forceinline__ void order_items(TreeCounters *ctr, const uint32_t *__restrict__ alist,
                                             const uint32_t *__restrict__ acnt,
                                             const int32_t *__restrict__ n_act, int64_t n,
@@ -1451,7 +1452,7 @@ __device__ __forceinline__ void order_items(TreeCounters *ctr, const uint32_t *_
   const uint32_t targets = (uint32_t)(n_act ? min((int64_t)n_act[0], n) : n);
   const uint32_t per = max((uint32_t)kMinPart, (targets + want - 1u) / want);
   auto parts_of = [&](uint32_t nt) { return min((uint32_t)kMaxParts, (nt + per - 1u) / per); };
-  const bool one = G >= whole;      // a split group is one item
+  const uint32_t most = kWhole && G >= whole ? 1u : (uint32_t)kMaxParts;   // items of a group
   // the range's items of each class and slots
   uint32_t cnt[kSizeClasses + 1] = {};
   for (uint32_t p0 = lo + tid; p0 < hi; p0 += kOrderChunk) {
@@ -1466,7 +1467,7 @@ __device__ __forceinline__ void order_items(TreeCounters *ctr, const uint32_t *_
       if (p0 + j * kOrderThreads >= hi) continue;
       const uint32_t k = size_class(nt[j]), np = parts_of(nt[j]);
 #pragma unroll
-      for (uint32_t q = 0; q < kSizeClasses; ++q) cnt[q] += k == q ? (one ? min(np, 1u) : np) : 0u;
+      for (uint32_t q = 0; q < kSizeClasses; ++q) cnt[q] += k == q ? min(np, most) : 0u;
       cnt[kSizeClasses] += np > 1u ? np : 0u;
     }
   }
@@ -1521,7 +1522,7 @@ __device__ __forceinline__ void order_items(TreeCounters *ctr, const uint32_t *_
     for (uint32_t j = 0; j < kOrderItems; ++j) {
       if (r0 + j >= m) break;
       const uint32_t nt = s_n[r0 + j], np = parts_of(nt);
-      mine += (uint64_t)(one ? min(np, 1u) : np) << (16u * size_class(nt));
+      mine += (uint64_t)min(np, most) << (16u * size_class(nt));
       my_slots += np > 1u ? np : 0u;
     }
     uint64_t tot;
@@ -1539,13 +1540,13 @@ __device__ __forceinline__ void order_items(TreeCounters *ctr, const uint32_t *_
 #pragma unroll
       for (uint32_t q = 1; q < kSizeClasses; ++q) dst = k == q ? at[q] : dst;
 #pragma unroll
-      for (uint32_t q = 0; q < kSizeClasses; ++q) at[q] += k == q ? (one ? min(np, 1u) : np) : 0u;
+      for (uint32_t q = 0; q < kSizeClasses; ++q) at[q] += k == q ? min(np, most) : 0u;
       if (np == 1u) {
         items[dst] = make_uint2(g, 0u);
       } else {
         for (uint32_t e = 0; e < np; ++e) {
-          if (e == 0u || !one)
-            items[dst + e] = make_uint2(g, e | (np - 1u) << 5 | s0 << 10 | (one ? kAllParts : 0u));
+          const uint32_t all = kWhole && most == 1u ? kAllParts : 0u;
+          if (!kWhole || e < most) items[dst + e] = make_uint2(g, e | (np - 1u) << 5 | s0 << 10 | all);
           slots[s0 + e] = make_uint2(g, e == 0u ? np : 0u);
         }
         s0 += np;
@@ -1623,7 +1624,7 @@ __global__ __launch_bounds__(256) void k_rel_records(const int32_t *__restrict__
 // evaluation, 131072 stars 748 -> 731 us a step.
 constexpr int kRecordBlocks = 504;
 
-template <class R>
+template <class R, bool kWhole>
 __global__ __launch_bounds__(kOrderThreads) void k_walk_prepare(
     const int32_t *__restrict__ gate, TreeCounters *ctr, const uint32_t *__restrict__ alist,
     const uint32_t *__restrict__ acnt, const int32_t *__restrict__ n_act, int64_t n, uint32_t want,
@@ -1631,7 +1632,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_walk_prepare(
     const double *__restrict__ mom, double eps2, int spline, void *cell, RelArgs rel) {
   if (gate && *gate <= 0) return;   // nothing active: skipped
   if (blockIdx.x < 8u) {
-    order_items(ctr, alist, acnt, n_act, n, want, gap, whole, items, slots);
+    order_items<kWhole>(ctr, alist, acnt, n_act, n, want, gap, whole, items, slots);
     return;
   }
   const uint32_t v0 = (blockIdx.x - 8u) * kOrderThreads + threadIdx.x;
@@ -1768,12 +1769,12 @@ static void launch_force_kernel(tg_ctx *c, const WalkArgs &A, bool whole) {
   };
   const bool mixed = c->cfg.precision == TG_MIXED;
   if (whole)
-    return mixed ? go(k_walk_forces<true, kRel, kSpline, kWhole>)
-                 : go(k_walk_forces<false, kRel, kSpline, kWhole>);
-  if (mixed) return go(k_walk_forces<true, kRel, kSpline, kFull>);
+    return mixed ? go(k_walk_forces<true, kRel, kSpline, kFormWhole>)
+                 : go(k_walk_forces<false, kRel, kSpline, kFormWhole>);
+  if (mixed) return go(k_walk_forces<true, kRel, kSpline, kFormFull>);
   if constexpr (!kSpline)              // (with the spline two waves fill a SIMD anyway)
-    if (c->n < kEvenBelow) return go(k_walk_forces<false, kRel, false, kEven>);
-  go(k_walk_forces<false, kRel, kSpline, kFull>);
+    if (c->n < kEvenBelow) return go(k_walk_forces<false, kRel, false, kFormEven>);
+  go(k_walk_forces<false, kRel, kSpline, kFormFull>);
 }
 
 hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta, const int32_t *n_act,
@@ -1800,21 +1801,25 @@ hipError_t launch_walk_forces(tg_ctx *c, double eps, double theta, const int32_t
   // not depend on waves_per_cu
   const uint32_t want = (uint32_t)(kItemsPerWave * c->n_cu * walk_per_cu(c));
   const bool mixed = c->cfg.precision == TG_MIXED;
-  hipLaunchKernelGGL((mixed ? k_walk_prepare<float> : k_walk_prepare<double>),
-                     dim3(8 + kRecordBlocks), dim3(kOrderThreads), 0, c->stream, c->gate, b.ctr,
-                     b.alist, b.acnt, n_act, c->n, want, (uint32_t)c->split_cap,
-                     walk_whole(c) ? whole_from(c, A.starts) : ~0u, b.items, b.slots,
-                     b.mom, A.eps2, spline, (void *)b.cell, rel_args(c, rel));
+  const bool whole = walk_whole(c);
+  auto prepare = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(8 + kRecordBlocks), dim3(kOrderThreads), 0, c->stream, c->gate,
+                       b.ctr, b.alist, b.acnt, n_act, c->n, want, (uint32_t)c->split_cap,
+                       whole_from(c, A.starts), b.items, b.slots, b.mom, A.eps2, spline,
+                       (void *)b.cell, rel_args(c, rel));
+  };
+  if (mixed) whole ? prepare(k_walk_prepare<float, true>) : prepare(k_walk_prepare<float, false>);
+  else whole ? prepare(k_walk_prepare<double, true>) : prepare(k_walk_prepare<double, false>);
   if (before) {
     hipError_t e = hipEventRecord(before, c->stream);
     if (e != hipSuccess) return e;
   }
   if (spline) {
-    if (rel) launch_force_kernel<true, true>(c, A, walk_whole(c));
-    else launch_force_kernel<false, true>(c, A, walk_whole(c));
+    if (rel) launch_force_kernel<true, true>(c, A, whole);
+    else launch_force_kernel<false, true>(c, A, whole);
   } else {
-    if (rel) launch_force_kernel<true, false>(c, A, walk_whole(c));
-    else launch_force_kernel<false, false>(c, A, walk_whole(c));
+    if (rel) launch_force_kernel<true, false>(c, A, whole);
+    else launch_force_kernel<false, false>(c, A, whole);
   }
   if (spline)
     hipLaunchKernelGGL(k_walk_finish<true>, dim3(kFinishBlocks), dim3(kFinishThreads), 0, c->stream,
